@@ -212,8 +212,14 @@ __device__ __forceinline__ void mma_superstep_rho1(const u4 (&pa)[WM], const u4 
 // V = sum P_i P_j give the table:
 //   C11 = S,  C10 = 2T - S,  C01 = 2U - S,  C00 = 4V - 2T - 2U + S
 // (rho(0) = 2P - rho(1)); the general 2-way loop reaches them through the
-// cheaper plane U = rho(1) + 2 [missing] (planes32_f4u).  Fields past n_f
-// carry the missing code, which is zero in rho(1) and P.
+// cheaper planes U = rho(1) + 2 [missing] and M = [missing] (planes32_f4u).
+// Fields past n_f carry the missing code, which is zero in rho(1) and P.
+//
+// The MFMAs take no block scales (mfma_f4).  The form with scales of 1 is a
+// longer instruction that leaves less room for the VALU beside it: a loop of
+// independent MFMAs with two VALU operations each, two waves per SIMD, takes
+// 22.0 cycles per MFMA with scales and 17.9 without (17.1 and 16.8 with no
+// VALU operation; cycles of 2.4 GHz).
 // ---------------------------------------------------------------------------
 
 constexpr unsigned kEven2 = 0x55555555u;  // bit 0 of every 2-bit field
@@ -274,37 +280,36 @@ __device__ __forceinline__ unsigned (&pair_of(unsigned (&x)[4], int q))[2] {
 }
 
 // The 2-way planes U = rho(1) + 2 [missing] (codes 00, 01, 10, 11 -> 0, 1,
-// 2, 2) and P of 16 fields (one word w) as fp4 nibbles, in seven operations: even fields
-// in the low two bits of a nibble (e2m1 value = plane / 2), odd fields in
-// its middle two bits (value = plane; U = 2 is the pattern 0100, never 0110).
-// With s = w >> 1, h = s & kEven2 (hi at bit 0 of each field, 0 at bit 1)
-// and q = h >> 1, truth tables 0x20 = c & a & ~b and 0xA2 = c & (a | ~b):
-//   ue: bit 0 = lo & ~hi, bit 1 = hi         uo: the same at bits 1, 2
-//   pe: bit 0 = lo | ~hi                     po: the same at bit 1
-// Two words at once: the shifts s and q are taken on the 64-bit pair
-// (shr_pair: the bit that crosses from the upper word lands in bit 31 of the
-// lower one, which no mask keeps), six operations per word.
+// 2, 2) and M = [missing] of 32 fields (two words) as fp4 nibbles holding the
+// plane in their middle two bits (e2m1 value = plane: 0010 is 1, 0100 is 2; U
+// is never 0110): even fields in ue / me, odd ones in uo / mo.  With
+// d = w << 1, s = w >> 1, b = w & 0xAA.. (hi at bit 1 of each field, 0 at
+// bit 0) and q = b >> 2, truth table 0x20 = c & a & ~b, 0x08 = c & ~a & b:
+//   ue from (d, b), uo from (s, q): bit 1 = lo & ~hi, bit 2 = hi
+//   me from (d, b), mo from (s, q): bit 1 = ~lo & hi
+// Thirteen operations for the two words, the shifts taken on the 64-bit pair
+// (the bits that cross between the words land in bits 0, 30 (zero there) and
+// 31, which no mask keeps).  Both halves carry the same scale, so the MFMAs
+// need no block scales (see mfma_f4).
+constexpr unsigned kMid2 = 0x66666666u;    // middle two bits of every nibble
+constexpr unsigned kMid1 = 0x22222222u;    // bit 1 of every nibble
+constexpr unsigned kHiBits = 0xAAAAAAAAu;  // bit 1 of every 2-bit field
 __device__ __forceinline__ void planes32_f4u(unsigned w0, unsigned w1, unsigned (&ue)[2],
-                                             unsigned (&uo)[2], unsigned (&pe)[2],
-                                             unsigned (&po)[2]) {
-  unsigned s0, s1, q0, q1;
+                                             unsigned (&uo)[2], unsigned (&me)[2],
+                                             unsigned (&mo)[2]) {
+  unsigned d0, d1, s0, s1, q0, q1;
+  shl_pair<1>(w0, w1, d0, d1);
   shr_pair<1>(w0, w1, s0, s1);
-  const unsigned h0 = s0 & kEven2, h1 = s1 & kEven2;
-  shr_pair<1>(h0, h1, q0, q1);
-  ue[0] = __builtin_amdgcn_bitop3_b32(w0, h0, 0x33333333u, 0x20);
-  ue[1] = __builtin_amdgcn_bitop3_b32(w1, h1, 0x33333333u, 0x20);
-  uo[0] = __builtin_amdgcn_bitop3_b32(s0, q0, 0x66666666u, 0x20);
-  uo[1] = __builtin_amdgcn_bitop3_b32(s1, q1, 0x66666666u, 0x20);
-  pe[0] = __builtin_amdgcn_bitop3_b32(w0, s0, 0x11111111u, 0xA2);
-  pe[1] = __builtin_amdgcn_bitop3_b32(w1, s1, 0x11111111u, 0xA2);
-  po[0] = __builtin_amdgcn_bitop3_b32(s0, q0, 0x22222222u, 0xA2);
-  po[1] = __builtin_amdgcn_bitop3_b32(s1, q1, 0x22222222u, 0xA2);
-}
-
-// fp4 MFMA with both E8M0 scales 2^(e - 127).
-template <int e>
-__device__ __forceinline__ v4f mfma_f4s(const v8i& a, const v8i& b, v4f c) {
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, e, 0, e);
+  const unsigned b0 = w0 & kHiBits, b1 = w1 & kHiBits;
+  shr_pair<2>(b0, b1, q0, q1);
+  ue[0] = __builtin_amdgcn_bitop3_b32(d0, b0, kMid2, 0x20);
+  ue[1] = __builtin_amdgcn_bitop3_b32(d1, b1, kMid2, 0x20);
+  uo[0] = __builtin_amdgcn_bitop3_b32(s0, q0, kMid2, 0x20);
+  uo[1] = __builtin_amdgcn_bitop3_b32(s1, q1, kMid2, 0x20);
+  me[0] = __builtin_amdgcn_bitop3_b32(d0, b0, kMid1, 0x08);
+  me[1] = __builtin_amdgcn_bitop3_b32(d1, b1, kMid1, 0x08);
+  mo[0] = __builtin_amdgcn_bitop3_b32(s0, q0, kMid1, 0x08);
+  mo[1] = __builtin_amdgcn_bitop3_b32(s1, q1, kMid1, 0x08);
 }
 
 // rho(1) of 16 fields; `complete` words hold no missing code, where
@@ -347,69 +352,71 @@ __device__ __forceinline__ v8i operand_f4(const unsigned (&x0)[2], const unsigne
 }
 
 __device__ __forceinline__ v4f mfma_f4(const v8i& a, const v8i& b, v4f c) {
-  // formats 4 = e2m1 for A and B; E8M0 scales 127 = 2^0
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 127, 0, 127);
+  // formats 4 = e2m1 for A and B; zero scale operands: the unscaled form
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
 }
 
 __device__ __forceinline__ int f4_count(float x) { return (int)(4.0f * x); }
 
-// Table (entry 2a+b) from the four sums of the U and P planes
-// (planes32_f4u) over the K fields of the loop: rho(1) = U + 2P - 2 gives
-//   S = UU + 2UP + 2PU + 4PP - 2 n_i(1) - 2 n_j(1) - 4K,
-//   T = UP + 2PP - 2 m_j,  U' = PU + 2PP - 2 m_i,  V = PP
-// (sum_q U_i = n_i(1) + 2 (K - m_i), sum_q P_i = m_i).
-__device__ __forceinline__ v4i table_f4u(float uu, float up, float pu, float pp, const v4i& ci,
+// Table (entry 2a+b) from the four sums of the U and M planes
+// (planes32_f4u) over the K fields of the loop (fields past n_f are missing
+// ones): rho(1) = U - 2M and P = 1 - M give
+//   S  = sum rho_i rho_j = UU - 2 UM - 2 MU + 4 MM,
+//   T  = sum rho_i P_j   = n_i(1) - UM + 2 MM,
+//   U' = sum P_i rho_j   = n_j(1) - MU + 2 MM,
+//   V  = sum P_i P_j     = m_i + m_j - K + MM
+// (sum_q rho_i = n_i(1), sum_q M_i = K - m_i).
+__device__ __forceinline__ v4i table_f4u(float uu, float um, float mu, float mm, const v4i& ci,
                                          const v4i& cj, int kpad) {
-  const int UU = f4_count(uu), UP = f4_count(up), PU = f4_count(pu), PP = f4_count(pp);
-  const int S = UU + 2 * UP + 2 * PU + 4 * PP - 2 * ci.y - 2 * cj.y - 4 * kpad;
-  const int T = UP + 2 * PP - 2 * cj.z, U = PU + 2 * PP - 2 * ci.z, V = PP;
+  const int UU = (int)uu, UM = (int)um, MU = (int)mu, MM = (int)mm;
+  const int S = UU - 2 * UM - 2 * MU + 4 * MM;
+  const int T = ci.y - UM + 2 * MM, U = cj.y - MU + 2 * MM, V = ci.z + cj.z - kpad + MM;
   return v4i{4 * V - 2 * T - 2 * U + S, 2 * U - S, 2 * T - S, S};
 }
 
-// One 256-field super-step of the four sums of the U and P planes
+// One 256-field super-step of the four sums of the U and M planes
 // (planes32_f4u): the MFMA step of the even fields of the lane's four words,
-// then the one of the odd fields, whose nibble values are twice as large
-// (scales 2^-1 on A and B).
+// then the one of the odd fields.
 template <int WM, int WN>
 __device__ __forceinline__ void mma_superstep_f4u(const u4 (&xa)[WM], const u4 (&xb)[WN],
                                                   v4f (&acc)[WM][WN][4]) {
-  v8i bu[2][WN], bp[2][WN];
+  v8i bu[2][WN], bm[2][WN];
 #pragma unroll
   for (int n = 0; n < WN; ++n) {
-    unsigned ue[4], uo[4], pe[4], po[4];
+    unsigned ue[4], uo[4], me[4], mo[4];
 #pragma unroll
     for (int q = 0; q < 4; q += 2)
       planes32_f4u(word_of(xb[n], q), word_of(xb[n], q + 1), pair_of(ue, q), pair_of(uo, q),
-                   pair_of(pe, q), pair_of(po, q));
+                   pair_of(me, q), pair_of(mo, q));
     bu[0][n] = v8i{(int)ue[0], (int)ue[1], (int)ue[2], (int)ue[3], 0, 0, 0, 0};
     bu[1][n] = v8i{(int)uo[0], (int)uo[1], (int)uo[2], (int)uo[3], 0, 0, 0, 0};
-    bp[0][n] = v8i{(int)pe[0], (int)pe[1], (int)pe[2], (int)pe[3], 0, 0, 0, 0};
-    bp[1][n] = v8i{(int)po[0], (int)po[1], (int)po[2], (int)po[3], 0, 0, 0, 0};
+    bm[0][n] = v8i{(int)me[0], (int)me[1], (int)me[2], (int)me[3], 0, 0, 0, 0};
+    bm[1][n] = v8i{(int)mo[0], (int)mo[1], (int)mo[2], (int)mo[3], 0, 0, 0, 0};
   }
 #pragma unroll
   for (int m = 0; m < WM; ++m) {
-    unsigned ue[4], uo[4], pe[4], po[4];
+    unsigned ue[4], uo[4], me[4], mo[4];
 #pragma unroll
     for (int q = 0; q < 4; q += 2)
       planes32_f4u(word_of(xa[m], q), word_of(xa[m], q + 1), pair_of(ue, q), pair_of(uo, q),
-                   pair_of(pe, q), pair_of(po, q));
+                   pair_of(me, q), pair_of(mo, q));
     const v8i au0{(int)ue[0], (int)ue[1], (int)ue[2], (int)ue[3], 0, 0, 0, 0};
-    const v8i ap0{(int)pe[0], (int)pe[1], (int)pe[2], (int)pe[3], 0, 0, 0, 0};
+    const v8i am0{(int)me[0], (int)me[1], (int)me[2], (int)me[3], 0, 0, 0, 0};
     const v8i au1{(int)uo[0], (int)uo[1], (int)uo[2], (int)uo[3], 0, 0, 0, 0};
-    const v8i ap1{(int)po[0], (int)po[1], (int)po[2], (int)po[3], 0, 0, 0, 0};
+    const v8i am1{(int)mo[0], (int)mo[1], (int)mo[2], (int)mo[3], 0, 0, 0, 0};
 #pragma unroll
     for (int n = 0; n < WN; ++n) {
-      acc[m][n][0] = mfma_f4s<127>(au0, bu[0][n], acc[m][n][0]);
-      acc[m][n][1] = mfma_f4s<127>(au0, bp[0][n], acc[m][n][1]);
-      acc[m][n][2] = mfma_f4s<127>(ap0, bu[0][n], acc[m][n][2]);
-      acc[m][n][3] = mfma_f4s<127>(ap0, bp[0][n], acc[m][n][3]);
+      acc[m][n][0] = mfma_f4(au0, bu[0][n], acc[m][n][0]);
+      acc[m][n][1] = mfma_f4(au0, bm[0][n], acc[m][n][1]);
+      acc[m][n][2] = mfma_f4(am0, bu[0][n], acc[m][n][2]);
+      acc[m][n][3] = mfma_f4(am0, bm[0][n], acc[m][n][3]);
     }
 #pragma unroll
     for (int n = 0; n < WN; ++n) {
-      acc[m][n][0] = mfma_f4s<126>(au1, bu[1][n], acc[m][n][0]);
-      acc[m][n][1] = mfma_f4s<126>(au1, bp[1][n], acc[m][n][1]);
-      acc[m][n][2] = mfma_f4s<126>(ap1, bu[1][n], acc[m][n][2]);
-      acc[m][n][3] = mfma_f4s<126>(ap1, bp[1][n], acc[m][n][3]);
+      acc[m][n][0] = mfma_f4(au1, bu[1][n], acc[m][n][0]);
+      acc[m][n][1] = mfma_f4(au1, bm[1][n], acc[m][n][1]);
+      acc[m][n][2] = mfma_f4(am1, bu[1][n], acc[m][n][2]);
+      acc[m][n][3] = mfma_f4(am1, bm[1][n], acc[m][n][3]);
     }
   }
 }
