@@ -7,7 +7,12 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <stdlib.h>
+
+#include <atomic>
+#include <functional>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "../../include/ccc.h"
@@ -25,13 +30,34 @@ constexpr int64_t kMaxLd = int64_t(1) << 28;
 // the general path.
 constexpr int64_t kGramMaxRows = 32768;
 
+// Largest operand layout (operands.hip) a call keeps in the workspace; beyond
+// it the fp4 kernels read the packed rows.  $CCC_OPERAND_LIMIT (bytes)
+// overrides it.
+constexpr int64_t kOperandLimit = int64_t(16) << 30;
+
+// Workspaces: one buffer per (device, stream), so that calls on different
+// streams never share scratch.  A call holds g_mu while it enqueues its
+// kernels, so that calls of several threads on one stream do not interleave.
+// Buffers used under stream capture are pinned: a graph holds their address,
+// so they are given back by ccc_release_workspace alone.
 struct Workspace {
+  int dev = 0;
+  hipStream_t stream = nullptr;
+  size_t thread = 0;  // of hipStreamPerThread, which names a stream per thread
   void* ptr = nullptr;
   size_t bytes = 0;
+  bool pinned = false;
+  uint64_t last_use = 0;
 };
+constexpr size_t kMaxWorkspaces = 16;  // per device, pinned ones aside
 
 std::mutex g_mu;
-std::vector<Workspace> g_ws;  // indexed by device ordinal
+std::vector<Workspace> g_ws;
+std::vector<Workspace> g_retired;  // outgrown while pinned or under capture
+uint64_t g_clock = 0;
+
+// Identity of a call in the complete-data flag (Pair2Args::flag).
+std::atomic<unsigned long long> g_call{1};
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -61,6 +87,13 @@ int use_fp4(const ccc_opts& o, int64_t n_f) {
 // Compared by division first, so that no product of a huge n_f overflows.
 bool fields_in_range(int64_t n_f, int64_t mult) { return n_f <= kInt32Max / mult; }
 
+size_t round256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+int64_t operand_limit() {
+  const char* env = getenv("CCC_OPERAND_LIMIT");
+  return env && *env ? atoll(env) : kOperandLimit;
+}
+
 int check_input(const uint8_t* v, int64_t n, int64_t n_f, int64_t ld) {
   if (n < 0 || n_f < 0 || ld < 0) return CCC_ERR_ARG;
   if (n > kInt32Max) return CCC_ERR_ARG;
@@ -76,28 +109,106 @@ int check_input(const uint8_t* v, int64_t n, int64_t n_f, int64_t ld) {
 
 namespace ccc {
 
-// Workspace of at least `bytes` on the current device (grown on demand).
-int workspace(size_t bytes, void** out) {
+namespace {
+
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
+}
+
+// hipMalloc that is also allowed while a stream of this thread is captured.
+void* allocate(size_t bytes, bool capture) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (capture && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    p = nullptr;
+  }
+  if (capture) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return p;
+}
+
+// Free every unpinned buffer of `dev` except index `keep` (waits for the
+// device); all: also those that only the bound on their number would evict.
+void free_idle(int dev, size_t keep) {
+  if (hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  for (size_t i = 0; i < g_ws.size(); ++i)
+    if (i != keep && g_ws[i].dev == dev && !g_ws[i].pinned && g_ws[i].ptr) {
+      (void)hipFree(g_ws[i].ptr);
+      g_ws[i].ptr = nullptr;
+      g_ws[i].bytes = 0;
+    }
+}
+
+}  // namespace
+
+// A workspace of at least `bytes` for `stream` on the current device (grown
+// on demand); `lock` is held until the caller has enqueued its work.
+int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lock, void** out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return CCC_ERR_HIP;
-  std::lock_guard<std::mutex> lk(g_mu);
-  if ((int)g_ws.size() <= dev) g_ws.resize(dev + 1);
-  Workspace& w = g_ws[dev];
-  if (w.bytes < bytes) {
-    if (w.ptr) {
+  const size_t thread =
+      stream == hipStreamPerThread ? std::hash<std::thread::id>()(std::this_thread::get_id()) : 0;
+  if (!lock.owns_lock()) lock = std::unique_lock<std::mutex>(g_mu);
+  size_t at = g_ws.size(), mine = 0, oldest = g_ws.size();
+  for (size_t i = 0; i < g_ws.size(); ++i) {
+    const Workspace& w = g_ws[i];
+    if (w.dev != dev) continue;
+    if (w.stream == stream && w.thread == thread) at = i;
+    else if (!w.pinned) {
+      ++mine;
+      if (oldest == g_ws.size() || w.last_use < g_ws[oldest].last_use) oldest = i;
+    }
+  }
+  const bool fits = at < g_ws.size() && g_ws[at].bytes >= bytes;
+  const bool capture = (!fits || !g_ws[at].pinned) && capturing(stream);
+  if (at == g_ws.size()) {
+    if (mine >= kMaxWorkspaces && !capture && hipDeviceSynchronize() == hipSuccess) {
+      if (g_ws[oldest].ptr) (void)hipFree(g_ws[oldest].ptr);
+      g_ws[oldest] = Workspace{};
+      at = oldest;
+    } else {
+      g_ws.push_back(Workspace{});
+    }
+    g_ws[at].dev = dev;
+    g_ws[at].stream = stream;
+    g_ws[at].thread = thread;
+  }
+  Workspace& w = g_ws[at];
+  if (!fits) {
+    if (w.ptr && (w.pinned || capture)) {
+      g_retired.push_back(w);
+      w.ptr = nullptr;
+    } else if (w.ptr) {
       // the old buffer may still be in use by enqueued work
       if (hipDeviceSynchronize() != hipSuccess) return CCC_ERR_HIP;
       (void)hipFree(w.ptr);
       w.ptr = nullptr;
-      w.bytes = 0;
     }
-    size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
-    if (hipMalloc(&w.ptr, want) != hipSuccess) {
-      (void)hipGetLastError();
-      return CCC_ERR_NOMEM;
+    w.bytes = 0;
+    w.pinned = false;
+    const size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
+    w.ptr = allocate(want, capture);
+    if (!w.ptr && !capture) {
+      free_idle(dev, at);
+      w.ptr = allocate(want, false);
     }
+    if (!w.ptr) return CCC_ERR_NOMEM;
     w.bytes = want;
   }
+  w.pinned = w.pinned || capture;
+  w.last_use = ++g_clock;
   *out = w.ptr;
   return CCC_OK;
 }
@@ -171,28 +282,19 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   unsigned long long* zero = sel ? sel->count : nullptr;
   const int64_t row_end = i_end < n_v - 1 ? i_end : n_v - 1;  // the last row has no pair
   if (row_end <= i_begin && !counts && !zero) return CCC_OK;  // nothing to compute or write
+  std::unique_lock<std::mutex> lock;
   if (n_v == 1) {
     if (!counts && !zero) return CCC_OK;
     if (!counts) {  // only the selection counter to clear
       void* ws = nullptr;
-      if ((st = ccc::workspace(16, &ws))) return st;
+      if ((st = ccc::workspace(16, stream, lock, &ws))) return st;
       counts = static_cast<int32_t*>(ws);
     }
     return ccc::launch_count1_zero(v, ld, n_v, n_f, counts, 0, zero, stream) == hipSuccess
                ? CCC_OK
                : CCC_ERR_HIP;
   }
-  // workspace: the counts (unless the caller's), then the MFMA path's
-  // complete-data flag
-  const size_t cnt_bytes = counts ? 0 : ((size_t)n_v * 16 + 255) / 256 * 256;
-  void* ws = nullptr;
-  if ((st = ccc::workspace(cnt_bytes + 256, &ws))) return st;
-  int32_t* cnt = counts ? counts : static_cast<int32_t*>(ws);
-  if (ccc::launch_count1_zero(v, ld, n_v, n_f, cnt, 0, zero, stream) != hipSuccess)
-    return CCC_ERR_HIP;
-  if (row_end <= i_begin) return CCC_OK;
   ccc::Pair2Args a{};
-  a.complete = reinterpret_cast<int*>(static_cast<char*>(ws) + cnt_bytes);
   a.va = v; a.lda = ld; a.n_a = n_v;
   a.vb = v; a.ldb = ld; a.n_b = n_v;
   a.n_f = n_f;
@@ -201,16 +303,55 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   a.accumulate = 0;
   a.tables = tables;
   a.ccc = ccc;
-  a.counts_a = cnt;
-  a.counts_b = cnt;
-  a.chunk_a = cnt;
-  a.chunk_b = cnt;
   a.gamma = o.gamma;
   a.row_begin = i_begin;
   a.row_end = row_end;
   a.p_base = i_begin * n_v - i_begin * (i_begin + 1) / 2;  // p(i_begin, i_begin + 1)
   a.sel = sel ? ccc::Select{sel->count, sel->cap, threshold, sel->index, sel->ccc, sel->tables}
               : ccc::Select{nullptr, 0, 0.0, nullptr, nullptr, nullptr};
+  // workspace: the MFMA path's complete-data flag, the counts (unless the
+  // caller's), and on fp4 the operands and the partial sums of split tiles
+  const bool have_pairs = row_end > i_begin;
+  const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 16);
+  const size_t head = 256 + cnt_bytes;
+  void* ws = nullptr;
+  bool operands = f4 && have_pairs && ccc::operand_bytes(n_v, n_f) <= operand_limit();
+  size_t op_bytes = 0;
+  if (operands) {
+    a.steps = ccc::operand_steps(n_f);
+    op_bytes = (size_t)ccc::operand_bytes(n_v, n_f);
+    a.part_bytes = ccc::mfma2_part_bytes(a);
+    // the pre-pass is done with its part when the tiles write theirs
+    const size_t pre_bytes = ccc::operand_part_bytes(n_v, n_f);
+    st = ccc::workspace(head + op_bytes + (pre_bytes > a.part_bytes ? pre_bytes : a.part_bytes),
+                        stream, lock, &ws);
+    if (st == CCC_ERR_NOMEM) operands = false;  // the packed rows do
+    else if (st) return st;
+  }
+  if (!operands && (st = ccc::workspace(head, stream, lock, &ws))) return st;
+  char* wsb = static_cast<char*>(ws);
+  int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 256);
+  a.counts_a = a.counts_b = a.chunk_a = a.chunk_b = cnt;
+  a.flag = reinterpret_cast<unsigned long long*>(wsb);
+  a.id = g_call++;
+  if (operands) {
+    a.za = a.zb = wsb + head;
+    a.part = wsb + head + op_bytes;
+    ccc::OperandJob job{};
+    job.set[0] = ccc::OperandSet{v, ld, n_v, (uint32_t)ccc::operand_blocks(n_v), wsb + head, cnt,
+                                 nullptr};
+    job.n_f = n_f;
+    job.steps = a.steps;
+    job.zero = zero;
+    job.flag = a.flag;
+    job.id = a.id;
+    job.shares = ccc::operand_shares(n_v, n_f);
+    job.part = static_cast<int2*>(a.part);
+    if (ccc::launch_operands(job, stream) != hipSuccess) return CCC_ERR_HIP;
+  } else if (ccc::launch_count1_zero(v, ld, n_v, n_f, cnt, 0, zero, stream) != hipSuccess) {
+    return CCC_ERR_HIP;
+  }
+  if (!have_pairs) return CCC_OK;
   return ccc::run_pair2(a, o.path, stream);
 }
 
@@ -303,7 +444,9 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
   }
   const size_t gram_bytes = use_gram ? (size_t)ng * (size_t)ng * 4 : 0;
   void* ws = nullptr;
-  if ((st = fixed ? noalloc_scratch(&ws) : ccc::workspace(head_bytes + gram_bytes, &ws)))
+  std::unique_lock<std::mutex> lock;
+  if ((st = fixed ? noalloc_scratch(&ws)
+                  : ccc::workspace(head_bytes + gram_bytes, stream, lock, &ws)))
     return st;
   char* wsb = static_cast<char*>(ws);
   int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 2 * offs_bytes + gen_bytes);
@@ -405,23 +548,6 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
   if (!aligned16(tables) || !aligned16(ccc) || !aligned16(counts_a) || !aligned16(counts_b))
     return CCC_ERR_ALIGN;
   if (n_a == 0 || n_b == 0) return CCC_OK;
-  // workspace: an accumulating call's own chunk counts, or else the MFMA
-  // path's complete-data flag
-  int32_t* chunk_a = counts_a;
-  int32_t* chunk_b = counts_b;
-  void* ws = nullptr;
-  if ((st = ccc::workspace(acc ? (size_t)(n_a + n_b) * 16 : 256, &ws))) return st;
-  if (acc) {
-    chunk_a = static_cast<int32_t*>(ws);
-    chunk_b = chunk_a + 4 * n_a;
-    if (ccc::launch_count1(va, lda, n_a, n_f, chunk_a, 0, stream) != hipSuccess ||
-        ccc::launch_count1(vb, ldb, n_b, n_f, chunk_b, 0, stream) != hipSuccess)
-      return CCC_ERR_HIP;
-  }
-  if (ccc::launch_count1(va, lda, n_a, n_f, counts_a, acc, stream) != hipSuccess)
-    return CCC_ERR_HIP;
-  if (ccc::launch_count1(vb, ldb, n_b, n_f, counts_b, acc, stream) != hipSuccess)
-    return CCC_ERR_HIP;
   ccc::Pair2Args a{};
   a.va = va; a.lda = lda; a.n_a = n_a;
   a.vb = vb; a.ldb = ldb; a.n_b = n_b;
@@ -433,14 +559,57 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
   a.ccc = fin ? ccc : nullptr;
   a.counts_a = counts_a;
   a.counts_b = counts_b;
-  a.chunk_a = chunk_a;
-  a.chunk_b = chunk_b;
   a.gamma = o.gamma;
   a.row_begin = 0;
   a.row_end = n_a;
   a.p_base = 0;
   a.sel = ccc::Select{nullptr, 0, 0.0, nullptr, nullptr, nullptr};
-  a.complete = acc ? nullptr : static_cast<int*>(ws);
+  // workspace: the MFMA path's complete-data flag, an accumulating call's own
+  // chunk counts, and on fp4 the operands of both sides and the partial sums
+  // of split tiles
+  const size_t cnt_bytes = acc ? round256((size_t)(n_a + n_b) * 16) : 0, head = 256 + cnt_bytes;
+  const size_t op_a = (size_t)ccc::operand_bytes(n_a, n_f), op_b = (size_t)ccc::operand_bytes(n_b, n_f);
+  bool operands = f4 && (int64_t)(op_a + op_b) <= operand_limit();
+  std::unique_lock<std::mutex> lock;
+  void* ws = nullptr;
+  if (operands) {
+    a.steps = ccc::operand_steps(n_f);
+    a.part_bytes = ccc::mfma2_part_bytes(a);
+    st = ccc::workspace(head + op_a + op_b + a.part_bytes, stream, lock, &ws);
+    if (st == CCC_ERR_NOMEM) operands = false;  // the packed rows do
+    else if (st) return st;
+  }
+  if (!operands && (st = ccc::workspace(head, stream, lock, &ws))) return st;
+  char* wsb = static_cast<char*>(ws);
+  int32_t* chunk_a = acc ? reinterpret_cast<int32_t*>(wsb + 256) : counts_a;
+  int32_t* chunk_b = acc ? chunk_a + 4 * n_a : counts_b;
+  a.chunk_a = chunk_a;
+  a.chunk_b = chunk_b;
+  a.flag = acc ? nullptr : reinterpret_cast<unsigned long long*>(wsb);
+  a.id = g_call++;
+  if (operands) {
+    a.za = wsb + head;
+    a.zb = wsb + head + op_a;
+    a.part = wsb + head + op_a + op_b;
+    ccc::OperandJob job{};
+    job.set[0] = ccc::OperandSet{va, lda, n_a, (uint32_t)ccc::operand_blocks(n_a), wsb + head,
+                                 counts_a, acc ? chunk_a : nullptr};
+    job.set[1] = ccc::OperandSet{vb, ldb, n_b, (uint32_t)ccc::operand_blocks(n_b),
+                                 wsb + head + op_a, counts_b, acc ? chunk_b : nullptr};
+    job.n_f = n_f;
+    job.steps = a.steps;
+    job.accumulate = acc ? 1 : 0;
+    job.flag = a.flag;
+    job.id = a.id;
+    if (ccc::launch_operands(job, stream) != hipSuccess) return CCC_ERR_HIP;
+  } else {
+    if (acc && (ccc::launch_count1(va, lda, n_a, n_f, chunk_a, 0, stream) != hipSuccess ||
+                ccc::launch_count1(vb, ldb, n_b, n_f, chunk_b, 0, stream) != hipSuccess))
+      return CCC_ERR_HIP;
+    if (ccc::launch_count1(va, lda, n_a, n_f, counts_a, acc, stream) != hipSuccess ||
+        ccc::launch_count1(vb, ldb, n_b, n_f, counts_b, acc, stream) != hipSuccess)
+      return CCC_ERR_HIP;
+  }
   return ccc::run_pair2(a, o.path, stream);
 }
 
@@ -465,10 +634,11 @@ int ccc_2way_multi(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int s
   if (f4 < 0) return f4;
   if (n_v >= 2 && !tables && !ccc) return CCC_ERR_ARG;
   if (n_v == 0 || (n_v == 1 && !counts)) return CCC_OK;
+  std::unique_lock<std::mutex> lock;
   int32_t* cnt = counts;
   if (!cnt) {
     void* ws = nullptr;
-    if ((st = ccc::workspace((size_t)n_v * 32, &ws))) return st;
+    if ((st = ccc::workspace((size_t)n_v * 32, stream, lock, &ws))) return st;
     cnt = static_cast<int32_t*>(ws);
   }
   if (ccc::launch_multi_count(v, ld, n_v, n_f, s, cnt, stream) != hipSuccess) return CCC_ERR_HIP;
@@ -513,13 +683,15 @@ void ccc_release_workspace(void) {
   std::lock_guard<std::mutex> lk(g_mu);
   int cur = 0;
   bool have_cur = hipGetDevice(&cur) == hipSuccess;
-  for (size_t d = 0; d < g_ws.size(); ++d) {
-    if (!g_ws[d].ptr) continue;
-    if (hipSetDevice((int)d) == hipSuccess) {
-      (void)hipDeviceSynchronize();
-      (void)hipFree(g_ws[d].ptr);
+  for (auto* list : {&g_ws, &g_retired}) {
+    for (const Workspace& w : *list) {
+      if (!w.ptr) continue;
+      if (hipSetDevice(w.dev) == hipSuccess) {
+        (void)hipDeviceSynchronize();
+        (void)hipFree(w.ptr);
+      }
     }
-    g_ws[d] = Workspace{};
+    list->clear();
   }
   if (have_cur) (void)hipSetDevice(cur);
 }

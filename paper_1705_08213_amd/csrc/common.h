@@ -136,15 +136,18 @@ __device__ __forceinline__ void pair_ccc(v4i t, const double (&wi)[2], const dou
 __device__ __forceinline__ void store_pair(int64_t p, v4i t, const double (&wi)[2],
                                            const double (&wj)[2], int32_t* __restrict__ tables,
                                            double* __restrict__ ccc) {
-  // streaming stores: the dense output is written once and not read back here
+  // streaming stores for the tables, where an instruction covers whole
+  // stretches of 256 bytes; plain ones for the CCC rows, of which it writes
+  // every other 16 bytes and L2 has to join the two halves (a store-only
+  // kernel of this shape: 1.6 TB/s streaming, 4.8 plain)
   if (tables) __builtin_nontemporal_store(t, reinterpret_cast<v4i*>(tables + 4 * p));
   if (ccc) {
     double r[4];
     pair_ccc(t, wi, wj, r);
     typedef double d2 __attribute__((ext_vector_type(2)));
     d2* out = reinterpret_cast<d2*>(ccc + 4 * p);
-    __builtin_nontemporal_store(d2{r[0], r[1]}, out);
-    __builtin_nontemporal_store(d2{r[2], r[3]}, out + 1);
+    out[0] = d2{r[0], r[1]};
+    out[1] = d2{r[2], r[3]};
   }
 }
 
@@ -161,6 +164,20 @@ __device__ __forceinline__ int64_t select_slot(bool keep, unsigned long long* co
   base = __shfl(base, leader);
   if (!keep) return -1;
   return (int64_t)(base + (unsigned long long)__popcll(mask & ((1ull << lane) - 1ull)));
+}
+
+// One record of a selection: pair index p, CCC values r and table t, for the
+// lanes that keep theirs; every lane of the wave must call it.
+__device__ __forceinline__ void select_pair(const Select& sel, bool keep, int64_t p, v4i t,
+                                            const double (&r)[4]) {
+  const int64_t slot = select_slot(keep, sel.count);
+  if (slot >= 0 && slot < sel.cap) {
+    sel.index[slot] = p;
+    double2* c = reinterpret_cast<double2*>(sel.ccc + 4 * slot);
+    c[0] = double2{r[0], r[1]};
+    c[1] = double2{r[2], r[3]};
+    if (sel.tables) *reinterpret_cast<v4i*>(sel.tables + 4 * slot) = t;
+  }
 }
 
 }  // namespace ccc

@@ -44,11 +44,45 @@ struct Pair2Args {
   int64_t p_base;
   int64_t sq_offset;          // first square tile of the row range (triangle)
   Select sel;                 // threshold selection (sel.count != null) instead of dense output
-  // Device flag (one int) that launch_mfma2 sets to 1 when every row of A and
-  // B has all n_f fields present, 0 otherwise; null: no such check (each
-  // workgroup tile votes for itself).  Only for calls that do not accumulate.
-  int* complete;
+  // Device flag that holds `id` when some row of A or B misses an entry (any
+  // other value: every row has all n_f fields present); null: no such check
+  // (each tile votes for itself).  Only for calls that do not accumulate.
+  unsigned long long* flag;
+  unsigned long long id;
+  // The rows as operands (operands.hip), in super-steps of 256 fields; null:
+  // the kernels read the packed rows.
+  const void* za;
+  const void* zb;
+  int64_t steps;
+  // Workspace for the partial sums of field-split tiles, and its size
+  void* part;
+  size_t part_bytes;
 };
+
+// Rows for which the pre-pass of the fp4 kernels writes operands and counts.
+struct OperandSet {
+  const uint8_t* v;
+  int64_t ld, n;
+  uint32_t blocks;  // (n + 15) / 16, or 0: no such set
+  void* z;          // [blocks][steps][1024 bytes]
+  int32_t* counts;  // [n][4] or null; added to when accumulating
+  int32_t* chunk;   // [n][4] or null: this call's own counts
+};
+struct OperandJob {
+  OperandSet set[2];
+  int64_t n_f, steps;  // steps = ceil(n_f / 256)
+  int accumulate;
+  unsigned long long* zero;  // a counter to clear, or null
+  unsigned long long* flag;  // set to `id` when some row misses an entry, or null
+  unsigned long long id;
+  int shares;  // workgroups along the fields of a block (one set only; see below)
+  int2* part;  // [shares][n]: their counts, when shares > 1
+};
+inline int64_t operand_steps(int64_t n_f) { return (n_f + 255) / 256; }
+inline int64_t operand_blocks(int64_t n) { return (n + 15) / 16; }
+inline int64_t operand_bytes(int64_t n, int64_t n_f) {
+  return operand_blocks(n) * operand_steps(n_f) * 1024;
+}
 
 // Largest n_f for which the MFMA kernels may take fp4 operands (their fp32
 // sums of quarter-multiples, at most n_f, stay exact); int8 beyond.
@@ -235,6 +269,8 @@ struct TuneChoice {
   int variant;    // tile variant, in [0, n_variants)
   int wg_per_cu;  // persistent workgroups per compute unit; 0: the launcher's default
 };
+// The one-shot variant that the environment forces (0 .. n_variants - 1), or -1.
+int tune_forced_oneshot(int n_variants);
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants);
 
 // Optional event timing around the main kernel of a launcher (no-ops unless
@@ -250,6 +286,23 @@ hipError_t launch_count1(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, i
 hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f,
                               int32_t* counts, int accumulate, unsigned long long* zero,
                               hipStream_t stream);
+hipError_t launch_operands(OperandJob job, hipStream_t stream);
+// Shares of the fields for the pass over one set: few blocks of long rows are
+// bound by the memory path of the few CUs that hold them (24 blocks x 977
+// super-steps: 39 us in one share), but the counts' second launch costs 5 us.
+inline int operand_shares(int64_t n, int64_t n_f) {
+  const int64_t blocks = operand_blocks(n), steps = operand_steps(n_f);
+  if (blocks <= 0 || blocks > 128 || steps < 256) return 1;
+  const int64_t a = 512 / blocks, b = steps / 32, s = a < b ? a : b;
+  return (int)(s < 16 ? s : 16);
+}
+inline size_t operand_part_bytes(int64_t n, int64_t n_f) {
+  const int s = operand_shares(n, n_f);
+  return s > 1 ? ((size_t)s * n * sizeof(int2) + 255) / 256 * 256 : 0;
+}
+// Bytes of partial sums that launch_mfma2 wants for a call (0: it will not
+// split the fields).
+size_t mfma2_part_bytes(const Pair2Args& a);
 hipError_t launch_pop2(const Pair2Args& a, hipStream_t stream);
 hipError_t launch_mfma2(const Pair2Args& a, hipStream_t stream);
 hipError_t launch_mfma3(const Triple3Args& a, hipStream_t stream);

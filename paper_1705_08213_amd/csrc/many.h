@@ -5,7 +5,6 @@
 
 namespace ccc {
 
-int workspace(size_t bytes, void** out);
 // f4: fp4 operands for the MFMA path (the caller checked that every n_f
 // allows them), else int8.
 int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f4,

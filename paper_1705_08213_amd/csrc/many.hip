@@ -112,7 +112,12 @@ __device__ __forceinline__ Pair2Args pair_args(const ProbDesc& p, double gamma) 
   a.p_base = 0;
   a.sq_offset = 0;
   a.sel = Select{nullptr, 0, 0.0, nullptr, nullptr, nullptr};
-  a.complete = nullptr;
+  a.flag = nullptr;
+  a.id = 0;
+  a.za = a.zb = nullptr;
+  a.steps = 0;
+  a.part = nullptr;
+  a.part_bytes = 0;
   return a;
 }
 

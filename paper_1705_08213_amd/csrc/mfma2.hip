@@ -1,41 +1,48 @@
 // mfma2.hip -- 2-way tallies on the matrix cores (fp4 or int8 operands): the
-// one-shot kernel over the triangle (ccc_2way) or the rectangle
-// (ccc_2way_block).  The tile body and its design notes are in tile2.h.
+// one-shot kernels over the triangle (ccc_2way) or the rectangle
+// (ccc_2way_block).  The tile bodies and their design notes are in tile2o.h
+// (fp4, on the operands of the pre-pass) and tile2.h (packed rows: int8, and
+// fp4 where the operands find no room).
+#include <stdlib.h>
+
 #include "tile2.h"
+#include "tile2o.h"
 
 namespace ccc {
 
 namespace {
 
-// *flag = 1 if every row of A and B has all n_f fields present (one
-// workgroup; its threads read the counts with a stride).
+// *flag = id if some row of A or B misses an entry, else 0 (one workgroup;
+// its threads read the counts with a stride).  For calls on packed rows; the
+// pre-pass of the operands sets the flag itself.
 __global__ __launch_bounds__(1024) void complete_flag_kernel(const int32_t* __restrict__ ca,
                                                              int64_t n_a,
                                                              const int32_t* __restrict__ cb,
                                                              int64_t n_b, int64_t n_f,
-                                                             int* __restrict__ flag) {
+                                                             unsigned long long* __restrict__ flag,
+                                                             unsigned long long id) {
   bool ok = n_f > 0;
   for (int64_t r = threadIdx.x; r < n_a && ok; r += blockDim.x)
     ok = reinterpret_cast<const v4i*>(ca)[r].z == n_f;
   for (int64_t r = threadIdx.x; r < n_b && ok; r += blockDim.x)
     ok = reinterpret_cast<const v4i*>(cb)[r].z == n_f;
   ok = __syncthreads_and(ok ? 1 : 0) != 0;
-  if (threadIdx.x == 0) *flag = ok ? 1 : 0;
+  if (threadIdx.x == 0) *flag = ok ? 0ull : id;
 }
 
-// Workgroup tile (I, J) of `b` in a grid of tiles of BM x BN pairs
-// (triangle: BM / BN tiles per square, squares in strips of H square rows).
+// Workgroup tile (I, J) of `b` in a grid of tiles of BM x BN pairs.  A
+// triangle is cut into squares of the larger side, each a few whole tiles,
+// the squares in strips of H square rows.
 template <int BM, int BN, int H = kStripRows>
 __device__ __forceinline__ void tile_of(const Pair2Args& a, int64_t b, int64_t tiles_side,
                                         int64_t tiles_n, int64_t& I, int64_t& J) {
-  constexpr int HALVES = BM / BN;
-  static_assert(BM == HALVES * BN, "a square splits into whole tiles");
+  constexpr int S = BM > BN ? BM : BN, PARTS = S / (BM > BN ? BN : BM);
+  static_assert(S % BM == 0 && S % BN == 0, "a square splits into whole tiles");
   if (a.tri) {
     int64_t sq_i, sq_j;
-    strip_square(b / HALVES, tiles_side, a.row_begin / BM, (a.row_end + BM - 1) / BM, sq_i,
-                 sq_j, H);
-    I = sq_i;
-    J = HALVES * sq_j + b % HALVES;
+    strip_square(b / PARTS, tiles_side, a.row_begin / S, (a.row_end + S - 1) / S, sq_i, sq_j, H);
+    I = BM < BN ? PARTS * sq_i + b % PARTS : sq_i;
+    J = BM < BN ? sq_j : PARTS * sq_j + b % PARTS;
   } else {
     I = b / tiles_n;
     J = b % tiles_n;
@@ -45,6 +52,11 @@ __device__ __forceinline__ void tile_of(const Pair2Args& a, int64_t b, int64_t t
 // Square rows per strip of the complete-data kernel's triangle order: its
 // squares are twice the height of the general kernel's.
 constexpr int kCompleteStripRows = 4;
+// ... and of the kernels on operands: fewer rows in flight than the packed
+// kernel's strips of 8 write their output in fewer, longer runs (16384 x
+// 2000: 1.62 -> 1.55 ms, 16384 x 32768: 5.81 -> 5.66 ms; with 2 the latter
+// takes 5.90 ms).
+constexpr int kOperandStripRows = 4;
 
 // Calls whose every row is complete: 2 x 2 waves of (16 WM) x (16 WN) pairs
 // (mfma2_complete_wave_tile); a workgroup exits at once when the flag says
@@ -53,7 +65,7 @@ template <int WM, int WN, bool F4>
 __global__ __launch_bounds__(256, 2) void mfma2_complete_kernel(Pair2Args a,
                                                                 int64_t tiles_side,
                                                                 int64_t tiles_n) {
-  if (*a.complete == 0) return;  // uniform
+  if (*a.flag == a.id) return;  // uniform: some row is not complete
   constexpr int BM = 32 * WM, BN = 32 * WN, NB = 2 * WM + 2 * WN;
   const int wave = threadIdx.x >> 6;
   int64_t I, J;
@@ -71,7 +83,7 @@ __global__ __launch_bounds__(256, 2) void mfma2_complete_kernel(Pair2Args a,
 template <int WM, int WN, bool F4, int MIN_WG>
 __global__ __launch_bounds__(256, MIN_WG) void mfma2_kernel(Pair2Args a, int64_t tiles_side,
                                                             int64_t tiles_n) {
-  if (a.complete && *a.complete) return;  // uniform: mfma2_complete_kernel covers the call
+  if (a.flag && *a.flag != a.id) return;  // uniform: mfma2_complete_kernel covers the call
   constexpr int BM = 32 * WM, BN = 32 * WN, NB = 2 * WM + 2 * WN;
   constexpr bool kCoop = WM == 4 && WN == 2;
   const int wave = threadIdx.x >> 6;
@@ -95,16 +107,130 @@ __global__ __launch_bounds__(256, MIN_WG) void mfma2_kernel(Pair2Args a, int64_t
                                      reinterpret_cast<u4(*)[NB][64]>(smem));
 }
 
-// Grid of BM x BN workgroup tiles: tiles along a side (rows, columns) and
-// the tile count (triangle: the squares of the row range, BM / BN tiles
-// each); 0 tiles when there is nothing to do.
+// Calls whose every row is complete, on operands (tile2o.h).
+template <tile2::Out OUT, int WM, int WN>
+__global__ __launch_bounds__(256, 2) void mfma2_complete_operand_kernel(Pair2Args a,
+                                                                        int64_t tiles_side,
+                                                                        int64_t tiles_n) {
+  if (*a.flag == a.id) return;  // uniform: some row is not complete
+  constexpr int BM = 32 * WM, BN = 32 * WN;
+  int64_t I, J;
+  tile_of<BM, BN, kCompleteStripRows>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I,
+                                      J);
+  __shared__ u4 stage[3][2 * WM + 2 * WN][64];
+  tile2::complete_tile<OUT, WM, WN>(a, I * BM, J * BN, stage);
+}
+
+// The general kernel on operands: workgroup tiles of (32 WM) x (32 WN).
+template <tile2::Out OUT, int WM, int WN, int MIN_WG>
+__global__ __launch_bounds__(256, MIN_WG) void mfma2_operand_kernel(Pair2Args a,
+                                                                    int64_t tiles_side,
+                                                                    int64_t tiles_n) {
+  if (a.flag && *a.flag != a.id) return;  // uniform: the complete-data kernel covers the call
+  constexpr int BM = 32 * WM, BN = 32 * WN;
+  int64_t I, J;
+  tile_of<BM, BN, kOperandStripRows>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I, J);
+  __shared__ u4 stage[3][2 * WM + 2 * WN][64];
+  tile2::staged_tile<OUT, WM, WN>(a, I * BM, J * BN, stage);
+}
+
+// The field-split kernel on operands: 32 x 32 tiles, each by `splits`
+// workgroups that take a share of the super-steps.  With one, the workgroup
+// emits its tile; with more, the partial sums go to a.part, [tile][split]
+// [block][plane][lane], and mfma2_split_finish_kernel adds and emits them.
+constexpr int kSplitTile = 32;
+__device__ __forceinline__ bool split_tile_of(const Pair2Args& a, int64_t t, int64_t tiles_side,
+                                              int64_t tiles_n, int64_t& I0, int64_t& J0) {
+  int64_t I, J;
+  tile_of<kSplitTile, kSplitTile, kOperandStripRows>(a, t, tiles_side, tiles_n, I, J);
+  I0 = I * kSplitTile;
+  J0 = J * kSplitTile;
+  return tile2::wave_complete<kSplitTile, kSplitTile>(a, I0, J0);
+}
+
+using SplitSides = tile2::Sides<kSplitTile, kSplitTile>;
+
+// This wave's block of the tile: its sums `s` to the output.
+template <tile2::Out OUT, bool GENERAL, int NP>
+__device__ __forceinline__ void split_emit(const Pair2Args& a, int64_t I0, int64_t J0,
+                                           const v4i (&s)[1][NP], SplitSides& sides) {
+  const int wave = threadIdx.x >> 6, m = wave & 1, n = wave >> 1;
+  tile2::load_sides<OUT>(a, I0, J0, sides, threadIdx.x, 256);
+  __syncthreads();
+  const int64_t i0 = I0 + 16 * m, j0 = J0 + 16 * n;
+  if (i0 >= a.n_a || j0 >= a.n_b || (a.tri && i0 >= j0 + 15)) return;  // no pair
+  tile2::emit_blocks<OUT, GENERAL>(a, sides, 16 * m, 16 * n, j0, s);
+}
+
+template <tile2::Out OUT>
+__global__ __launch_bounds__(256, 2) void mfma2_split_kernel(Pair2Args a, int64_t tiles_side,
+                                                             int64_t tiles_n, int splits) {
+  __shared__ v4i red[4][4][64];
+  __shared__ SplitSides sides;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t b = xcd_unit(blockIdx.x, gridDim.x), t = b / splits;
+  const int sp = (int)(b % splits);
+  int64_t I0, J0;
+  const bool whole = split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
+  const int64_t s0 = a.steps * sp / splits, s1 = a.steps * (sp + 1) / splits;
+  v4i* part = reinterpret_cast<v4i*>(a.part) + ((b * 4 + wave) * 4) * 64 + lane;
+  auto run = [&](auto general, auto& s) {
+    tile2::split_sums<general.value>(a, I0, J0, s0, s1, red, s[0]);
+    if (splits == 1) {
+      split_emit<OUT, general.value>(a, I0, J0, s, sides);
+    } else {
+      tile2::static_for<general.value ? 4 : 1>([&](auto p) { part[64 * p.value] = s[0][p.value]; });
+    }
+  };
+  if (whole) {
+    v4i s[1][1];
+    run(std::false_type{}, s);
+  } else {
+    v4i s[1][4];
+    run(std::true_type{}, s);
+  }
+}
+
+template <tile2::Out OUT>
+__global__ __launch_bounds__(256) void mfma2_split_finish_kernel(Pair2Args a, int64_t tiles_side,
+                                                                 int64_t tiles_n, int splits) {
+  __shared__ SplitSides sides;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = xcd_unit(blockIdx.x, gridDim.x);
+  int64_t I0, J0;
+  const bool whole = split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
+  const v4i* part = reinterpret_cast<const v4i*>(a.part) + ((t * splits * 4 + wave) * 4) * 64 + lane;
+  auto run = [&](auto general, auto& s) {
+    constexpr int NP = general.value ? 4 : 1;
+    tile2::static_for<NP>([&](auto p) { s[0][p.value] = part[64 * p.value]; });
+#pragma unroll 4
+    for (int k = 1; k < splits; ++k)
+      tile2::static_for<NP>([&](auto p) { s[0][p.value] += part[(k * 16 + p.value) * 64]; });
+    split_emit<OUT, general.value>(a, I0, J0, s, sides);
+  };
+  if (whole) {
+    v4i s[1][1];
+    run(std::false_type{}, s);
+  } else {
+    v4i s[1][4];
+    run(std::true_type{}, s);
+  }
+}
+
+// Grid of BM x BN workgroup tiles: tiles along a side (rows, columns; for a
+// triangle squares) and the tile count (triangle: the squares of the row
+// range, a few tiles each); 0 tiles when there is nothing to do.
 template <int BM, int BN>
 int64_t tile_grid(const Pair2Args& a, int64_t& tm, int64_t& tn) {
-  tm = (a.n_a + BM - 1) / BM;
-  tn = (a.n_b + BN - 1) / BN;
-  if (!a.tri) return tm * tn;
-  const int64_t s0 = a.row_begin / BM, s1 = (a.row_end + BM - 1) / BM;
-  return BM / BN * (s1 * tm - s1 * (s1 - 1) / 2 - (s0 * tm - s0 * (s0 - 1) / 2));
+  constexpr int S = BM > BN ? BM : BN, PARTS = S / (BM > BN ? BN : BM);
+  if (!a.tri) {
+    tm = (a.n_a + BM - 1) / BM;
+    tn = (a.n_b + BN - 1) / BN;
+    return tm * tn;
+  }
+  tm = tn = (a.n_a + S - 1) / S;
+  const int64_t s0 = a.row_begin / S, s1 = (a.row_end + S - 1) / S;
+  return PARTS * (s1 * tm - s1 * (s1 - 1) / 2 - (s0 * tm - s0 * (s0 - 1) / 2));
 }
 
 template <int WM, int WN, bool F4, int MIN_WG>
@@ -136,6 +262,8 @@ hipError_t launch_general(const Pair2Args& a, hipStream_t stream) {
 
 // The complete-data kernel's wave tile: 128 x 64 pairs (8 x 4 blocks of 16).
 constexpr int kCWM = 8, kCWN = 4;
+// ... and on operands: 64 x 128, for the longer stretches of a row.
+constexpr int kCOM = 4, kCON = 8;
 
 template <bool F4>
 hipError_t launch_complete(const Pair2Args& a, hipStream_t stream) {
@@ -150,11 +278,11 @@ hipError_t launch_complete(const Pair2Args& a, hipStream_t stream) {
 
 template <bool F4>
 hipError_t launch_f(const Pair2Args& a, hipStream_t stream) {
-  if (a.complete) {
+  if (a.flag) {
     // the flag first, then both kernels: each exits at once unless the flag
     // picks it
     hipLaunchKernelGGL(complete_flag_kernel, dim3(1), dim3(1024), 0, stream, a.counts_a, a.n_a,
-                       a.counts_b, a.n_b, a.n_f, a.complete);
+                       a.counts_b, a.n_b, a.n_f, a.flag, a.id);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if ((e = launch_complete<F4>(a, stream)) != hipSuccess) return e;
@@ -162,12 +290,125 @@ hipError_t launch_f(const Pair2Args& a, hipStream_t stream) {
   return launch_general<F4>(a, stream);
 }
 
+// Shapes on operands: 0 = 64 x 128 staged tiles, 1 = field-split 32 x 32
+// tiles, 2 = 64 x 64 staged tiles.
+struct OperandShape {
+  int variant;
+  int splits;  // workgroups per tile (variant 1)
+};
+
+int64_t split_tiles(const Pair2Args& a, int64_t& tm, int64_t& tn) {
+  return tile_grid<kSplitTile, kSplitTile>(a, tm, tn);
+}
+
+// The shape by the number of 32 x 32 tiles (n^2 / 2048 for a triangle) and
+// super-steps, from timings of whole calls with 1% missing, us for shapes 1 /
+// 2 / 0: 1500 x 9000 39 / 51 / 56, 2600 x 6000 69 / 65 / 70, 2600 x 20000 128 /
+// 134 / 144, 3500 x 4000 92 / 94 / 105, 4500 x 15000 273 / 249 / 298, 8000 x
+// 10000 656 / 569 / 586, 12000 x 4000 980 / 893 / 872, 16384 x 32768 6570 /
+// 5880 / 5660.  Small tiles give a small call more workgroups and a shorter
+// chain each; large ones read their operands less often.  With very short
+// fields a call is its output, and the 32 x 32 tiles, one block per wave,
+// start storing at once: 12000 x 1000 719 / 862 / 835.  A selection stores
+// little, so its smaller tiles pay for longer (12000 x 8009: 957 / 1000 for
+// shapes 2 / 0).
+OperandShape operand_shape(const Pair2Args& a) {
+  int64_t tm, tn;
+  const int64_t tiles = split_tiles(a, tm, tn);
+  OperandShape s{0, 1};
+  const int forced = tune_forced_oneshot(kOneShotVariants);
+  if (a.n_f > tile2::kStagedMaxFields)
+    s.variant = 1;  // four waves' sums, each exact
+  else if (forced >= 0)
+    s.variant = forced;
+  else if (tiles < 6000 || a.n_f <= 1024)
+    s.variant = 1;
+  else if (tiles < 50000 || (a.sel.count && a.steps < 64))
+    s.variant = 2;
+  if (s.variant == 1 && tiles > 0) {
+    // Enough workgroups for two per CU, but no share below 16 super-steps:
+    // the sums' way through memory and the second launch cost about 5 us
+    // (384 x 250007: 173 us with 1 split, 94 with 3, 83 with 6, 85 with 12;
+    // 700 x 50000: 48, 44 with 2, 46 with 6; 700 x 5000: 18, 20 with 2).
+    int64_t n = 512 / tiles < a.steps / 16 ? 512 / tiles : a.steps / 16;
+    if (const char* env = getenv("CCC_SPLIT")) n = atoi(env) < a.steps ? atoi(env) : a.steps;
+    s.splits = n > 1 ? (int)n : 1;
+  }
+  return s;
+}
+
+template <tile2::Out OUT, int WM, int WN, int MIN_WG>
+hipError_t launch_operand_shape(const Pair2Args& a, hipStream_t stream) {
+  int64_t tm, tn;
+  const int64_t ntiles = tile_grid<32 * WM, 32 * WN>(a, tm, tn);
+  if (ntiles <= 0) return hipSuccess;
+  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((mfma2_operand_kernel<OUT, WM, WN, MIN_WG>), dim3((unsigned)ntiles),
+                     dim3(256), 0, stream, a, tm, tn);
+  return hipGetLastError();
+}
+
+template <tile2::Out OUT>
+hipError_t launch_split(const Pair2Args& a, int splits, hipStream_t stream) {
+  int64_t tm, tn;
+  const int64_t ntiles = split_tiles(a, tm, tn);
+  if (ntiles <= 0) return hipSuccess;
+  if (ntiles * splits > 0x7FFFFFFF) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mfma2_split_kernel<OUT>, dim3((unsigned)(ntiles * splits)), dim3(256), 0,
+                     stream, a, tm, tn, splits);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || splits == 1) return e;
+  hipLaunchKernelGGL(mfma2_split_finish_kernel<OUT>, dim3((unsigned)ntiles), dim3(256), 0, stream,
+                     a, tm, tn, splits);
+  return hipGetLastError();
+}
+
+template <tile2::Out OUT>
+hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
+  OperandShape s = operand_shape(a);
+  int64_t tm, tn;
+  if (s.variant == 1 && s.splits > 1 && mfma2_part_bytes(a) > a.part_bytes) s.splits = 1;
+  if (s.variant == 1) return launch_split<OUT>(a, s.splits, stream);  // its tiles vote
+  if constexpr (OUT != tile2::kAccumulate) {  // (whose counts are running totals)
+    const int64_t n = tile_grid<32 * kCOM, 32 * kCON>(a, tm, tn);
+    if (n > 0x7FFFFFFF) return hipErrorInvalidValue;
+    // Long fields bind these tiles by their operand reads, which a plain
+    // output stream pushes out of L2; short ones by the output, whose lines
+    // plain stores let L2 join (16000 x 40000: 3.20 ms plain, 2.87 with the
+    // tables streamed; 16384 x 16384: 2.26 and 2.19; 16384 x 2000: 1.71 and
+    // 2.06).
+    auto* kernel = mfma2_complete_operand_kernel<OUT, kCOM, kCON>;
+    if constexpr (OUT == tile2::kDense)
+      if (a.n_f >= 12288) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
+    if (n > 0) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(256), 0, stream, a, tm, tn);
+      if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+  }
+  return s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)
+                        : launch_operand_shape<OUT, 2, 4, 2>(a, stream);
+}
+
+hipError_t launch_operands_out(const Pair2Args& a, hipStream_t stream) {
+  if (a.sel.count) return launch_operand_kernels<tile2::kSelect>(a, stream);
+  if (a.accumulate) return launch_operand_kernels<tile2::kAccumulate>(a, stream);
+  return launch_operand_kernels<tile2::kDense>(a, stream);
+}
+
 }  // namespace
 
+size_t mfma2_part_bytes(const Pair2Args& a) {
+  const OperandShape s = operand_shape(a);
+  if (s.variant != 1 || s.splits == 1) return 0;
+  int64_t tm, tn;
+  return (size_t)(split_tiles(a, tm, tn) * s.splits) * 16 * 64 * sizeof(v4i);
+}
+
 hipError_t launch_mfma2(const Pair2Args& a, hipStream_t stream) {
-  if (a.complete && a.accumulate) return hipErrorInvalidValue;
+  if (a.flag && a.accumulate) return hipErrorInvalidValue;
   timing_begin("mfma2", stream);
-  const hipError_t e = a.f4 ? launch_f<true>(a, stream) : launch_f<false>(a, stream);
+  const hipError_t e = a.f4 ? (a.za ? launch_operands_out(a, stream) : launch_f<true>(a, stream))
+                            : launch_f<false>(a, stream);
   timing_end(stream);
   return e;
 }

@@ -45,14 +45,7 @@ __device__ __forceinline__ void emit_pair(const Pair2Args& a, bool valid, int64_
       keep = r[0] >= a.sel.threshold || r[1] >= a.sel.threshold ||
              r[2] >= a.sel.threshold || r[3] >= a.sel.threshold;
     }
-    const int64_t slot = select_slot(keep, a.sel.count);
-    if (slot >= 0 && slot < a.sel.cap) {
-      a.sel.index[slot] = p;
-      double2* c = reinterpret_cast<double2*>(a.sel.ccc + 4 * slot);
-      c[0] = double2{r[0], r[1]};
-      c[1] = double2{r[2], r[3]};
-      if (a.sel.tables) *reinterpret_cast<v4i*>(a.sel.tables + 4 * slot) = t;
-    }
+    select_pair(a.sel, keep, p, t, r);
     return;
   }
   if (!valid) return;
@@ -81,7 +74,7 @@ __device__ __forceinline__ void emit_pair_staged(const Pair2Args& a, bool valid,
   const int64_t p = valid ? (a.tri ? pair_index(a.n_a, i, j) : i * a.n_b + j) - a.p_base : 0;
   // streaming stores: the dense output is written once and not read back here
   if (valid && a.tables)
-    __builtin_nontemporal_store(t, reinterpret_cast<v4i*>(a.tables + 4 * p));
+    *reinterpret_cast<v4i*>(a.tables + 4 * p) = t;
   if (!a.ccc) return;
   const unsigned gm = (unsigned)(__ballot(valid ? 1 : 0) >> (16 * g)) & 0xFFFFu;
   const int first = gm ? __ffs(gm) - 1 : 0;
@@ -743,6 +736,69 @@ __device__ __forceinline__ void mfma2_wave_tile(const Pair2Args& a, int64_t row0
   }
 }
 
+// Epilogue of a complete-data wave tile: sum(m, n, e) is C11 of row 4g + e of
+// block (m, n) (m, n integral constants).  `stage` is the workgroup's LDS
+// stage, reused; every wave of the workgroup must call it.
+template <int WM, int WN, typename Sum>
+__device__ __forceinline__ void complete_epilogue(const Pair2Args& a, int64_t row0, int64_t col0,
+                                                  bool active, u4* stage, u4* outs, Sum sum) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
+  const int wave = threadIdx.x >> 6;
+  // The epilogue's inputs are read before its first store (a wait for a
+  // load also waits for every store issued before it): the columns' into
+  // registers, the 16 WM rows' (n(1) and factors) into this wave's part of
+  // the stage, which every wave is done with after the barrier.
+  struct RowIn {
+    double w[2];
+    int n1, pad0, pad1, pad2;
+  };
+  static_assert(sizeof(RowIn) == 32, "two 16-byte halves");
+  static_assert(4 * 16 * WM * sizeof(RowIn) <= sizeof(u4) * (2 * WM + 2 * WN) * 64 * 2,
+                "the rows fit in the stage");
+  __syncthreads();
+  if (!active) return;
+  RowIn* rows = reinterpret_cast<RowIn*>(stage) + 16 * WM * wave;
+  for (int t = lane; t < 16 * WM; t += 64) {
+    const int64_t i = row0 + t, ii = i < a.n_a ? i : a.n_a - 1;
+    RowIn ri;
+    side_factors(a, 0, ii, ri.w);
+    ri.n1 = reinterpret_cast<const v4i*>(a.counts_a)[ii].y;
+    ri.pad0 = ri.pad1 = ri.pad2 = 0;
+    rows[t] = ri;
+  }
+
+  // Epilogue: lane holds rows 4g + e (e = 0..3) of column rl of each 16x16 block.
+  const int nf4 = (int)(4 * a.n_f);
+  double wj[WN][2];
+  int n1j[WN];
+#pragma unroll
+  for (int n = 0; n < WN; ++n) {
+    const int64_t j = col0 + 16 * n + rl;
+    side_factors(a, 1, j, wj[n]);
+    n1j[n] = reinterpret_cast<const v4i*>(a.counts_b)[j < a.n_b ? j : a.n_b - 1].y;
+  }
+  static_for<WM>([&](auto mc) {
+    constexpr int m = decltype(mc)::value;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t i = row0 + 16 * m + 4 * g + e;
+      const RowIn ri = rows[16 * m + 4 * g + e];
+      const int n1i = ri.n1;
+      const double(&wi)[2] = ri.w;
+      static_for<WN>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        const int64_t j = col0 + 16 * n + rl;
+        const int c11 = sum(mc, nc, e);
+        const bool valid = i < a.n_a && j < a.n_b && !(a.tri && i >= j);
+        emit_pair_staged(a, valid, i, j,
+                         v4i{nf4 - 2 * n1i - 2 * n1j[n] + c11, 2 * n1j[n] - c11, 2 * n1i - c11,
+                             c11},
+                         wi, wj[n], outs);
+      });
+    }
+  });
+}
+
 // Wave tile of a call whose every row of A and B has all n_f fields
 // present (P = 1 on every field): only C11 = sum rho_i(1) rho_j(1) is
 // multiplied, and the table follows from the allele counts n(1):
@@ -826,63 +882,14 @@ __device__ __forceinline__ void mfma2_complete_wave_tile(const Pair2Args& a, int
       [&](const u4 (&xa)[WM], const u4 (&xb)[WN]) { body(xa, xb, std::true_type{}); },
       [&](const u4 (&xa)[WM], const u4 (&xb)[WN]) { body(xa, xb, std::false_type{}); });
 
-  // The epilogue's inputs are read before its first store (a wait for a
-  // load also waits for every store issued before it): the columns' into
-  // registers, the 16 WM rows' (n(1) and factors) into this wave's part of
-  // the stage, which every wave is done with after the barrier.
-  struct RowIn {
-    double w[2];
-    int n1, pad0, pad1, pad2;
-  };
-  static_assert(sizeof(RowIn) == 32, "two 16-byte halves");
-  static_assert(4 * 16 * WM * sizeof(RowIn) <= sizeof(u4) * (2 * WM + 2 * WN) * 64 * 2,
-                "the rows fit in the stage");
-  __syncthreads();
-  if (!active) return;
-  RowIn* rows = reinterpret_cast<RowIn*>(&stage[0][0][0]) + 16 * WM * wave;
-  for (int t = lane; t < 16 * WM; t += 64) {
-    const int64_t i = row0 + t, ii = i < a.n_a ? i : a.n_a - 1;
-    RowIn ri;
-    side_factors(a, 0, ii, ri.w);
-    ri.n1 = reinterpret_cast<const v4i*>(a.counts_a)[ii].y;
-    ri.pad0 = ri.pad1 = ri.pad2 = 0;
-    rows[t] = ri;
-  }
-
-  // Epilogue: lane holds rows 4g + e (e = 0..3) of column rl of each 16x16 block.
-  const int nf4 = (int)(4 * a.n_f);
-  double wj[WN][2];
-  int n1j[WN];
-#pragma unroll
-  for (int n = 0; n < WN; ++n) {
-    const int64_t j = col0 + 16 * n + rl;
-    side_factors(a, 1, j, wj[n]);
-    n1j[n] = reinterpret_cast<const v4i*>(a.counts_b)[j < a.n_b ? j : a.n_b - 1].y;
-  }
-  static_for<WM>([&](auto mc) {
-    constexpr int m = decltype(mc)::value;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = row0 + 16 * m + 4 * g + e;
-      const RowIn ri = rows[16 * m + 4 * g + e];
-      const int n1i = ri.n1;
-      const double(&wi)[2] = ri.w;
-#pragma unroll
-      for (int n = 0; n < WN; ++n) {
-        const int64_t j = col0 + 16 * n + rl;
-        int c11;
+  complete_epilogue<WM, WN>(
+      a, row0, col0, active, &stage[0][0][0], outs,
+      [&](auto m, auto n, int e) {
         if constexpr (F4)
-          c11 = f4_count(acc[m][n][e]);
+          return f4_count(acc[m.value][n.value][e]);
         else
-          c11 = acc[m][n][e];
-        const bool valid = i < a.n_a && j < a.n_b && !(a.tri && i >= j);
-        emit_pair_staged(a, valid, i, j,
-                         v4i{nf4 - 2 * n1i - 2 * n1j[n] + c11, 2 * n1j[n] - c11, 2 * n1i - c11,
-                             c11},
-                         wi, wj[n], outs);
-      }
-    }
-  });
+          return acc[m.value][n.value][e];
+      });
 }
 
 // Complete-data workgroup tile (every one of its rows has all n_f fields

@@ -85,6 +85,10 @@ static int env_int(const char* name, int lo, int hi) {
   return (*end == 0 && v >= lo && v <= hi) ? (int)v : -1;
 }
 
+int tune_forced_oneshot(int n_variants) {
+  return env_int("CCC_ONESHOT_VARIANT", 0, n_variants - 1);
+}
+
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants) {
   TuneChoice c{0, 0};
   std::call_once(g_once, load_table);
