@@ -423,24 +423,22 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
   unsigned long long* zero = sel ? sel->count : nullptr;
   const int64_t row_end = i_end < n_v - 2 ? i_end : n_v - 2;  // first index below n_v - 2
   if (row_end <= i_begin && !counts && !zero) return CCC_OK;  // nothing to compute or write
-  // workspace: offsets of the tetrahedral work units (per tile pair; the
-  // one-j grid, the grid of the complete-data kernel's runs of j, the fp4
-  // general kernel's grid of 32-row tiles), then (if needed) counts, then
-  // (MFMA path) the complete-data flag and the rho(1) Gram matrix of rows
-  // [g0, n_v) used by complete-data units; g0 is i_begin rounded down to the
-  // unit tile
-  const ccc::UnitGrid ug = ccc::unit_grid(n_v, ccc::kUnitTile, i_begin, row_end);
-  const size_t offs_bytes = ((size_t)(ccc::grid_pairs(ug) + 1) * 8 + 255) / 256 * 256;
-  const ccc::UnitGrid ug32 = ccc::unit_grid(n_v, ccc::kRunTile, i_begin, row_end);
-  const size_t gen_bytes = ((size_t)(ccc::grid_pairs(ug32) + 1) * 8 + 255) / 256 * 256;
-  const size_t cnt_bytes = counts ? 0 : ((size_t)n_v * 16 + 255) / 256 * 256;
-  // offsets (one-j grid, runs grid, 32-row runs grid), counts, flag
-  const size_t head_bytes = 2 * offs_bytes + gen_bytes + cnt_bytes + 256;
+  // scratch: the complete-data flag, the counts (unless the caller's), then
+  // (MFMA path) the rho(1) Gram matrix of rows [g0, n_v) used by complete-data
+  // units; g0 is i_begin rounded down to the unit tile
+  const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 16);
+  const size_t head_bytes = 256 + cnt_bytes;
   const int64_t g0 = i_begin / ccc::kUnitTile * ccc::kUnitTile, ng = n_v - g0;
   bool use_gram = o.path != CCC_PATH_POPCOUNT && ng <= kGramMaxRows && i_begin < row_end;
   if (fixed) {
-    if (head_bytes > fixed->bytes) return CCC_ERR_RANGE;
-    if (use_gram && (size_t)ng * (size_t)ng * 4 > fixed->bytes - head_bytes) use_gram = false;
+    // the bound of the documented interface: tables of unit offsets (8 bytes
+    // per tile pair of three unit grids) that the kernels no longer need
+    const ccc::UnitGrid u64 = ccc::unit_grid(n_v, ccc::kUnitTile, i_begin, row_end);
+    const ccc::UnitGrid u32 = ccc::unit_grid(n_v, ccc::kRunTile, i_begin, row_end);
+    const size_t bound = 2 * round256((size_t)(ccc::grid_pairs(u64) + 1) * 8) +
+                         round256((size_t)(ccc::grid_pairs(u32) + 1) * 8) + head_bytes;
+    if (bound > fixed->bytes) return CCC_ERR_RANGE;
+    if (use_gram && (size_t)ng * (size_t)ng * 4 > fixed->bytes - bound) use_gram = false;
   }
   const size_t gram_bytes = use_gram ? (size_t)ng * (size_t)ng * 4 : 0;
   void* ws = nullptr;
@@ -449,22 +447,21 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
                   : ccc::workspace(head_bytes + gram_bytes, stream, lock, &ws)))
     return st;
   char* wsb = static_cast<char*>(ws);
-  int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 2 * offs_bytes + gen_bytes);
-  if (n_v < 3)
-    return ccc::launch_count1_zero(v, ld, n_v, n_f, cnt, 0, zero, stream) == hipSuccess
-               ? CCC_OK
-               : CCC_ERR_HIP;
-  if (ccc::launch_count1_zero(v, ld, n_v, n_f, cnt, 0, zero, stream) != hipSuccess)
-    return CCC_ERR_HIP;
-  if (row_end <= i_begin) return CCC_OK;
+  int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 256);
   ccc::Triple3Args a{};
+  // the complete-data kernel (fp4 operands, with the Gram matrix)
+  a.flag = use_gram && f4 && n_f > 0 ? reinterpret_cast<unsigned long long*>(wsb) : nullptr;
+  a.id = g_call++;
+  if (ccc::launch_count1_zero(v, ld, n_v, n_f, cnt, 0, zero, stream, a.flag, a.id, g0) !=
+      hipSuccess)
+    return CCC_ERR_HIP;
+  if (n_v < 3 || row_end <= i_begin) return CCC_OK;
   a.v = v; a.ld = ld; a.n = n_v; a.n_f = n_f;
   a.f4 = f4;
   a.tables = tables;
   a.ccc = ccc;
   a.counts = cnt;
   a.gamma = o.gamma;
-  a.offs = static_cast<int64_t*>(ws);
   a.i_begin = i_begin;
   a.i_end = row_end;
   a.t_base = choose3(n_v) - choose3(n_v - i_begin);  // T(i_begin, i_begin+1, i_begin+2)
@@ -473,11 +470,6 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
   a.gram = use_gram ? reinterpret_cast<int32_t*>(wsb + head_bytes) : nullptr;
   a.g0 = g0;
   a.ng = use_gram ? ng : 0;
-  // the complete-data kernel (fp4 operands, with the Gram matrix)
-  a.complete = use_gram && f4 ? reinterpret_cast<int*>(wsb + 2 * offs_bytes + gen_bytes + cnt_bytes)
-                              : nullptr;
-  a.offs_run = reinterpret_cast<int64_t*>(wsb + offs_bytes);
-  a.offs_gen = reinterpret_cast<int64_t*>(wsb + 2 * offs_bytes);
   hipError_t e = o.path == CCC_PATH_POPCOUNT ? ccc::launch_pop3(a, stream)
                                              : ccc::launch_mfma3(a, stream);
   return e == hipSuccess ? CCC_OK : CCC_ERR_HIP;

@@ -188,8 +188,11 @@ namespace ccc {
 // (n(0), n(1), m, 0) at out[0..3] from lane 0.  Popcounts on the bit planes:
 // b0 = low bits (01, 11), b1 = high bits (11, 10); n(1) = pop(b0) +
 // pop(b0 & b1), missing = pop(b1 & ~b0), n(0) = 2m - n(1).
+// *flag = id when the row misses an entry (flag may be null).
 __device__ __forceinline__ void count_row_wave(const uint8_t* __restrict__ r, int64_t n_f,
-                                               int32_t* __restrict__ out, int accumulate) {
+                                               int32_t* __restrict__ out, int accumulate,
+                                               unsigned long long* flag = nullptr,
+                                               unsigned long long id = 0) {
   const int lane = threadIdx.x & 63;
   const int64_t nbytes = (n_f + 3) / 4;
   int n1 = 0, miss = 0;
@@ -216,6 +219,7 @@ __device__ __forceinline__ void count_row_wave(const uint8_t* __restrict__ r, in
     present += __shfl_xor(present, off);
   }
   if (lane == 0) {
+    if (flag && present != n_f) *flag = id;
     v4i c = v4i{2 * present - n1, n1, present, 0};
     v4i* o4 = reinterpret_cast<v4i*>(out);
     if (accumulate) {
@@ -252,69 +256,21 @@ void timing_end(hipStream_t stream);
 
 namespace {
 
-// offs[p] = number of units of all tile pairs before p, for p = 0..pairs
-// (one workgroup; thread t walks a contiguous run of pairs).
-__global__ void unit_offsets_kernel(UnitGrid g, int64_t* __restrict__ offs) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int64_t P = grid_pairs(g);
-  const int64_t per = (P + 1023) / 1024;
-  const int64_t lo = t * per, hi = lo + per < P ? lo + per : P;
-  int64_t s = 0, it = 0, kt = 0;
-  if (lo < hi) pair_tiles(g, lo, it, kt);
-  for (int64_t p = lo; p < hi; ++p) {
-    s += pair_units(g, it, kt);
-    if (++kt == g.nt) kt = ++it;
-  }
-  part[t] = s;
-  __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int x = 0; x < 1024; ++x) {
-      int64_t v = part[x];
-      part[x] = run;
-      run += v;
-    }
-  }
-  __syncthreads();
-  int64_t run = part[t];
-  if (lo < hi) pair_tiles(g, lo, it, kt);
-  for (int64_t p = lo; p < hi; ++p) {
-    offs[p] = run;
-    run += pair_units(g, it, kt);
-    if (++kt == g.nt) kt = ++it;
-  }
-  if (t == 1023) offs[P] = run;
-}
-
-// Units of a whole grid (host side).
-inline int64_t grid_units(const UnitGrid& g) {
-  int64_t total = 0;
-  for (int64_t it = g.it0; it < g.it1; ++it)
-    for (int64_t kt = it; kt < g.nt; ++kt) total += pair_units(g, it, kt);
-  return total;
-}
-
 // Launch a 3-way kernel over all its tetrahedral units of b x b tiles and
 // `run` middle vectors (256 threads each), in slices of at most 2^30
-// workgroups.  offs must hold grid_pairs + 1 int64; `name` (if any) opens a
-// timing mark around the launches.
+// workgroups; `name` (if any) opens a timing mark around the launches.
 template <typename Kernel, typename Args>
 hipError_t launch_units(Kernel kernel, const Args& a, int64_t b, const char* name,
-                        hipStream_t stream, int64_t run = 1, int64_t* offs = nullptr) {
-  if (!offs) offs = a.offs;
+                        hipStream_t stream, int64_t run = 1) {
   const UnitGrid g = unit_grid(a.n, b, a.i_begin, a.i_end, run);
-  const int64_t total = grid_units(g);
+  const int64_t total = grid_unit_count(g);
   if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(unit_offsets_kernel, dim3(1), dim3(1024), 0, stream, g, offs);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const int64_t kMaxGrid = 0x40000000;
   if (name) timing_begin(name, stream);
   for (int64_t base = 0; base < total; base += kMaxGrid) {
     int64_t cnt = total - base < kMaxGrid ? total - base : kMaxGrid;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(256), 0, stream, a, g,
-                       (const int64_t*)offs, base, cnt);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(256), 0, stream, a, g, base, cnt);
     if ((e = hipGetLastError()) != hipSuccess) break;
   }
   if (name) timing_end(stream);

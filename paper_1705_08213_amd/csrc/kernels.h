@@ -183,6 +183,70 @@ __host__ __device__ __forceinline__ void unit_coords(int64_t u, const UnitGrid& 
   j = jlo + g.run * (u - offs[lo]);
 }
 
+// The same without the table of offsets.  With s = jlo(it) the first middle
+// vector of I tile it (the same for all its K tiles) and every tile but the
+// last whole, pair (it, it + d) has (d + 1) b/run - f units, f = floor((2 +
+// delta) / run) and delta how far the range begins inside the tile (first I
+// tile only), and the last K tile ceil((n - 1 - s) / run).  So the units
+// before a pair are a quadratic in d, and those before an I tile a cubic,
+// searched by halving: no dependent loads, no kernel that writes a table.
+// (Only d = 0 can come out negative, -1 with run = 1; it is then 0.)
+struct UnitRow {
+  int64_t q, f, fix, last, tail;  // b / run, f, units added back at d = 0, last d, its units
+};
+__host__ __device__ __forceinline__ UnitRow unit_row(const UnitGrid& g, int64_t it) {
+  const int64_t first = it * g.b, delta = g.i_begin > first ? g.i_begin - first : 0;
+  UnitRow r;
+  r.q = g.b / g.run;
+  r.f = (2 + delta) / g.run;
+  r.fix = r.q < r.f ? r.f - r.q : 0;
+  r.last = g.nt - 1 - it;
+  const int64_t js = g.n - 1 - (first + delta + 1);  // middle vectors of the last K tile
+  r.tail = js > 0 ? (js + g.run - 1) / g.run : 0;
+  return r;
+}
+// Units of the pairs (it, it) .. (it, it + d - 1), d <= last.
+__host__ __device__ __forceinline__ int64_t row_units_before(const UnitRow& r, int64_t d) {
+  return r.q * (d * (d + 1) / 2) - d * r.f + (d > 0 ? r.fix : 0);
+}
+// Units of I tiles it0 .. it - 1.
+__host__ __device__ __forceinline__ int64_t tile_units_before(const UnitGrid& g, int64_t it) {
+  if (it <= g.it0) return 0;
+  const UnitRow r0 = unit_row(g, g.it0);
+  const int64_t head = row_units_before(r0, r0.last) + r0.tail;
+  // the whole tiles after the first: rows x = it0 + 1 .. it - 1 with D = nt -
+  // 1 - x whole pairs and a tail of ceil((n - 2 - x b) / run)
+  const int64_t lo = g.it0 + 1, cnt = it - lo, q = g.b / g.run, f = 2 / g.run;
+  const int64_t D1 = g.nt - 1 - lo, D0 = D1 - cnt;  // D runs D1 .. D0 + 1
+  const int64_t pairs = (D1 * (D1 + 1) - D0 * (D0 + 1)) / 2;                          // sum of D
+  const int64_t tets = (D1 * (D1 + 1) * (D1 + 2) - D0 * (D0 + 1) * (D0 + 2)) / 6;     // D(D+1)/2
+  const int64_t rows = (lo + it - 1) * cnt / 2;                                       // sum of x
+  return head + q * tets - f * pairs + cnt * ((g.n - 2 + g.run - 1) / g.run) - q * rows;
+}
+__host__ __device__ __forceinline__ int64_t grid_unit_count(const UnitGrid& g) {
+  return tile_units_before(g, g.it1);
+}
+__host__ __device__ __forceinline__ void unit_at(int64_t u, const UnitGrid& g, int64_t& j,
+                                                 int64_t& it, int64_t& kt) {
+  int64_t lo = g.it0, hi = g.it1;  // tile_units_before(lo) <= u < tile_units_before(hi)
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (tile_units_before(g, mid) <= u) lo = mid; else hi = mid;
+  }
+  it = lo;
+  u -= tile_units_before(g, it);
+  const UnitRow r = unit_row(g, it);
+  lo = 0, hi = r.last + 1;  // row_units_before(lo) <= u
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (row_units_before(r, mid) <= u) lo = mid; else hi = mid;
+  }
+  kt = it + lo;
+  int64_t jlo, jhi;
+  pair_j_range(g, it, kt, jlo, jhi);
+  j = jlo + g.run * (u - row_units_before(r, lo));
+}
+
 // Workgroup b of a grid of `count` -> unit index, so that the workgroups the
 // dispatcher sends to one of the 8 XCDs (b mod 8) take one contiguous run of
 // units, in order.
@@ -240,7 +304,6 @@ struct Triple3Args {
   double* ccc;
   const int32_t* counts;
   double gamma;
-  int64_t* offs;  // workspace: tile pairs + 1 int64 (work-unit offsets per tile pair)
   // triples whose first index lies in [i_begin, i_end); triple t goes to entry t - t_base
   int64_t i_begin, i_end;
   int64_t t_base;
@@ -249,15 +312,10 @@ struct Triple3Args {
   // MFMA launcher; null turns the complete-data path off.
   int32_t* gram;
   int64_t g0, ng;
-  // Complete-data flag and the unit offsets of the run grid its kernel walks
-  // (fp4 MFMA with a Gram matrix only; null: every unit votes for itself).
-  // launch_mfma3 sets *complete to 1 when every row of [g0, n) has all n_f
-  // fields present.
-  int* complete;
-  int64_t* offs_run;
-  // Unit offsets of the fp4 general kernel's grid (32-row tiles, runs of
-  // four middle vectors).
-  int64_t* offs_gen;
+  // Complete-data flag (fp4 MFMA with a Gram matrix only; null: every unit
+  // votes for itself): holds `id` when some row of [g0, n) misses an entry.
+  unsigned long long* flag;
+  unsigned long long id;
 };
 
 enum Path { kPathPopcount = 1, kPathMfma = 2 };
@@ -282,10 +340,12 @@ void timing_host(const char* name, double ms);
 
 hipError_t launch_count1(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int32_t* counts,
                          int accumulate, hipStream_t stream);
-// count1 that also zeroes a selection counter (a kernel store, graph safe)
+// count1 that also zeroes a selection counter (a kernel store, graph safe) and
+// sets *flag = id when some row from flag_from on misses an entry
 hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f,
                               int32_t* counts, int accumulate, unsigned long long* zero,
-                              hipStream_t stream);
+                              hipStream_t stream, unsigned long long* flag = nullptr,
+                              unsigned long long id = 0, int64_t flag_from = 0);
 hipError_t launch_operands(OperandJob job, hipStream_t stream);
 // Shares of the fields for the pass over one set: few blocks of long rows are
 // bound by the memory path of the few CUs that hold them (24 blocks x 977

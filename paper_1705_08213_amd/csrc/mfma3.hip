@@ -43,7 +43,7 @@
 // eight.
 #include <type_traits>
 
-#include "tile2.h"
+#include "tile2o.h"
 #include "tile3.h"
 
 namespace ccc {
@@ -449,7 +449,7 @@ __device__ __forceinline__ void complete_unit(const Triple3Args& a, int64_t j, i
 constexpr int64_t kJRun = 4;
 
 // Complete-data kernel, for calls whose every row has all n_f fields present
-// (the flag set by complete3_flag_kernel picks it; it exits at once
+// (the flag set by the count pass picks it; it exits at once
 // otherwise).  A workgroup takes a run of kJRun consecutive middle vectors j
 // of one tile pair (I tile, K tile), one per wave, and each wave computes the
 // whole 64 x 64 (i, k) tile of S_xyz = G[i][k] + sum rho_i(1) D_j rho_k(1)
@@ -468,11 +468,10 @@ constexpr int64_t kJRun = 4;
 // step s - 1 are free (raw(s + 2) goes into the buffer of raw(s), which was
 // read in step s - 1).  The last, padded step takes plain loads.
 __global__ __launch_bounds__(256, 3) void mfma3_complete_kernel(Triple3Args a, UnitGrid ug,
-                                                                const int64_t* __restrict__ offs,
                                                                 int64_t unit_base,
                                                                 int64_t count) {
 #pragma clang fp contract(off)
-  if (*a.complete == 0) return;  // uniform
+  if (*a.flag == a.id) return;  // uniform: some row is not complete
   constexpr int NB = 9, BPW = 3;  // raw row blocks per step; copies per wave (the last idle)
   __shared__ u4 raw[2][NB][64];        // 18 KB
   __shared__ u4 planes[2][8][2][64];   // 32 KB: [step & 1][block][half][lane]; then store staging
@@ -481,7 +480,7 @@ __global__ __launch_bounds__(256, 3) void mfma3_complete_kernel(Triple3Args a, U
   const int64_t n = a.n;
   const int64_t u = unit_base + xcd_unit(blockIdx.x, count);
   int64_t j0, it, kt, jlo, jhi;
-  unit_coords(u, ug, offs, j0, it, kt);
+  unit_at(u, ug, j0, it, kt);
   pair_j_range(ug, it, kt, jlo, jhi);
   const int64_t jn = jhi - j0 < kJRun ? jhi - j0 : kJRun;  // middle vectors of this run
   const int64_t j = j0 + (wave < jn ? wave : jn - 1);      // inactive waves repeat the last
@@ -719,11 +718,10 @@ __global__ __launch_bounds__(256, 3) void mfma3_complete_kernel(Triple3Args a, U
 // lanes of a group read one address).  The words of batch b + 1 are loaded
 // while batch b is multiplied.
 __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGrid ug,
-                                                           const int64_t* __restrict__ offs,
                                                            int64_t unit_base, int64_t count) {
 #pragma clang fp contract(off)
-  if (a.complete && *a.complete) return;  // uniform: mfma3_complete_kernel covers the call
-  __shared__ u4 raw[2][4][64];            // 8 KB: [step & 1][row block][lane]
+  if (a.flag && *a.flag != a.id) return;  // uniform: mfma3_complete_kernel covers the call
+  __shared__ u4 raw[4][4][64];            // 16 KB: [step & 3][row block][lane]
   __shared__ u4 planes[2][4][2][2][64];   // 32 KB: [step & 1][block][half][rho(1), P][lane]
   __shared__ u4 jm[4][4][16][3];          // 12 KB: [wave][group][half step][y, sg, p]
   const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
@@ -731,7 +729,7 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
   const int64_t n = a.n;
   const int64_t u = unit_base + xcd_unit(blockIdx.x, count);
   int64_t j0, it, kt, jlo, jhi;
-  unit_coords(u, ug, offs, j0, it, kt);
+  unit_at(u, ug, j0, it, kt);
   pair_j_range(ug, it, kt, jlo, jhi);
   const int64_t jn = jhi - j0 < kJRun ? jhi - j0 : kJRun;  // middle vectors of this run
   const int64_t j = j0 + (wave < jn ? wave : jn - 1);      // inactive waves repeat the last
@@ -751,8 +749,11 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
                     (uint32_t)__builtin_amdgcn_readfirstlane((int)bp));
     off = (uint32_t)((r - rf) * a.ld + 16 * g);
   }
-  auto issue = [&](int64_t st, int buf) {
-    tile2::stage_row((const uint8_t*)(base + st * 64 + off), &raw[buf][wave][0]);
+  // asynchronous (tile2o.h); the waits are in the loop
+  const uint32_t dst = __builtin_amdgcn_readfirstlane(tile2::lds_offset(&raw[0][wave][0]));
+  auto issue = [&](int64_t st) {
+    tile2::copy_async(base + st * 64, off,
+                      __builtin_amdgcn_readfirstlane(dst + (uint32_t)(st & 3) * 4096));
   };
   // the planes of one row block's 16 bytes: per half, rho(1) and P
   auto planes_of = [](const u4& x, int h, u4& R, u4& P) {
@@ -771,7 +772,7 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
       planes[buf][wave][h][1][lane] = P;
     }
   };
-  auto build = [&](int buf) { build_from(raw[buf][wave][lane], buf); };
+  auto build = [&](int64_t st) { build_from(raw[st & 3][wave][lane], (int)(st & 1)); };
 
   v4f acc[2][2][8];
 #pragma unroll
@@ -843,8 +844,9 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
   };
   u2 jw = u2{0u, 0u};
   if (nfull > 0) {
-    issue(0, 0);
-    if (nfull > 1) issue(1, 1);
+    issue(0);
+    if (nfull > 1) issue(1);
+    if (nfull > 2) issue(2);
     if (active) jw = jwords(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -852,7 +854,12 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
   }
   for (int64_t st = 0; st < nfull; ++st) {
     const int buf = (int)(st & 1);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // raw(st + 1) of this wave has landed
+    // raw(st + 1) of this wave has landed; raw(st + 2) may fly on (a load of
+    // j's words in between only makes the wait longer)
+    if (st + 2 < nfull)
+      asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every wave's has; planes(st) are written; step st - 1's buffers are free
     if (active && (st & 7) == 0) {  // uniform: the masks of steps st .. st + 7
       u4 y, sg, pm;
@@ -864,9 +871,9 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
       jw = jwords(st + 8);
     }
     const bool more = st + 1 < nfull;  // uniform
-    if (more && st + 2 < nfull) issue(st + 2, buf);
+    if (st + 3 < nfull) issue(st + 3);
     if (!active) {
-      if (more) build(buf ^ 1);
+      if (more) build(st + 1);
     } else {
       // Every LDS read of the step goes out ahead of the MFMAs that need it:
       // the next step's row block and the first half's operands, then the
@@ -875,7 +882,7 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
       // step's planes are built between the two halves; on the last step
       // the build reads and writes buffers that no wave uses any more (no
       // branch, so that the compiler keeps the MFMAs where they are).
-      const u4 xn = raw[buf ^ 1][wave][lane];
+      const u4 xn = raw[(st + 1) & 3][wave][lane];
       u4 AR[2][2], AP[2][2], KR[2][2], KP[2][2], M[2][3];
       auto read_half = [&](int h) {
 #pragma unroll
@@ -964,30 +971,17 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
   });
 }
 
-// *flag = 1 if every row of [r0, n) has all n_f fields present (one
-// workgroup; its threads read the counts with a stride).
-__global__ __launch_bounds__(1024) void complete3_flag_kernel(const int32_t* __restrict__ counts,
-                                                              int64_t r0, int64_t n, int64_t n_f,
-                                                              int* __restrict__ flag) {
-  bool ok = n_f > 0;
-  for (int64_t r = r0 + threadIdx.x; r < n && ok; r += blockDim.x)
-    ok = reinterpret_cast<const v4i*>(counts)[r].z == n_f;
-  ok = __syncthreads_and(ok ? 1 : 0) != 0;
-  if (threadIdx.x == 0) *flag = ok ? 1 : 0;
-}
-
 // The int8 form over one-j units: 2 x 2 waves over a 64 x 64 (i, k) tile
 // for one middle vector j; a unit whose rows are all complete computes its
 // tile together in the one-plane form (complete_unit).
 __global__ __launch_bounds__(256, 2) void mfma3_kernel(Triple3Args a, UnitGrid ug,
-                                                       const int64_t* __restrict__ offs,
-                                                       int64_t unit_base, int64_t count) {
+                                                           int64_t unit_base, int64_t count) {
   __shared__ v4i part[4][16][64];  // 64 KB: the complete-data partial tiles
   const int wave = threadIdx.x >> 6;
   const int64_t n = a.n;
   const int64_t u = unit_base + xcd_unit(blockIdx.x, count);
   int64_t j, it, kt;
-  unit_coords(u, ug, offs, j, it, kt);
+  unit_at(u, ug, j, it, kt);
 
   // Complete-data vote over the unit's 64 i rows, 64 k rows and v_j
   // (workgroup-uniform; rows past n repeat row n-1).
@@ -1014,7 +1008,10 @@ __global__ __launch_bounds__(256, 2) void mfma3_kernel(Triple3Args a, UnitGrid u
 // of 128 x 64.
 __global__ __launch_bounds__(256, 2) void gram1_kernel(const uint8_t* __restrict__ v, int64_t ld,
                                                        int64_t g0, int64_t ng, int64_t n_f,
-                                                       int32_t* __restrict__ gram) {
+                                                       int32_t* __restrict__ gram,
+                                                       const unsigned long long* __restrict__ flag,
+                                                       unsigned long long id) {
+  if (flag && *flag == id) return;  // uniform: no unit will read it
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, rl = lane & 15;
   const int64_t row0 = (int64_t)blockIdx.y * 128 + (wave & 1) * 64;
@@ -1057,21 +1054,16 @@ hipError_t launch_mfma3(const Triple3Args& a, hipStream_t stream) {
   if (a.gram && a.ng > 0) {
     const dim3 grid((unsigned)((a.ng + 63) / 64), (unsigned)((a.ng + 127) / 128));
     hipLaunchKernelGGL(gram1_kernel, grid, dim3(256), 0, stream, a.v, a.ld, a.g0, a.ng, a.n_f,
-                       a.gram);
+                       a.gram, a.flag, a.id);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   timing_begin("mfma3", stream);
   hipError_t e = hipSuccess;
-  if (a.complete) {
-    // the flag, then both kernels: each exits at once unless the flag picks it
-    hipLaunchKernelGGL(complete3_flag_kernel, dim3(1), dim3(1024), 0, stream, a.counts, a.g0,
-                       a.n, a.n_f, a.complete);
-    if ((e = hipGetLastError()) == hipSuccess)
-      e = launch_units(mfma3_complete_kernel, a, BI, nullptr, stream, kJRun, a.offs_run);
-  }
+  if (a.flag)  // both kernels: each exits at once unless the flag picks it
+    e = launch_units(mfma3_complete_kernel, a, BI, nullptr, stream, kJRun);
   if (e == hipSuccess)
-    e = a.f4 ? launch_units(mfma3_run_kernel, a, kRunTile, nullptr, stream, kJRun, a.offs_gen)
+    e = a.f4 ? launch_units(mfma3_run_kernel, a, kRunTile, nullptr, stream, kJRun)
              : launch_units(mfma3_kernel, a, BI, nullptr, stream);
   timing_end(stream);
   return e;

@@ -31,7 +31,6 @@ __device__ __forceinline__ void make_planes(unsigned w0, unsigned w1, unsigned& 
 }
 
 __global__ __launch_bounds__(256) void pop3_kernel(Triple3Args a, UnitGrid ug,
-                                                   const int64_t* __restrict__ offs,
                                                    int64_t unit_base, int64_t count) {
 #pragma clang fp contract(off)
   __shared__ unsigned sP[2][kStageWords][kTile], sO[2][kStageWords][kTile],
@@ -40,7 +39,7 @@ __global__ __launch_bounds__(256) void pop3_kernel(Triple3Args a, UnitGrid ug,
 
   const int64_t n = a.n;
   int64_t j, it, kt;
-  unit_coords(unit_base + xcd_unit(blockIdx.x, count), ug, offs, j, it, kt);
+  unit_at(unit_base + xcd_unit(blockIdx.x, count), ug, j, it, kt);
   const int64_t I0 = it * kTile, K0 = kt * kTile;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
 
