@@ -49,7 +49,7 @@ struct Pair2Args {
   // (each tile votes for itself).  Only for calls that do not accumulate.
   unsigned long long* flag;
   unsigned long long id;
-  // The rows as operands (operands.hip), in super-steps of 256 fields; null:
+  // The rows as operands (operands.h), in super-steps of 256 fields; null:
   // the kernels read the packed rows.
   const void* za;
   const void* zb;
@@ -329,6 +329,10 @@ struct TuneChoice {
 };
 // The one-shot variant that the environment forces (0 .. n_variants - 1), or -1.
 int tune_forced_oneshot(int n_variants);
+// Shape of a 2-way call on operands by its 32 x 32 tiles and fields: 0 = 64 x
+// 128 staged tiles, 1 = field-split 32 x 32 tiles, 2 = 64 x 64 staged tiles
+// (mfma2.hip).
+int operand_variant(int64_t tiles, int64_t n_f, bool selection);
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants);
 
 // Optional event timing around the main kernel of a launcher (no-ops unless

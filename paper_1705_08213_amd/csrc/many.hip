@@ -1,31 +1,33 @@
 // many.hip -- many independent 2-way problems in one persistent launch.
 //
-// Host side: every problem gets a tile variant from the tune table (by its
-// size class), its tiles become work items (problem, tile), and the items are
-// ordered longest first (cost ~ tile pairs x n_f: the LPT rule), so the tail
-// of the launch is made of the cheapest tiles.  Descriptors and items live in
-// a device buffer owned by a cache entry keyed on the batch (every descriptor
-// field, the path and gamma).  On first sight of a batch the two launches
-// below are captured into a HIP graph; later calls with the same batch only
-// replay the graph on the caller's stream.
+// Host side: every problem gets a tile variant, its tiles become work items
+// (problem, tile), and the items are ordered longest first (cost ~ tile pairs
+// x n_f: the LPT rule), so the tail of the launch is made of the cheapest
+// tiles.  Descriptors, items and (fp4) the rows' operands live in a device
+// buffer owned by a cache entry keyed on the batch (every descriptor field,
+// the path and gamma).  On first sight of a batch the launches below are
+// captured into a HIP graph; later calls with the same batch only replay the
+// graph on the caller's stream.
 //
-// Device side:
+// Device side, fp4 (operands.h, tile2o.h):
+//   1. operands_many_kernel: counts and operands of every 16-row block;
+//   2. one launch per tile variant in the batch (the one-shot kernels' shapes:
+//      0 = 64 x 128 staged, 1 = 32 x 32 field-split, 2 = 64 x 64 staged), a
+//      workgroup per item.
+// Packed rows (int8, popcount, fp4 batches whose operands find no room):
 //   1. count_many_kernel: 1-way counts of every row of every problem (one
-//      wave per row), and the persistent work counter reset to 0 (a kernel
+//      wave per row), and the persistent work counters reset to 0 (a kernel
 //      store, so graphs hold no memset node);
 //   2. many_*_kernel, one persistent launch per tile variant in the batch: a
 //      grid of a few workgroups per compute unit (the tune table's figure
 //      for the variant's problems, else 2); each workgroup takes the next
 //      item of its variant's list with an atomic on that list's counter and
 //      computes the tile with the same device code as the one-shot kernels
-//      (tile2.h), until the list is exhausted.  The variants run on forked
-//      graph branches, concurrently.
-//
-// Tile variants (mfma path), workgroup tile (wave tile): 0 = 128 x 64
-// (64 x 32), 1 = 64 x 32 (32 x 16), 2 = 64 x 64 (32 x 32), 3 = 32 x 32
-// (16 x 16).  A triangle is cut into squares of the workgroup tile's height,
-// each one or two workgroup tiles.  The popcount path has one shape
-// (64 x 64).
+//      (tile2.h), until the list is exhausted.  Variants from the tune table,
+//      workgroup tile (wave tile): 0 = 128 x 64 (64 x 32), 1 = 64 x 32 (32 x
+//      16), 2 = 64 x 64 (32 x 32), 3 = 32 x 32 (16 x 16); the popcount path
+//      has one shape (64 x 64).
+// The variants run on forked graph branches, concurrently.
 #include <dlfcn.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -38,7 +40,8 @@
 #include <vector>
 
 #include "many.h"
-#include "tile2.h"
+#include "operands.h"
+#include "tile2o.h"
 
 namespace ccc {
 
@@ -53,6 +56,11 @@ struct ProbDesc {
   int64_t row_begin;  // first row of this problem in the concatenated row range
   int32_t variant;
   int32_t tiles_side;  // square tiles per side for the variant
+  // operands (operands.h): first 16-row block in the concatenated block range,
+  // their address and super-steps
+  int64_t block_begin;
+  void* z;
+  int64_t steps;
 };
 
 struct WorkItem {
@@ -92,6 +100,30 @@ __global__ __launch_bounds__(256) void count_many_kernel(const ProbDesc* __restr
   count_row_wave(p.v + r * p.ld, p.n_f, p.counts + 4 * r, 0);
 }
 
+// The same on operands: one workgroup per 16-row block writes its counts and
+// operands.
+__global__ __launch_bounds__(512) void operands_many_kernel(const ProbDesc* __restrict__ d,
+                                                            int n_probs) {
+  const int64_t block = blockIdx.x;
+  int lo = 0, hi = n_probs;  // d[lo].block_begin <= block < d[hi].block_begin
+  while (hi - lo > 1) {
+    int mid = (lo + hi) >> 1;
+    if (d[mid].block_begin <= block) lo = mid; else hi = mid;
+  }
+  const ProbDesc p = d[lo];
+  OperandJob job{};
+  job.n_f = p.n_f;
+  job.steps = p.steps;
+  job.shares = 1;
+  OperandSet s{};
+  s.v = p.v;
+  s.ld = p.ld;
+  s.n = p.n_v;
+  s.z = p.z;
+  s.counts = p.counts;
+  operand_block(job, s, block - p.block_begin, 0);
+}
+
 __device__ __forceinline__ Pair2Args pair_args(const ProbDesc& p, double gamma) {
   Pair2Args a;
   a.va = p.v; a.lda = p.ld; a.n_a = p.n_v;
@@ -114,8 +146,8 @@ __device__ __forceinline__ Pair2Args pair_args(const ProbDesc& p, double gamma) 
   a.sel = Select{nullptr, 0, 0.0, nullptr, nullptr, nullptr};
   a.flag = nullptr;
   a.id = 0;
-  a.za = a.zb = nullptr;
-  a.steps = 0;
+  a.za = a.zb = p.z;
+  a.steps = p.steps;
   a.part = nullptr;
   a.part_bytes = 0;
   return a;
@@ -181,6 +213,61 @@ __global__ __launch_bounds__(256) void many_pop_kernel(const ProbDesc* __restric
   }
 }
 
+// Work item of workgroup b: the workgroups of one XCD (b mod 8) take the items
+// in turns of 32, so that neighbouring tiles, which share row blocks, meet in
+// one L2 while the longest items still start first everywhere.
+__device__ __forceinline__ int item_of(int b, int n_items) {
+  const int turn = b / 256 * 256;
+  return turn + 256 <= n_items ? turn + b % 8 * 32 + b % 256 / 8 : b;
+}
+
+// Strips of 4 square rows, as the one-shot kernels on operands.
+constexpr int kManyStripRows = 4;
+
+// The batch's kernels on operands: one workgroup per item, dispatched longest
+// first (no counter: the dispatcher hands out workgroups as others end).
+template <int WM, int WN, int MIN_WG>
+__global__ __launch_bounds__(256, MIN_WG) void many_staged_kernel(
+    const ProbDesc* __restrict__ d, const WorkItem* __restrict__ items, int n_items,
+    double gamma) {
+  constexpr int BM = 32 * WM, BN = 32 * WN, PARTS = BN / BM;
+  static_assert(BN == PARTS * BM, "a square is whole workgroup tiles");
+  __shared__ u4 stage[3][2 * WM + 2 * WN][64];
+  const WorkItem w = items[item_of(blockIdx.x, n_items)];
+  const ProbDesc p = d[w.prob];
+  int64_t I, J;
+  strip_square(w.tile / PARTS, p.tiles_side, 0, p.tiles_side, I, J, kManyStripRows);
+  tile2::staged_tile<tile2::kDense, WM, WN>(pair_args(p, gamma),
+                                            (PARTS * I + w.tile % PARTS) * BM, J * BN, stage);
+}
+
+__global__ __launch_bounds__(256, 3) void many_split_kernel(const ProbDesc* __restrict__ d,
+                                                            const WorkItem* __restrict__ items,
+                                                            int n_items, double gamma) {
+  __shared__ v4i red[4][4][64];
+  __shared__ tile2::SplitSides sides;
+  const WorkItem w = items[item_of(blockIdx.x, n_items)];
+  const ProbDesc p = d[w.prob];
+  const Pair2Args a = pair_args(p, gamma);
+  int64_t I, J;
+  strip_square(w.tile, p.tiles_side, 0, p.tiles_side, I, J, kManyStripRows);
+  const int64_t I0 = I * tile2::kSplitTile, J0 = J * tile2::kSplitTile;
+  if (threadIdx.x >= 192)  // one wave; the barriers of the sums cover it
+    tile2::load_sides<tile2::kDense>(a, I0, J0, sides, threadIdx.x - 192, 64);
+  tile2::split_tile(
+      a, I0, J0, 0, a.steps, red,
+      [&] { return tile2::wave_complete<tile2::kSplitTile, tile2::kSplitTile>(a, I0, J0); },
+      [&](auto general, const auto& s) {
+        tile2::split_emit<tile2::kDense, general.value>(a, I0, J0, s, sides);
+      });
+}
+
+// Variants on operands: the one-shot kernels' shapes (operand_variant).
+constexpr int kOpSquare[3] = {128, 32, 64}, kOpParts[3] = {2, 1, 1};
+// Largest operand layout a batch keeps in its cache entry; beyond it (and when
+// it finds no room) the kernels read the packed rows.
+constexpr int64_t kManyOperandLimit = int64_t(2) << 30;
+
 // Tile variant and workgroups per CU of a problem from the kernel-shape
 // table (tune.hip).
 TuneChoice pick_variant(int64_t n_v, int64_t n_f, int path) {
@@ -206,6 +293,8 @@ struct Entry {
   int item_begin[kVariants] = {}, n_items[kVariants] = {};
   int64_t total_rows = 0;
   int path = 0;
+  bool operands = false;          // the rows as operands in dbuf
+  int64_t total_blocks = 0;       // 16-row blocks of all problems
   bool f4 = true;                 // fp4 operands (every n_f <= kF4MaxFields), else int8
   double gamma = 0;
   int grid[kVariants] = {};
@@ -246,7 +335,7 @@ std::vector<unsigned char> make_key(const ccc_problem* probs, int n, const ccc_o
   memcpy(k.data() + off, &dev, sizeof(int));
   off += sizeof(int);
   // the choices can be forced from the environment; make them part of the key
-  for (const char* name : {"CCC_MANY_VARIANT", "CCC_MANY_WG"}) {
+  for (const char* name : {"CCC_MANY_VARIANT", "CCC_MANY_WG", "CCC_OPERAND_LIMIT"}) {
     const char* env = getenv(name);
     const int forced = env ? atoi(env) + 1 : 0;
     memcpy(k.data() + off, &forced, sizeof(int));
@@ -272,6 +361,19 @@ hipError_t launch_variant(const Entry& e, int v, hipStream_t stream) {
                        e.n_items[v], e.counters + v, e.gamma);
     return hipGetLastError();
   }
+  if (e.operands) {
+    const dim3 grid((unsigned)e.n_items[v]), wg(256);
+    if (v == 0)
+      hipLaunchKernelGGL((many_staged_kernel<2, 4, 2>), grid, wg, 0, stream, e.d, items,
+                         e.n_items[v], e.gamma);
+    else if (v == 1)
+      hipLaunchKernelGGL(many_split_kernel, grid, wg, 0, stream, e.d, items, e.n_items[v],
+                         e.gamma);
+    else
+      hipLaunchKernelGGL((many_staged_kernel<2, 2, 4>), grid, wg, 0, stream, e.d, items,
+                         e.n_items[v], e.gamma);
+    return hipGetLastError();
+  }
   switch (v * 2 + (e.f4 ? 1 : 0)) {
     case 0: launch_mfma<0, false>(e, items, stream); break;
     case 1: launch_mfma<0, true>(e, items, stream); break;
@@ -289,8 +391,12 @@ hipError_t launch_variant(const Entry& e, int v, hipStream_t stream) {
 // the first non-empty one runs on a forked stream joined back before the
 // end, so the variants' kernels can share the GPU.
 hipError_t enqueue(const Entry& e, hipStream_t stream, bool fork) {
-  hipLaunchKernelGGL(count_many_kernel, dim3((unsigned)((e.total_rows + 3) / 4)), dim3(256), 0,
-                     stream, e.d, e.n_probs, e.total_rows, e.counters);
+  if (e.operands)
+    hipLaunchKernelGGL(operands_many_kernel, dim3((unsigned)e.total_blocks), dim3(512), 0, stream,
+                       e.d, e.n_probs);
+  else
+    hipLaunchKernelGGL(count_many_kernel, dim3((unsigned)((e.total_rows + 3) / 4)), dim3(256), 0,
+                       stream, e.d, e.n_probs, e.total_rows, e.counters);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   int first = -1, forked = 0;
@@ -315,8 +421,16 @@ hipError_t enqueue(const Entry& e, hipStream_t stream, bool fork) {
 }
 
 // Build descriptors and the LPT-ordered work list; allocate and upload.
-int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, Entry* e) {
+int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, bool operands,
+                Entry* e) {
   e->f4 = f4;
+  e->operands = operands;
+  int64_t blocks = 0, batch_tiles = 0;  // 32 x 32 tiles of the whole batch
+  auto small_tiles = [](int64_t n_v) {
+    const int64_t t = (n_v + tile2::kSplitTile - 1) / tile2::kSplitTile;
+    return t * (t + 1) / 2;
+  };
+  for (int p = 0; p < n; ++p) batch_tiles += small_tiles(probs[p].n_v);
   std::vector<ProbDesc> d(n);
   std::vector<WorkItem> items[kVariants];
   std::vector<int64_t> cost[kVariants];
@@ -336,8 +450,27 @@ int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, Ent
     const bool pop = o.path == CCC_PATH_POPCOUNT;
     const TuneChoice tc = pick_variant(q.n_v, q.n_f, pop ? CCC_PATH_POPCOUNT : CCC_PATH_MFMA);
     x.variant = pop ? 0 : tc.variant;
-    const int side = pop ? kPopTile : kSquare[x.variant];
-    const int halves = pop ? 1 : kHalves[x.variant];
+    if (operands) {
+      // A batch that fills the chip anyway takes the larger tiles, which read
+      // their operands less often, also for problems that alone would be cut
+      // small (us with every problem in shape 1 / 2: 64 problems of 64 .. 2048
+      // vectors 389 / 351, 64 of 500 .. 1000 274 / 232, but 8 of 300 .. 900
+      // 51 / 68).
+      int64_t t = small_tiles(q.n_v);
+      if (batch_tiles >= 6000 && q.n_v >= 256 && t < 6000) t = 6000;
+      const char* forced = getenv("CCC_MANY_VARIANT");  // 0 .. 2 of the operand shapes
+      x.variant = forced && q.n_f <= tile2::kStagedMaxFields && tc.variant < 3
+                      ? tc.variant
+                      : operand_variant(t, q.n_f, false);
+      // a work list of millions of small tiles costs the host more than they gain
+      if (x.variant == 1 && t > (1 << 23) && q.n_f <= tile2::kStagedMaxFields) x.variant = 0;
+    }
+    const int side = pop ? kPopTile : operands ? kOpSquare[x.variant] : kSquare[x.variant];
+    const int halves = pop ? 1 : operands ? kOpParts[x.variant] : kHalves[x.variant];
+    x.block_begin = blocks;
+    x.steps = operands ? operand_steps(q.n_f) : 0;
+    x.z = nullptr;
+    blocks += operand_blocks(q.n_v);
     const int64_t T = (q.n_v + side - 1) / side;
     if (T > 65536 || halves * (T * (T + 1) / 2) > 0x7FFFFFFF)
       return CCC_ERR_ARG;  // item indices must fit int32
@@ -369,8 +502,12 @@ int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, Ent
   const size_t d_bytes = (sizeof(ProbDesc) * n + 255) / 256 * 256;
   const size_t i_bytes = (sizeof(WorkItem) * sorted.size() + 255) / 256 * 256;
   const size_t c_bytes = 256;
-  const size_t s_bytes = (size_t)scratch_counts * 16;
-  if (hipMalloc(&e->dbuf, d_bytes + i_bytes + c_bytes + s_bytes) != hipSuccess) {
+  const size_t s_bytes = ((size_t)scratch_counts * 16 + 255) / 256 * 256;
+  size_t o_bytes = 0;
+  if (operands)
+    for (int p = 0; p < n; ++p) o_bytes += (size_t)operand_bytes(probs[p].n_v, probs[p].n_f);
+  e->total_blocks = blocks;
+  if (hipMalloc(&e->dbuf, d_bytes + i_bytes + c_bytes + s_bytes + o_bytes) != hipSuccess) {
     (void)hipGetLastError();
     return CCC_ERR_NOMEM;
   }
@@ -379,6 +516,11 @@ int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, Ent
   e->items = reinterpret_cast<WorkItem*>(base + d_bytes);
   e->counters = reinterpret_cast<unsigned*>(base + d_bytes + i_bytes);
   int32_t* scratch = reinterpret_cast<int32_t*>(base + d_bytes + i_bytes + c_bytes);
+  char* z = base + d_bytes + i_bytes + c_bytes + s_bytes;
+  for (int p = 0; p < n && operands; ++p) {
+    d[p].z = z;
+    z += operand_bytes(d[p].n_v, d[p].n_f);
+  }
   for (int p = 0; p < n; ++p)
     if (!d[p].counts) {
       d[p].counts = scratch;
@@ -433,7 +575,18 @@ int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f
     const auto t0 = std::chrono::steady_clock::now();
     e = new Entry();
     e->key = key;
-    int st = build_entry(probs, n_probs, opts, f4, e);
+    int64_t op_bytes = 0;
+    for (int p = 0; p < n_probs; ++p) op_bytes += operand_bytes(probs[p].n_v, probs[p].n_f);
+    const char* limit = getenv("CCC_OPERAND_LIMIT");
+    const bool operands = f4 && opts.path != CCC_PATH_POPCOUNT &&
+                          op_bytes <= (limit && *limit ? atoll(limit) : kManyOperandLimit);
+    int st = build_entry(probs, n_probs, opts, f4, operands, e);
+    if (st == CCC_ERR_NOMEM && operands) {  // the packed rows do
+      delete e;
+      e = new Entry();
+      e->key = key;
+      st = build_entry(probs, n_probs, opts, f4, false, e);
+    }
     if (st != CCC_OK) {
       destroy(e);
       return st;

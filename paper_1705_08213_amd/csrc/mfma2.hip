@@ -138,32 +138,19 @@ __global__ __launch_bounds__(256, MIN_WG) void mfma2_operand_kernel(Pair2Args a,
 // workgroups that take a share of the super-steps.  With one, the workgroup
 // emits its tile; with more, the partial sums go to a.part, [tile][split]
 // [block][plane][lane], and mfma2_split_finish_kernel adds and emits them.
-constexpr int kSplitTile = 32;
-__device__ __forceinline__ bool split_tile_of(const Pair2Args& a, int64_t t, int64_t tiles_side,
+using tile2::kSplitTile;
+__device__ __forceinline__ void split_tile_of(const Pair2Args& a, int64_t t, int64_t tiles_side,
                                               int64_t tiles_n, int64_t& I0, int64_t& J0) {
   int64_t I, J;
   tile_of<kSplitTile, kSplitTile, kOperandStripRows>(a, t, tiles_side, tiles_n, I, J);
   I0 = I * kSplitTile;
   J0 = J * kSplitTile;
-  return tile2::wave_complete<kSplitTile, kSplitTile>(a, I0, J0);
 }
 
-using SplitSides = tile2::Sides<kSplitTile, kSplitTile>;
-
-// This wave's block of the tile: its sums `s` to the output.
-template <tile2::Out OUT, bool GENERAL, int NP>
-__device__ __forceinline__ void split_emit(const Pair2Args& a, int64_t I0, int64_t J0,
-                                           const v4i (&s)[1][NP], SplitSides& sides) {
-  const int wave = threadIdx.x >> 6, m = wave & 1, n = wave >> 1;
-  tile2::load_sides<OUT>(a, I0, J0, sides, threadIdx.x, 256);
-  __syncthreads();
-  const int64_t i0 = I0 + 16 * m, j0 = J0 + 16 * n;
-  if (i0 >= a.n_a || j0 >= a.n_b || (a.tri && i0 >= j0 + 15)) return;  // no pair
-  tile2::emit_blocks<OUT, GENERAL>(a, sides, 16 * m, 16 * n, j0, s);
-}
+using tile2::SplitSides;
 
 template <tile2::Out OUT>
-__global__ __launch_bounds__(256, 2) void mfma2_split_kernel(Pair2Args a, int64_t tiles_side,
+__global__ __launch_bounds__(256, 3) void mfma2_split_kernel(Pair2Args a, int64_t tiles_side,
                                                              int64_t tiles_n, int splits) {
   __shared__ v4i red[4][4][64];
   __shared__ SplitSides sides;
@@ -171,24 +158,21 @@ __global__ __launch_bounds__(256, 2) void mfma2_split_kernel(Pair2Args a, int64_
   const int64_t b = xcd_unit(blockIdx.x, gridDim.x), t = b / splits;
   const int sp = (int)(b % splits);
   int64_t I0, J0;
-  const bool whole = split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
-  const int64_t s0 = a.steps * sp / splits, s1 = a.steps * (sp + 1) / splits;
-  v4i* part = reinterpret_cast<v4i*>(a.part) + ((b * 4 + wave) * 4) * 64 + lane;
-  auto run = [&](auto general, auto& s) {
-    tile2::split_sums<general.value>(a, I0, J0, s0, s1, red, s[0]);
-    if (splits == 1) {
-      split_emit<OUT, general.value>(a, I0, J0, s, sides);
-    } else {
-      tile2::static_for<general.value ? 4 : 1>([&](auto p) { part[64 * p.value] = s[0][p.value]; });
-    }
-  };
-  if (whole) {
-    v4i s[1][1];
-    run(std::false_type{}, s);
-  } else {
-    v4i s[1][4];
-    run(std::true_type{}, s);
-  }
+  split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
+  if (splits == 1 && threadIdx.x >= 192)  // one wave; the barriers of the sums cover it
+    tile2::load_sides<OUT>(a, I0, J0, sides, threadIdx.x - 192, 64);
+  tile2::split_tile(
+      a, I0, J0, a.steps * sp / splits, a.steps * (sp + 1) / splits, red,
+      [&] { return tile2::wave_complete<kSplitTile, kSplitTile>(a, I0, J0); },
+      [&](auto general, const auto& s) {
+        if (splits == 1) {
+          tile2::split_emit<OUT, general.value>(a, I0, J0, s, sides);
+        } else {
+          v4i* part = reinterpret_cast<v4i*>(a.part) + ((b * 4 + wave) * 4) * 64 + lane;
+          tile2::static_for<general.value ? 4 : 1>(
+              [&](auto p) { part[64 * p.value] = s[0][p.value]; });
+        }
+      });
 }
 
 template <tile2::Out OUT>
@@ -198,7 +182,10 @@ __global__ __launch_bounds__(256) void mfma2_split_finish_kernel(Pair2Args a, in
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t t = xcd_unit(blockIdx.x, gridDim.x);
   int64_t I0, J0;
-  const bool whole = split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
+  split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
+  const bool whole = tile2::wave_complete<kSplitTile, kSplitTile>(a, I0, J0);
+  tile2::load_sides<OUT>(a, I0, J0, sides, threadIdx.x, 256);
+  __syncthreads();
   const v4i* part = reinterpret_cast<const v4i*>(a.part) + ((t * splits * 4 + wave) * 4) * 64 + lane;
   auto run = [&](auto general, auto& s) {
     constexpr int NP = general.value ? 4 : 1;
@@ -206,7 +193,7 @@ __global__ __launch_bounds__(256) void mfma2_split_finish_kernel(Pair2Args a, in
 #pragma unroll 4
     for (int k = 1; k < splits; ++k)
       tile2::static_for<NP>([&](auto p) { s[0][p.value] += part[(k * 16 + p.value) * 64]; });
-    split_emit<OUT, general.value>(a, I0, J0, s, sides);
+    tile2::split_emit<OUT, general.value>(a, I0, J0, s, sides);
   };
   if (whole) {
     v4i s[1][1];
@@ -301,30 +288,15 @@ int64_t split_tiles(const Pair2Args& a, int64_t& tm, int64_t& tn) {
   return tile_grid<kSplitTile, kSplitTile>(a, tm, tn);
 }
 
-// The shape by the number of 32 x 32 tiles (n^2 / 2048 for a triangle) and
-// super-steps, from timings of whole calls with 1% missing, us for shapes 1 /
-// 2 / 0: 1500 x 9000 39 / 51 / 56, 2600 x 6000 69 / 65 / 70, 2600 x 20000 128 /
-// 134 / 144, 3500 x 4000 92 / 94 / 105, 4500 x 15000 273 / 249 / 298, 8000 x
-// 10000 656 / 569 / 586, 12000 x 4000 980 / 893 / 872, 16384 x 32768 6570 /
-// 5880 / 5660.  Small tiles give a small call more workgroups and a shorter
-// chain each; large ones read their operands less often.  With very short
-// fields a call is its output, and the 32 x 32 tiles, one block per wave,
-// start storing at once: 12000 x 1000 719 / 862 / 835.  A selection stores
-// little, so its smaller tiles pay for longer (12000 x 8009: 957 / 1000 for
-// shapes 2 / 0).
 OperandShape operand_shape(const Pair2Args& a) {
   int64_t tm, tn;
   const int64_t tiles = split_tiles(a, tm, tn);
   OperandShape s{0, 1};
   const int forced = tune_forced_oneshot(kOneShotVariants);
-  if (a.n_f > tile2::kStagedMaxFields)
-    s.variant = 1;  // four waves' sums, each exact
-  else if (forced >= 0)
+  if (forced >= 0 && a.n_f <= tile2::kStagedMaxFields)
     s.variant = forced;
-  else if (tiles < 6000 || a.n_f <= 1024)
-    s.variant = 1;
-  else if (tiles < 50000 || (a.sel.count && a.steps < 64))
-    s.variant = 2;
+  else
+    s.variant = operand_variant(tiles, a.n_f, a.sel.count != nullptr);
   if (s.variant == 1 && tiles > 0) {
     // Enough workgroups for two per CU, but no share below 16 super-steps:
     // the sums' way through memory and the second launch cost about 5 us
@@ -396,6 +368,23 @@ hipError_t launch_operands_out(const Pair2Args& a, hipStream_t stream) {
 }
 
 }  // namespace
+
+// The shape by the number of 32 x 32 tiles (n^2 / 2048 for a triangle) and
+// super-steps, from timings of whole calls with 1% missing, us for shapes 1 /
+// 2 / 0: 1500 x 9000 39 / 51 / 56, 2600 x 6000 69 / 65 / 70, 2600 x 20000 128 /
+// 134 / 144, 3500 x 4000 92 / 94 / 105, 4500 x 15000 273 / 249 / 298, 8000 x
+// 10000 656 / 569 / 586, 12000 x 4000 980 / 893 / 872, 16384 x 32768 6570 /
+// 5880 / 5660.  Small tiles give a small call more workgroups and a shorter
+// chain each; large ones read their operands less often.  With very short
+// fields a call is its output, and the 32 x 32 tiles, one block per wave,
+// start storing at once: 12000 x 1000 719 / 862 / 835.  A selection stores
+// little, so its smaller tiles pay for longer (12000 x 8009: 957 / 1000 for
+// shapes 2 / 0).
+int operand_variant(int64_t tiles, int64_t n_f, bool selection) {
+  if (n_f > tile2::kStagedMaxFields) return 1;  // four waves' sums, each exact
+  if (tiles < 6000 || n_f <= 1024) return 1;
+  return tiles < 50000 || (selection && n_f < 16384) ? 2 : 0;
+}
 
 size_t mfma2_part_bytes(const Pair2Args& a) {
   const OperandShape s = operand_shape(a);

@@ -1,5 +1,5 @@
 // tile2o.h -- 2-way tally tiles on fp4 operands that the pre-pass has laid out
-// (operands.hip): device bodies of the one-shot kernels (mfma2.hip) and the
+// (operands.h): device bodies of the one-shot kernels (mfma2.hip) and the
 // persistent batched ones (many.hip).
 //
 // A tile needs the four sums of the planes W = rho(1) + 3 [missing], the
@@ -381,17 +381,22 @@ __device__ __forceinline__ void complete_tile(const Pair2Args& a, int64_t I0, in
   });
 }
 
+constexpr int kSplitTile = 32;
+using SplitSides = Sides<kSplitTile, kSplitTile>;
+
 // Field-split tile: 32 x 32 pairs at (I0, J0) whose super-steps [s0, s1) are
 // shared out over the workgroup's four waves, each multiplying the whole tile
 // over its quarter from registers (1 KB contiguous loads, no barrier), so
 // that a call with few tiles still fills the chip and a short chain of steps
 // ends early.  The four partial sums, whole numbers, meet in LDS (`red`,
-// 16 KB), after which wave w holds block (w & 1, w >> 1) of the tile in `out`.
-// A wave's own sum stays exact up to 4 kStagedMaxFields fields.
-template <bool GENERAL, int NP>
-__device__ __forceinline__ void split_sums(const Pair2Args& a, int64_t I0, int64_t J0, int64_t s0,
-                                           int64_t s1, v4i (*red)[4][64], v4i (&out)[NP]) {
-  static_assert(NP == (GENERAL ? 4 : 1), "sums");
+// 16 KB), after which wave w holds block (w & 1, w >> 1) of the tile, given to
+// done(general, sums).  A wave's own sum stays exact up to 4 kStagedMaxFields
+// fields.  These tiles are short (a few dozen steps at most), so what a wave
+// waits for at the start goes out together: the counts of the vote `whole()`
+// (every row of the tile complete) and the first two steps' loads.
+template <typename Vote, typename Done>
+__device__ __forceinline__ void split_tile(const Pair2Args& a, int64_t I0, int64_t J0, int64_t s0,
+                                           int64_t s1, v4i (*red)[4][64], Vote whole, Done done) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
   gbytes base[4];
@@ -399,56 +404,78 @@ __device__ __forceinline__ void split_sums(const Pair2Args& a, int64_t I0, int64
   for (int t = 0; t < 4; ++t)
     base[t] = t < 2 ? block_base(a.za, I0 / 16 + t, a.n_a, a.steps)
                     : block_base(a.zb, J0 / 16 + t - 2, a.n_b, a.steps);
-  v4f acc[2][2][NP];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < 2; ++n)
-#pragma unroll
-      for (int e = 0; e < NP; ++e) acc[m][n][e] = v4f{0, 0, 0, 0};
   typedef const __attribute__((address_space(1))) u4* gu4;
   auto load = [&](int64_t s, u4 (&x)[4]) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) x[t] = *(gu4)(base[t] + s * 1024 + 16 * lane);
   };
-  auto multiply = [&](const u4 (&x)[4]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      v8i bw[2], bm[2];
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-        operands32<GENERAL>(word_of(x[2 + n], 2 * h), word_of(x[2 + n], 2 * h + 1), bw[n], bm[n]);
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        v8i aw, am;
-        operands32<GENERAL>(word_of(x[m], 2 * h), word_of(x[m], 2 * h + 1), aw, am);
-        multiply_row<GENERAL>(aw, am, bw, bm, acc[m]);
-      }
-    }
-  };
   const int64_t len = s1 - s0, b = s0 + len * wave / 4, e = s0 + len * (wave + 1) / 4;
   u4 x[4], y[4];
   if (b < e) load(b, x);
-  int64_t s = b;
-  for (; s + 1 < e; s += 2) {
-    load(s + 1, y);
-    multiply(x);
-    if (s + 2 < e) load(s + 2, x);
-    multiply(y);
-  }
-  if (s < e) multiply(x);
-  // block k = 2n + m of plane p from every wave, added by wave k
+  auto sums = [&](auto general) {
+    constexpr bool GENERAL = decltype(general)::value;
+    constexpr int NP = GENERAL ? 4 : 1;
+    v4f acc[2][2][NP];
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const v4f f = acc[k & 1][k >> 1][p];
-      red[wave][k][lane] = v4i{f4_count(f[0]), f4_count(f[1]), f4_count(f[2]), f4_count(f[3])};
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) acc[m][n][p] = v4f{0, 0, 0, 0};
+    auto multiply = [&](const u4 (&x)[4]) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        v8i bw[2], bm[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+          operands32<GENERAL>(word_of(x[2 + n], 2 * h), word_of(x[2 + n], 2 * h + 1), bw[n],
+                              bm[n]);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          v8i aw, am;
+          operands32<GENERAL>(word_of(x[m], 2 * h), word_of(x[m], 2 * h + 1), aw, am);
+          multiply_row<GENERAL>(aw, am, bw, bm, acc[m]);
+        }
+      }
+    };
+    int64_t s = b;
+    for (; s + 1 < e; s += 2) {
+      load(s + 1, y);
+      multiply(x);
+      if (s + 2 < e) load(s + 2, x);
+      multiply(y);
     }
-    __syncthreads();
-    out[p] = red[0][wave][lane] + red[1][wave][lane] + red[2][wave][lane] + red[3][wave][lane];
-    __syncthreads();
-  }
+    if (s < e) multiply(x);
+    // block k = 2n + m of plane p from every wave, added by wave k
+    v4i out[1][NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const v4f f = acc[k & 1][k >> 1][p];
+        red[wave][k][lane] = v4i{f4_count(f[0]), f4_count(f[1]), f4_count(f[2]), f4_count(f[3])};
+      }
+      __syncthreads();
+      out[0][p] = red[0][wave][lane] + red[1][wave][lane] + red[2][wave][lane] + red[3][wave][lane];
+      __syncthreads();
+    }
+    done(general, out);
+  };
+  if (whole())
+    sums(std::false_type{});
+  else
+    sums(std::true_type{});
+}
+
+// This wave's block of the tile: its sums `s` to the output.  The workgroup
+// has filled `sides` before its last barrier.
+template <Out OUT, bool GENERAL, int NP>
+__device__ __forceinline__ void split_emit(const Pair2Args& a, int64_t I0, int64_t J0,
+                                           const v4i (&s)[1][NP], const SplitSides& sides) {
+  const int wave = threadIdx.x >> 6, m = wave & 1, n = wave >> 1;
+  const int64_t i0 = I0 + 16 * m, j0 = J0 + 16 * n;
+  if (i0 >= a.n_a || j0 >= a.n_b || (a.tri && i0 >= j0 + 15)) return;  // no pair
+  emit_blocks<OUT, GENERAL>(a, sides, 16 * m, 16 * n, j0, s);
 }
 
 }  // namespace tile2
