@@ -626,16 +626,26 @@ int ccc_2way_multi(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int s
   if (f4 < 0) return f4;
   if (n_v >= 2 && !tables && !ccc) return CCC_ERR_ARG;
   if (n_v == 0 || (n_v == 1 && !counts)) return CCC_OK;
+  // workspace: the counts (unless the caller's) and on fp4 the operands
   std::unique_lock<std::mutex> lock;
-  int32_t* cnt = counts;
-  if (!cnt) {
-    void* ws = nullptr;
-    if ((st = ccc::workspace((size_t)n_v * 32, stream, lock, &ws))) return st;
-    cnt = static_cast<int32_t*>(ws);
+  const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 32);
+  const size_t op_bytes = ccc::multi_operand_bytes(n_v, n_f, s);
+  bool operands = f4 && n_v >= 2 && n_f > 0 && (int64_t)op_bytes <= operand_limit();
+  void* ws = nullptr;
+  if (operands) {
+    st = ccc::workspace(cnt_bytes + op_bytes, stream, lock, &ws);
+    if (st == CCC_ERR_NOMEM) operands = false;  // the rows as given do
+    else if (st) return st;
   }
-  if (ccc::launch_multi_count(v, ld, n_v, n_f, s, cnt, stream) != hipSuccess) return CCC_ERR_HIP;
+  if (!operands && cnt_bytes && (st = ccc::workspace(cnt_bytes, stream, lock, &ws))) return st;
+  int32_t* cnt = counts ? counts : static_cast<int32_t*>(ws);
+  void* z = operands ? static_cast<char*>(ws) + cnt_bytes : nullptr;
+  const hipError_t e =
+      operands ? ccc::launch_multi_operands(v, ld, n_v, n_f, s, cnt, z, stream)
+               : ccc::launch_multi_count(v, ld, n_v, n_f, s, cnt, stream);
+  if (e != hipSuccess) return CCC_ERR_HIP;
   if (n_v < 2) return CCC_OK;
-  return ccc::launch_multi2(v, ld, n_v, n_f, s, tables, ccc, cnt, o.gamma, f4, stream) ==
+  return ccc::launch_multi2(v, ld, n_v, n_f, s, tables, ccc, cnt, o.gamma, f4, z, stream) ==
                  hipSuccess
              ? CCC_OK
              : CCC_ERR_HIP;

@@ -377,6 +377,11 @@ hipError_t launch_multi_count(const uint8_t* v, int64_t ld, int64_t n, int64_t n
                               int32_t* counts, hipStream_t stream);
 hipError_t launch_multi2(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int s,
                          int32_t* tables, double* ccc, const int32_t* counts, double gamma,
-                         int f4, hipStream_t stream);
+                         int f4, const void* z, hipStream_t stream);
+// The count pass that also writes the rows as fp4 operands (multi2.hip) to z,
+// multi_operand_bytes of them; launch_multi2 reads them when z is given.
+size_t multi_operand_bytes(int64_t n, int64_t n_f, int s);
+hipError_t launch_multi_operands(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int s,
+                                 int32_t* counts, void* z, hipStream_t stream);
 
 }  // namespace ccc

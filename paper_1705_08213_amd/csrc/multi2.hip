@@ -33,7 +33,7 @@
 // is multiplied.
 #include <type_traits>
 
-#include "tile2.h"
+#include "tile2o.h"
 
 namespace ccc {
 
@@ -425,6 +425,205 @@ __global__ __launch_bounds__(256, 2) void multi2_kernel(Multi2Args a, int64_t ti
   }
 }
 
+// The count pass that also writes the operands: one workgroup per block of 16
+// rows, its waves take the steps of 128 fields in turn.
+__global__ __launch_bounds__(1024) void multi_operands_kernel(
+    const uint8_t* __restrict__ v, int64_t ld, int64_t n, int64_t n_f, int s,
+    int32_t* __restrict__ counts, u4* __restrict__ z, int64_t steps, int pieces) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
+  const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int64_t b = blockIdx.x, row = 16 * b + rl;
+  const bool have = row < n;
+  const uint8_t* r = v + (have ? row : n - 1) * ld;
+  z += b * steps * pieces * 64 + lane;
+  unsigned c[4] = {0u, 0u, 0u, 0u};
+  auto put = [&](int64_t st, const u4& lo, const u4& hi) {
+    // piece 0 holds the low nibbles (states 0 and 1) of word q of both
+    // halves, piece 1 the high ones
+    constexpr unsigned kL = 0x0F0F0F0Fu, kH = 0xF0F0F0F0u;
+    u4 a, bb;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = (lo[q] & kL) | ((hi[q] & kL) << 4);
+      bb[q] = ((lo[q] & kH) >> 4) | (hi[q] & kH);
+    }
+    z[st * pieces * 64] = a;
+    if (pieces > 1) z[(st * pieces + 1) * 64] = bb;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {  // states t (piece 0) and 2 + t (piece 1)
+        const unsigned m1 = 0x11111111u << (2 * t), m2 = 0x22222222u << (2 * t);
+        c[t] += __popc(a[q] & m1) + 2 * __popc(a[q] & m2);
+        c[2 + t] += __popc(bb[q] & m1) + 2 * __popc(bb[q] & m2);
+      }
+  };
+  const u4 none = u4{0u, 0u, 0u, 0u};
+  const int64_t whole = n_f / 128;
+  int64_t st = wave;
+  for (; st + 3 * waves < whole; st += 4 * waves) {  // several loads in flight
+    u4 lo[4], hi[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint8_t* p = r + (st + t * waves) * 128 + 32 * g;
+      lo[t] = have ? *reinterpret_cast<const u4*>(p) : none;
+      hi[t] = have ? *reinterpret_cast<const u4*>(p + 16) : none;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) put(st + t * waves, lo[t], hi[t]);
+  }
+  for (; st < steps; st += waves) {
+    const int64_t ob = st * 128 + 32 * g;
+    put(st, have ? load_bytes16(r, ob, n_f) : none, have ? load_bytes16(r, ob + 16, n_f) : none);
+  }
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) c[a] += __shfl_xor(c[a], o);
+  __shared__ unsigned part[16][16][4];
+  if (lane < 16)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) part[wave][lane][a] = c[a];
+  __syncthreads();
+  if (threadIdx.x < 16 && 16 * b + threadIdx.x < n) {
+    unsigned t[4] = {0u, 0u, 0u, 0u};
+    for (int w = 0; w < waves; ++w)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) t[a] += part[w][threadIdx.x][a];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      if (a >= s) t[a] = 0;
+    v4i* o = reinterpret_cast<v4i*>(counts + kMultiCountStride * (16 * b + threadIdx.x));
+    o[0] = v4i{(int)t[0], (int)t[1], (int)t[2], (int)t[3]};
+    o[1] = v4i{(int)((t[0] + t[1] + t[2] + t[3]) >> 1), 0, 0, 0};
+  }
+}
+
+// A step's operand of state A from its piece.
+template <int A>
+__device__ __forceinline__ v8i piece_operand(const u4& p) {
+  constexpr unsigned k = 0x33333333u;
+  if constexpr (A % 2 == 0) {
+    return v8i{(int)(p.x & k), (int)(p.y & k), (int)(p.z & k), (int)(p.w & k), 0, 0, 0, 0};
+  } else {  // the bits that cross between the words land in bits 30-31, dropped
+    unsigned a, b, c, d;
+    tile2::shr_pair<2>(p.x, p.y, a, b);
+    tile2::shr_pair<2>(p.z, p.w, c, d);
+    return v8i{(int)(a & k), (int)(b & k), (int)(c & k), (int)(d & k), 0, 0, 0, 0};
+  }
+}
+template <int S, int P>
+__device__ __forceinline__ void piece_operands(const u4 (&p)[P], v8i (&o)[S]) {
+  o[0] = piece_operand<0>(p[0]);
+  o[1] = piece_operand<1>(p[0]);
+  if constexpr (S > 2) o[2] = piece_operand<2>(p[1]);
+  if constexpr (S > 3) o[3] = piece_operand<3>(p[1]);
+}
+
+template <int S>
+constexpr int kMultiPieces = S > 2 ? 2 : 1;
+
+template <int S>
+__global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, const void* z,
+                                                                int64_t steps,
+                                                                int64_t tiles_side) {
+  constexpr int WM = MultiShape<S, true>::WM, WN = MultiShape<S, true>::WN;
+  constexpr int BM = 32 * WM, BN = 32 * WN, PARTS = BM / BN, P = kMultiPieces<S>;
+  constexpr int ND = (2 * WM + 2 * WN) * P, DPW = ND / 4;
+  static_assert(ND % 4 == 0, "pieces split evenly over the waves");
+  __shared__ u4 stage[3][ND][64];
+  const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
+  const int64_t b = xcd_unit(blockIdx.x, gridDim.x);
+  int64_t sq_i, sq_j;
+  strip_square(b / PARTS, tiles_side, 0, tiles_side, sq_i, sq_j);
+  const int64_t I0 = sq_i * BM, J0 = (sq_j * PARTS + b % PARTS) * BN;
+  const int64_t row0 = I0 + (wave & 1) * 16 * WM, col0 = J0 + (wave >> 1) * 16 * WN;
+  const bool active = !(row0 >= a.n || col0 >= a.n || row0 >= col0 + 16 * WN - 1);
+  const int64_t last = (a.n + 15) / 16 - 1;
+  gbytes base[DPW];
+#pragma unroll
+  for (int t = 0; t < DPW; ++t) {
+    const int d = DPW * wave + t, blk = d / P, pc = d % P;
+    const int64_t x = blk < 2 * WM ? I0 / 16 + blk : J0 / 16 + blk - 2 * WM;
+    base[t] = (gbytes)z + ((x < last ? x : last) * steps * P + pc) * 1024;
+  }
+  if (!active) {  // only copies and meets the barriers
+    tile2::ring_loop<ND>(base, steps, stage, [](const u4 (&)[ND][64]) {}, P * 1024);
+    return;
+  }
+  v4f acc[WM][WN][S * S];
+#pragma unroll
+  for (int m = 0; m < WM; ++m)
+#pragma unroll
+    for (int n = 0; n < WN; ++n)
+#pragma unroll
+      for (int x = 0; x < S * S; ++x) acc[m][n][x] = v4f{0, 0, 0, 0};
+  const int ma = (wave & 1) * WM * P, nb = (2 * WM + (wave >> 1) * WN) * P;
+  tile2::ring_loop<ND>(
+      base, steps, stage,
+      [&](const u4 (&buf)[ND][64]) {
+        v8i B[WN][S];
+#pragma unroll
+        for (int n = 0; n < WN; ++n) {
+          u4 p[P];
+#pragma unroll
+          for (int k = 0; k < P; ++k) p[k] = buf[nb + n * P + k][lane];
+          piece_operands<S>(p, B[n]);
+        }
+#pragma unroll
+        for (int m = 0; m < WM; ++m) {
+          u4 p[P];
+#pragma unroll
+          for (int k = 0; k < P; ++k) p[k] = buf[ma + m * P + k][lane];
+          v8i A[S];
+          piece_operands<S>(p, A);
+#pragma unroll
+          for (int n = 0; n < WN; ++n)
+#pragma unroll
+            for (int x = 0; x < S * S; ++x)
+              acc[m][n][x] = tile2::mfma_f4(A[x / S], B[n][x % S], acc[m][n][x]);
+        }
+      },
+      P * 1024);
+
+  // Epilogue: lane holds rows 4g + e of column rl of each 16x16 block.
+  const bool want_w = a.ccc != nullptr;
+#pragma unroll
+  for (int n = 0; n < WN; ++n) {
+    const int64_t j = col0 + 16 * n + rl;
+    double wj[S];
+    if (want_w) multi_factors<S>(a, j, wj);
+#pragma unroll
+    for (int m = 0; m < WM; ++m)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = row0 + 16 * m + 4 * g + e;
+        if (!(i < j && j < a.n)) continue;
+        double wi[S];
+        if (want_w) multi_factors<S>(a, i, wi);
+        int t[S * S];
+#pragma unroll
+        for (int x = 0; x < S * S; ++x) t[x] = tile2::f4_count(acc[m][n][x][e]);
+        multi_store<S>(a, pair_index(a.n, i, j), t, wi, wj);
+      }
+  }
+}
+
+template <int S>
+hipError_t launch_multi2_operands(const Multi2Args& a, const void* z, hipStream_t stream) {
+  constexpr int BM = 32 * MultiShape<S, true>::WM, BN = 32 * MultiShape<S, true>::WN;
+  const int64_t T = (a.n + BM - 1) / BM;
+  const int64_t ntiles = (BM / BN) * (T * (T + 1) / 2);
+  if (ntiles <= 0) return hipSuccess;
+  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+  timing_begin("multi2", stream);
+  hipLaunchKernelGGL(multi2_operand_kernel<S>, dim3((unsigned)ntiles), dim3(256), 0, stream, a, z,
+                     (a.n_f + 127) / 128, T);
+  timing_end(stream);
+  return hipGetLastError();
+}
+
 template <int S, bool F4>
 hipError_t launch_multi2_shape(const Multi2Args& a, hipStream_t stream) {
   constexpr int BM = 32 * MultiShape<S, F4>::WM, BN = 32 * MultiShape<S, F4>::WN;
@@ -445,6 +644,20 @@ hipError_t launch_multi2_s(const Multi2Args& a, int f4, hipStream_t stream) {
 
 }  // namespace
 
+size_t multi_operand_bytes(int64_t n, int64_t n_f, int s) {
+  return (size_t)(operand_blocks(n) * ((n_f + 127) / 128)) * (s > 2 ? 2048 : 1024);
+}
+
+hipError_t launch_multi_operands(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int s,
+                                 int32_t* counts, void* z, hipStream_t stream) {
+  if (n <= 0) return hipSuccess;
+  const int64_t steps = (n_f + 127) / 128;
+  hipLaunchKernelGGL(multi_operands_kernel, dim3((unsigned)operand_blocks(n)),
+                     dim3(steps > 16 ? 1024 : 256), 0, stream, v, ld, n, n_f, s, counts,
+                     static_cast<u4*>(z), steps, s > 2 ? 2 : 1);
+  return hipGetLastError();
+}
+
 hipError_t launch_multi_count(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int s,
                               int32_t* counts, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
@@ -455,8 +668,14 @@ hipError_t launch_multi_count(const uint8_t* v, int64_t ld, int64_t n, int64_t n
 
 hipError_t launch_multi2(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int s,
                          int32_t* tables, double* ccc, const int32_t* counts, double gamma,
-                         int f4, hipStream_t stream) {
+                         int f4, const void* z, hipStream_t stream) {
   Multi2Args a{v, ld, n, n_f, tables, ccc, counts, gamma};
+  if (f4 && z) switch (s) {
+      case 2: return launch_multi2_operands<2>(a, z, stream);
+      case 3: return launch_multi2_operands<3>(a, z, stream);
+      case 4: return launch_multi2_operands<4>(a, z, stream);
+      default: return hipErrorInvalidValue;
+    }
   switch (s) {
     case 2: return launch_multi2_s<2>(a, f4, stream);
     case 3: return launch_multi2_s<3>(a, f4, stream);

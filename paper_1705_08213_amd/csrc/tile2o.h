@@ -162,7 +162,7 @@ __device__ __forceinline__ void copy_async(gbytes base, uint32_t off, uint32_t d
 
 // Steps 0 .. n - 1 of a workgroup of four waves whose ND pieces of 1 KB per
 // step travel into a ring of three LDS buffers, two steps ahead, split over
-// the waves: wave w copies pieces DPW w + t from base[t] + s * 1024.  One
+// the waves: wave w copies pieces DPW w + t from base[t] + s * stride.  One
 // barrier per step says that every piece of the step has landed and that the
 // buffer read one step earlier is free.  Every wave must call it; body(buf)
 // multiplies a step.  Two steps ahead, not one: a step is some 1100 to 2200
@@ -170,7 +170,8 @@ __device__ __forceinline__ void copy_async(gbytes base, uint32_t off, uint32_t d
 // two workgroups have theirs in flight.
 template <int ND, typename Body>
 __device__ __forceinline__ void ring_loop(const gbytes (&base)[ND / 4], int64_t n,
-                                          u4 (*stage)[ND][64], Body body) {
+                                          u4 (*stage)[ND][64], Body body,
+                                          uint32_t stride = 1024) {
   constexpr int DPW = ND / 4;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
@@ -189,7 +190,7 @@ __device__ __forceinline__ void ring_loop(const gbytes (&base)[ND / 4], int64_t 
     for (int t = 0; t < DPW; ++t) {
       copy_async(cur[t], 16 * lane,
                  __builtin_amdgcn_readfirstlane(dst0 + buf * kBuf + 1024 * t));
-      cur[t] += 1024;
+      cur[t] += stride;
     }
   };
   if (n > 0) issue(0);

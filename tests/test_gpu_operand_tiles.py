@@ -100,3 +100,20 @@ def test_capture_keeps_its_workspace():
         g.replay()
         torch.cuda.synchronize()
         _check(v, n_f, (tables, values, counts))
+
+
+@pytest.mark.parametrize("limit", ["", "0"])
+@pytest.mark.parametrize("s", [2, 3, 4])
+def test_multi_allelic_on_operands(s, limit, monkeypatch):
+    """Both routes of the multi-allelic call around its 128-field steps and
+    its tiles."""
+    if limit:
+        monkeypatch.setenv("CCC_OPERAND_LIMIT", limit)
+    for n_v, n_f, missing in ((2, 1, 0.0), (33, 127, 0.02), (65, 128, 0.3), (97, 129, 0.0),
+                              (130, 5000, 0.01), (64, 9000, 1.0)):
+        say("multi operands", s, limit, n_v, n_f)
+        v = synth.multi_hw(n_v, n_f, s, seed=5500 + n_v, missing=missing)
+        t, c, _ = ccc.ccc_2way_multi(dev(v), n_f, s)
+        ot, oc = oracle.multi_two_way(v, n_f, s)
+        assert_tables_equal(host(t), ot)
+        assert_ccc_identical(host(c), oc)
