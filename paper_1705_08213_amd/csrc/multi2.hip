@@ -520,6 +520,57 @@ __device__ __forceinline__ void piece_operands(const u4 (&p)[P], v8i (&o)[S]) {
   if constexpr (S > 3) o[3] = piece_operand<3>(p[1]);
 }
 
+// Store R rows' 16 pairs each (row r: i0 + dr r, columns j0 ..), SS values of
+// type E per pair, so that every instruction writes whole stretches: lanes of
+// the group g0 + r hold row r's pairs in x and put them into `buf` (LDS of
+// this wave) in output order, then lane after lane takes 16-byte (or single)
+// pieces of it.  A pair's values stored by its own lane touch a line per lane
+// and instruction.
+template <int SS, int R, typename E, typename V>
+__device__ __forceinline__ void store_rows(const Multi2Args& a, E* out, const E (&x)[SS],
+                                           int g0, int64_t i0, int dr, int64_t j0, void* buf) {
+  constexpr int PPP = SS * sizeof(E) / sizeof(V), ROW = 16 * PPP, N = R * ROW;
+  static_assert(PPP * sizeof(V) == SS * sizeof(E), "whole pieces per pair");
+  const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
+  asm volatile("" ::: "memory");  // the wave's LDS accesses run in program order
+  if (g >= g0 && g < g0 + R) {
+    E* b = static_cast<E*>(buf) + ((g - g0) * 16 + rl) * SS;
+#pragma unroll
+    for (int q = 0; q < SS; ++q) b[q] = x[q];
+  }
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int t = 0; t < (N + 63) / 64; ++t) {
+    const int idx = 64 * t + lane, r = idx / ROW, pc = idx % ROW;
+    const int64_t i = i0 + dr * r, j = j0 + pc / PPP;
+    if ((N % 64 == 0 || idx < N) && i < j && j < a.n) {
+      V* o = reinterpret_cast<V*>(out + SS * pair_index(a.n, i, j0)) + pc;
+      *o = static_cast<const V*>(buf)[idx];
+    }
+  }
+  asm volatile("" ::: "memory");  // the buffer is reused by the next call
+}
+
+// The CCC values of table t (zero when no field is common).
+template <int S>
+__device__ __forceinline__ void multi_values(const int (&t)[S * S], const double (&wi)[S],
+                                             const double (&wj)[S], double (&r)[S * S]) {
+#pragma clang fp contract(off)
+  int sum = 0;
+#pragma unroll
+  for (int x = 0; x < S * S; ++x) sum += t[x];
+  const int m_ij = sum >> 2;  // fields where both are present
+  if (m_ij > 0) {
+    const double den = 4.0 * (double)m_ij, y = 1.0 / den;
+#pragma unroll
+    for (int x = 0; x < S * S; ++x)
+      r[x] = quot_rn((double)t[x], den, y) * wi[x / S] * wj[x % S];
+  } else {
+#pragma unroll
+    for (int x = 0; x < S * S; ++x) r[x] = 0.0;
+  }
+}
+
 template <int S>
 constexpr int kMultiPieces = S > 2 ? 2 : 1;
 
@@ -550,6 +601,7 @@ __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, co
   }
   if (!active) {  // only copies and meets the barriers
     tile2::ring_loop<ND>(base, steps, stage, [](const u4 (&)[ND][64]) {}, P * 1024);
+    __syncthreads();
     return;
   }
   v4f acc[WM][WN][S * S];
@@ -587,27 +639,52 @@ __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, co
       },
       P * 1024);
 
-  // Epilogue: lane holds rows 4g + e of column rl of each 16x16 block.
-  const bool want_w = a.ccc != nullptr;
+  // Epilogue: lane holds rows 4g + e of column rl of each 16x16 block.  The
+  // factors are read before the first store (a wait for a load also waits for
+  // every store issued before it), into this wave's part of the stage.
+  __syncthreads();  // every wave is done with the stage
+  constexpr int NS = 16 * (WM + WN);
+  constexpr int SS = S * S;
+  using TV = std::conditional_t<SS % 4 == 0, u4, int>;      // pieces of tables
+  using CV = std::conditional_t<SS % 2 == 0, u4, double>;   // and of CCC rows
+  constexpr int kOut = 4 * 16 * SS * sizeof(int);           // 4 rows' tables, or 2 rows' CCC
+  constexpr int kWave = (NS * S * (int)sizeof(double) + kOut + 15) / 16 * 16;
+  static_assert(4 * kWave <= sizeof(stage), "factors and store staging fit in the stage");
+  char* mine = reinterpret_cast<char*>(&stage[0][0][0]) + kWave * wave;
+  double(*w)[S] = reinterpret_cast<double(*)[S]>(mine + kOut);
+  if (a.ccc && lane < NS) {
+    double f[S];
+    multi_factors<S>(a, lane < 16 * WM ? row0 + lane : col0 + (lane - 16 * WM), f);
 #pragma unroll
-  for (int n = 0; n < WN; ++n) {
-    const int64_t j = col0 + 16 * n + rl;
-    double wj[S];
-    if (want_w) multi_factors<S>(a, j, wj);
-#pragma unroll
-    for (int m = 0; m < WM; ++m)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t i = row0 + 16 * m + 4 * g + e;
-        if (!(i < j && j < a.n)) continue;
-        double wi[S];
-        if (want_w) multi_factors<S>(a, i, wi);
-        int t[S * S];
-#pragma unroll
-        for (int x = 0; x < S * S; ++x) t[x] = tile2::f4_count(acc[m][n][x][e]);
-        multi_store<S>(a, pair_index(a.n, i, j), t, wi, wj);
-      }
+    for (int x = 0; x < S; ++x) w[lane][x] = f[x];
   }
+  static_assert(NS <= 64, "one lane per row and column");
+#pragma unroll
+  for (int m = 0; m < WM; ++m)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double wi[S];
+#pragma unroll
+      for (int x = 0; x < S; ++x) wi[x] = w[16 * m + 4 * g + e][x];
+#pragma unroll
+      for (int n = 0; n < WN; ++n) {
+        const int64_t j0 = col0 + 16 * n, ib = row0 + 16 * m + e;  // rows ib + 4g
+        if (ib >= j0 + 15 || ib >= a.n || j0 >= a.n) continue;     // uniform: no pair
+        double wj[S];
+#pragma unroll
+        for (int x = 0; x < S; ++x) wj[x] = w[16 * WM + 16 * n + rl][x];
+        int t[SS];
+#pragma unroll
+        for (int x = 0; x < SS; ++x) t[x] = tile2::f4_count(acc[m][n][x][e]);
+        if (a.tables) store_rows<SS, 4, int, TV>(a, a.tables, t, 0, ib, 4, j0, mine);
+        if (a.ccc) {
+          double r[SS];
+          multi_values<S>(t, wi, wj, r);
+          store_rows<SS, 2, double, CV>(a, a.ccc, r, 0, ib, 4, j0, mine);
+          store_rows<SS, 2, double, CV>(a, a.ccc, r, 2, ib + 8, 4, j0, mine);
+        }
+      }
+    }
 }
 
 template <int S>
