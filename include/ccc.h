@@ -48,10 +48,18 @@
  *  - A negative return code comes from argument validation done before any
  *    work is enqueued; outputs are then untouched.  CCC_ERR_HIP means a HIP
  *    call or launch failed after validation.
- *  - The library keeps a per-device workspace (allocated on first need,
- *    grown on demand, released by ccc_release_workspace).  Calls are
- *    reentrant per stream; calls on different streams of one device that
- *    need the workspace must be ordered by the caller.
+ *  - The library keeps one workspace per device and stream (allocated on
+ *    first need, grown on demand, at most 16 per device besides those that a
+ *    captured graph holds, released by ccc_release_workspace), so that calls
+ *    on different streams never share scratch.  A call holds a lock while it
+ *    enqueues its kernels.  Besides what the calls below state, a workspace
+ *    holds the fp4 calls' operands: ceil(n/16) 16-row blocks of ceil(n_f/256)
+ *    KB (2-way), of ceil(n_f/128) KB (multi-allelic, twice that for three and
+ *    four states), and the partial sums of split tiles (16 KB a workgroup, at
+ *    most 32 MB).  Where the operands would pass 16 GiB ($CCC_OPERAND_LIMIT,
+ *    bytes) or find no memory, the call reads the packed rows instead, with
+ *    the same results.  A workspace used while its stream is captured stays
+ *    at its address until ccc_release_workspace.
  */
 #ifndef CCC_H
 #define CCC_H
@@ -143,13 +151,12 @@ int ccc_2way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int32_t* ta
  *   tables  int32 [C(n_v,3)][8] or NULL;  ccc double [C(n_v,3)][8] or NULL
  *   (at least one non-NULL);  counts as for ccc_2way.
  * n_v < 3 writes no tables.  CCC_ERR_RANGE if 8*n_f > INT32_MAX.
- * The path option selects the MFMA or popcount kernel.  Workspace: 8 bytes
- * per pair of 64-row tiles (work-unit offsets), 16 bytes per vector when
- * counts is NULL, and on the MFMA path the rho(1) Gram matrix that
- * complete-data units read: 4 bytes per entry over the rows from the first
- * staged row (i_begin of ccc_3way_rows, else 0) rounded down to 64, so n_v^2
- * * 4 bytes for a whole call; beyond 32768 such rows it is not kept and every
- * unit takes the general form.
+ * The path option selects the MFMA or popcount kernel.  Workspace: 256 bytes,
+ * 16 bytes per vector when counts is NULL, and on the MFMA path the rho(1)
+ * Gram matrix that complete-data units read: 4 bytes per entry over the rows
+ * from the first staged row (i_begin of ccc_3way_rows, else 0) rounded down to
+ * 64, so n_v^2 * 4 bytes for a whole call; beyond 32768 such rows it is not
+ * kept and every unit takes the general form.
  */
 int ccc_3way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int32_t* tables,
              double* ccc, int32_t* counts, const ccc_opts* opts, hipStream_t stream);
@@ -172,7 +179,7 @@ int ccc_3way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int32_t* ta
  * 4*n_f > INT32_MAX for this chunk; keeping the accumulated total within
  * range is the caller's duty (the counts' m_i bound it).  n_a or n_b == 0 is
  * valid and writes nothing.  A CCC_ACCUMULATE call uses (n_a + n_b) * 16 bytes
- * of the library workspace for its chunk's own counts.
+ * more of the workspace for its chunk's own counts.
  */
 int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* vb, int64_t n_b,
                    int64_t ldb, int64_t n_f, int32_t* tables, int32_t* counts_a,
@@ -243,7 +250,9 @@ typedef struct {
  * one persistent launch.  `probs` is a HOST array of n_probs descriptors
  * (device pointers inside).  Each problem gives exactly what ccc_2way would.
  * The launch sequence is captured once into a HIP graph per distinct batch
- * (same descriptors) and replayed on later calls with that batch.
+ * (same descriptors) and replayed on later calls with that batch; a batch
+ * keeps its fp4 operands (up to 2 GiB, else it reads the packed rows) as long
+ * as its graph, of which the library keeps eight.
  * Validation covers every problem before anything is enqueued.
  */
 int ccc_2way_many(const ccc_problem* probs, int n_probs, const ccc_opts* opts,
@@ -282,13 +291,13 @@ int ccc_2way_multi(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int s
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, validation and results as ccc_3way; it calls
  * no hipMalloc, hipFree or other allocating routine (with kernel timing off).
- * Its scratch (work-unit offsets, the counts when `counts` is NULL, and the
- * complete-data Gram matrix) lives in a fixed device array of
+ * Its scratch (the complete-data flag, the counts when `counts` is NULL, and
+ * the Gram matrix) lives in a fixed device array of
  * CCC_NOALLOC_SCRATCH_BYTES per device, kept until the process ends, instead
- * of the library workspace.  CCC_ERR_RANGE when the unit offsets (8 bytes per
- * tile pair of each of three unit grids: two of 64-row tiles and one of
- * 32-row tiles, about 3 n_v^2 / 512 bytes in all) plus the counts (16 bytes
- * per vector when `counts` is NULL) exceed it, about n_v > 64,000.  The Gram
+ * of the library workspace.  CCC_ERR_RANGE when 8 bytes per tile pair of each
+ * of three unit grids (two of 64-row tiles and one of 32-row tiles, about
+ * 3 n_v^2 / 512 bytes in all) plus the counts (16 bytes per vector when
+ * `counts` is NULL) exceed it, about n_v > 64,000.  The Gram
  * matrix (4 n_v^2 bytes) is used only when it also fits (n_v up to about
  * 2500); otherwise every unit takes the general form, with the same results.  Every call on a
  * device shares that device's array: calls whose work overlaps on one device

@@ -723,7 +723,10 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
   if (a.flag && *a.flag != a.id) return;  // uniform: mfma3_complete_kernel covers the call
   __shared__ u4 raw[4][4][64];            // 16 KB: [step & 3][row block][lane]
   __shared__ u4 planes[2][4][2][2][64];   // 32 KB: [step & 1][block][half][rho(1), P][lane]
-  __shared__ u4 jm[4][4][16][3];          // 12 KB: [wave][group][half step][y, sg, p]
+  // 12 KB: [wave][group][half step, y / sg / p].  The groups are 49 pieces
+  // apart: a read takes one piece per group, and 48 apart the four would lie in
+  // the same banks.
+  __shared__ u4 jm[4][4][16 * 3 + 1];
   const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
   const int64_t n = a.n;
@@ -864,7 +867,7 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
     if (active && (st & 7) == 0) {  // uniform: the masks of steps st .. st + 7
       u4 y, sg, pm;
       masks_of(jw.x, jw.y, y, sg, pm);
-      u4* d = &jm[wave][g][rl][0];
+      u4* d = &jm[wave][g][3 * rl];
       d[0] = y;
       d[1] = sg;
       d[2] = pm;
@@ -892,7 +895,7 @@ __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGr
           KR[h][m] = planes[buf][2 + m][h][0][lane];
           KP[h][m] = planes[buf][2 + m][h][1][lane];
         }
-        const u4* ms = &jm[wave][g][2 * (st & 7) + h][0];
+        const u4* ms = &jm[wave][g][3 * (2 * (st & 7) + h)];
 #pragma unroll
         for (int x = 0; x < 3; ++x) M[h][x] = ms[x];
       };

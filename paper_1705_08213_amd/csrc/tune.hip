@@ -8,10 +8,13 @@
 //   mfma, popcount  the batched 2-way launch (ccc_2way_many), per path;
 //   oneshot         the one-shot 2-way MFMA kernel (ccc_2way, _rows, _select,
 //                   _block), by the larger side of the call.
+// The table serves the kernels that read packed rows (int8, popcount, and fp4
+// where the operands find no room); those on operands follow operand_variant
+// (mfma2.hip).
 // The table is read once from $CCC_TUNE_FILE, else from tune_gfx950.txt next
 // to the library.  A missing table or line gives variant 0.  For the
 // autotuner, $CCC_MANY_VARIANT and $CCC_MANY_WG force the batched choice and
-// $CCC_ONESHOT_VARIANT the one-shot one.
+// $CCC_ONESHOT_VARIANT the one-shot one, on packed rows and on operands alike.
 #include <dlfcn.h>
 #include <stdio.h>
 #include <stdlib.h>

@@ -117,3 +117,19 @@ def test_multi_allelic_on_operands(s, limit, monkeypatch):
         ot, oc = oracle.multi_two_way(v, n_f, s)
         assert_tables_equal(host(t), ot)
         assert_ccc_identical(host(c), oc)
+
+
+@pytest.mark.parametrize("n_v,n_f", [(225, 40), (257, 300), (289, 90)])
+def test_3way_complete_data_around_the_small_call_rule(n_v, n_f):
+    """Complete inputs on both sides of the unit count at which the 3-way call
+    takes its complete-data form, with and without one missing entry."""
+    v = synth.beta_hw(n_v, n_f, seed=5600 + n_v, missing=0.0)
+    for k in range(2):
+        if k:
+            v = v.copy()
+            v[n_v // 2, 0] = (v[n_v // 2, 0] & 0xFC) | 2
+        say("3way small rule", n_v, n_f, k)
+        t, c, _ = ccc.ccc_3way(dev(v), n_f)
+        ot, oc = oracle.three_way(v, n_f)
+        assert_tables_equal(host(t), ot)
+        assert_ccc_identical(host(c), oc)
