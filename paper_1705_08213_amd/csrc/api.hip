@@ -392,7 +392,7 @@ struct FixedScratch {
 
 // All 3-way variants: dense first-index rows [i_begin, i_end) or selection.
 // With `fixed`, the scratch comes from there instead of the workspace: the
-// call returns CCC_ERR_RANGE if the unit offsets and counts do not fit, and
+// call returns CCC_ERR_RANGE past the documented bound on n_v, and
 // leaves the Gram matrix out (every unit then takes the general form, same
 // results) when it does not fit beside them.
 int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_begin,

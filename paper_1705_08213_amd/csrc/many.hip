@@ -1,4 +1,4 @@
-// many.hip -- many independent 2-way problems in one persistent launch.
+// many.hip -- many independent 2-way problems in one call.
 //
 // Host side: every problem gets a tile variant, its tiles become work items
 // (problem, tile), and the items are ordered longest first (cost ~ tile pairs
@@ -225,7 +225,10 @@ __device__ __forceinline__ int item_of(int b, int n_items) {
 constexpr int kManyStripRows = 4;
 
 // The batch's kernels on operands: one workgroup per item, dispatched longest
-// first (no counter: the dispatcher hands out workgroups as others end).
+// first (no counter: the dispatcher hands out workgroups as others end).  64
+// problems of 64..2048 vectors and 1000..20000 fields: 470 us with persistent
+// launches on packed rows, 352 here, of which the host's marshalling is 223;
+// of 256..8192 and 1000..50000: 12.4-12.6 ms and 11.2.
 template <int WM, int WN, int MIN_WG>
 __global__ __launch_bounds__(256, MIN_WG) void many_staged_kernel(
     const ProbDesc* __restrict__ d, const WorkItem* __restrict__ items, int n_items,

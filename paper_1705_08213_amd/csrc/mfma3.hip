@@ -467,6 +467,10 @@ constexpr int64_t kJRun = 4;
 // buffers: raw(s + 1) has landed, planes(s) are written, and the buffers of
 // step s - 1 are free (raw(s + 2) goes into the buffer of raw(s), which was
 // read in step s - 1).  The last, padded step takes plain loads.
+//
+// Bound by the output stream (641 x 5003: 3.4-3.9 TB/s of rows that start
+// anywhere in a line; 1.41 ms a call before the count pass flagged incomplete
+// rows and the tables went out by plain stores, 1.23 since).
 __global__ __launch_bounds__(256, 3) void mfma3_complete_kernel(Triple3Args a, UnitGrid ug,
                                                                 int64_t unit_base,
                                                                 int64_t count) {
@@ -717,6 +721,10 @@ __global__ __launch_bounds__(256, 3) void mfma3_complete_kernel(Triple3Args a, U
 // wave's part of `jm`, and each half step reads its masks back (the 16
 // lanes of a group read one address).  The words of batch b + 1 are loaded
 // while batch b is multiplied.
+//
+// Bound by VALU and MFMA issue together: 30 cycles per 16-cycle MFMA, the
+// epilogue's fifth included.  720 x 16384: 4.02 ms with scaled MFMAs and
+// streaming tables, 3.76 without; 2048 x 16384: 77.5.
 __global__ __launch_bounds__(256, 2) void mfma3_run_kernel(Triple3Args a, UnitGrid ug,
                                                            int64_t unit_base, int64_t count) {
 #pragma clang fp contract(off)

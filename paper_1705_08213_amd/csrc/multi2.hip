@@ -30,7 +30,9 @@
 // state a of piece 0's word r (4 fields) in its low nibbles and of piece 1's
 // word r in its high nibbles, 3-4 VALU ops per 8 fields.  The next step's
 // pieces travel from memory into the wave's LDS stage while the current step
-// is multiplied.
+// is multiplied.  multi_operands_kernel writes the rows as such operands with
+// the counts and multi2_operand_kernel multiplies them; the form that reads the
+// one-byte rows runs where the operands find no room.
 #include <type_traits>
 
 #include "tile2o.h"
@@ -574,6 +576,11 @@ __device__ __forceinline__ void multi_values(const int (&t)[S * S], const double
 template <int S>
 constexpr int kMultiPieces = S > 2 ? 2 : 1;
 
+// The fp4 form on operands: the packed kernel's tiles and sums; copies are 1 KB
+// contiguous, an operand takes 1.9 VALU operations per MFMA instead of 5.3
+// (s = 4), and the rows' values leave through LDS.  Bound by its output, the
+// matrix cores 40% busy at 16384 fields.  s = 4: 4096 x 16384 1.50 ms from the
+// one-byte rows, 0.97 here; 16384 x 32768 38.9-39.2 and 26.0.
 template <int S>
 __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, const void* z,
                                                                 int64_t steps,

@@ -1,5 +1,6 @@
 // operands.h -- the pre-pass of the fp4 MFMA kernels (device code; kernels in
-// operands.hip and many.hip): one read of the packed rows gives the 1-way counts and the rows as matrix-core operands.
+// operands.hip and many.hip): one read of the packed rows gives the 1-way
+// counts and the rows as matrix-core operands.
 //
 // Layout: rows in blocks of 16, fields in super-steps of 256; super-step s of
 // block b is the 1 KB at z + (b * steps + s) * 1024.  Lane (g, rl) = 16 g + rl

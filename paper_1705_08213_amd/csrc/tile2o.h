@@ -322,7 +322,10 @@ __device__ __forceinline__ void emit_blocks(const Pair2Args& a, const Sides<NR, 
 }
 
 // One workgroup's tile of (32 WM) x (32 WN) pairs at (I0, J0), 2 x 2 waves;
-// `stage` is its LDS (three buffers), reused for the epilogue's inputs.
+// `stage` is its LDS (three buffers), reused for the epilogue's inputs.  Bound
+// by MFMA issue (matrix cores 65% busy over long fields, where power holds
+// the clock near 2.0 GHz), then by the output.  16384 x 32768: 6.50 ms from
+// packed rows, 5.69 here; 32768 x 65536: 45.2-48.1 and 41.2.
 template <Out OUT, int WM, int WN>
 __device__ __forceinline__ void staged_tile(const Pair2Args& a, int64_t I0, int64_t J0,
                                             u4 (*stage)[2 * WM + 2 * WN][64]) {
@@ -360,7 +363,9 @@ __device__ __forceinline__ void staged_tile(const Pair2Args& a, int64_t I0, int6
 
 // Tile of a call whose every row is complete: WW alone, so the accumulators
 // of a (16 WM) x (16 WN) wave tile are a quarter of the general form's and
-// the tile four times the size.
+// the tile four times the size.  Bound by its operands' reads past L2 beside
+// the output stream.  16000 x 40000: 3.55 ms from packed rows, 2.83 here;
+// 32768 x 65536: 19.4-20.5 and 15.7.
 template <Out OUT, int WM, int WN>
 __device__ __forceinline__ void complete_tile(const Pair2Args& a, int64_t I0, int64_t J0,
                                               u4 (*stage)[2 * WM + 2 * WN][64]) {
@@ -394,7 +399,9 @@ using SplitSides = Sides<kSplitTile, kSplitTile>;
 // done(general, sums).  A wave's own sum stays exact up to 4 kStagedMaxFields
 // fields.  These tiles are short (a few dozen steps at most), so what a wave
 // waits for at the start goes out together: the counts of the vote `whole()`
-// (every row of the tile complete) and the first two steps' loads.
+// (every row of the tile complete) and the first two steps' loads.  Bound by
+// the latency of that chain, and of the launches before it: 384 x 250007 481
+// us from packed rows and 61.5 here, 200 x 1337 24 and 14.
 template <typename Vote, typename Done>
 __device__ __forceinline__ void split_tile(const Pair2Args& a, int64_t I0, int64_t J0, int64_t s0,
                                            int64_t s1, v4i (*red)[4][64], Vote whole, Done done) {
