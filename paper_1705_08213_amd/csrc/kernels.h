@@ -169,6 +169,7 @@ __host__ __device__ __forceinline__ void pair_tiles(const UnitGrid& g, int64_t p
 
 // Unit u -> (first middle vector j of its run, I tile, K tile), given
 // offs[p] = units of all pairs before p (p = 0..pairs).
+// The host tests hold unit_at to it.
 __host__ __device__ __forceinline__ void unit_coords(int64_t u, const UnitGrid& g,
                                                      const int64_t* __restrict__ offs,
                                                      int64_t& j, int64_t& it, int64_t& kt) {

@@ -340,10 +340,6 @@ __device__ __forceinline__ v8i rho1_nibbles_complete(unsigned w0, unsigned w1) {
              0, 0, 0, 0};
 }
 
-__device__ __forceinline__ v8i operand_f4(const unsigned (&x0)[2], const unsigned (&x1)[2]) {
-  return v8i{(int)x0[0], (int)x0[1], (int)x1[0], (int)x1[1], 0, 0, 0, 0};
-}
-
 __device__ __forceinline__ v4f mfma_f4(const v8i& a, const v8i& b, v4f c) {
   // formats 4 = e2m1 for A and B; zero scale operands: the unscaled form
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
