@@ -257,22 +257,18 @@ void timing_end(hipStream_t stream);
 namespace {
 
 // Launch a 3-way kernel over all its tetrahedral units of b x b tiles and
-// `run` middle vectors (256 threads each), in slices of at most 2^30
-// workgroups; `name` (if any) opens a timing mark around the launches.
+// `run` middle vectors (256 threads each), in slices
+// (launch_slices); `name` (if any) opens a timing mark around the launches.
 template <typename Kernel, typename Args>
 hipError_t launch_units(Kernel kernel, const Args& a, int64_t b, const char* name,
                         hipStream_t stream, int64_t run = 1) {
   const UnitGrid g = unit_grid(a.n, b, a.i_begin, a.i_end, run);
   const int64_t total = grid_unit_count(g);
   if (total <= 0) return hipSuccess;
-  hipError_t e = hipSuccess;
-  const int64_t kMaxGrid = 0x40000000;
   if (name) timing_begin(name, stream);
-  for (int64_t base = 0; base < total; base += kMaxGrid) {
-    int64_t cnt = total - base < kMaxGrid ? total - base : kMaxGrid;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(256), 0, stream, a, g, base, cnt);
-    if ((e = hipGetLastError()) != hipSuccess) break;
-  }
+  const hipError_t e = launch_slices(total, 256, [&](int64_t base, dim3 grid) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, a, g, base, (int64_t)grid.x);
+  });
   if (name) timing_end(stream);
   return e;
 }

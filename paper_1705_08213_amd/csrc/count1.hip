@@ -19,9 +19,11 @@ __global__ __launch_bounds__(256) void count1_kernel(const uint8_t* __restrict__
                                                      int accumulate,
                                                      unsigned long long* __restrict__ zero,
                                                      unsigned long long* __restrict__ flag,
-                                                     unsigned long long id, int64_t flag_from) {
-  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0ull;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                     unsigned long long id, int64_t flag_from,
+                                                     int64_t base) {
+  const int64_t b = base + blockIdx.x;
+  if (zero && b == 0 && threadIdx.x == 0) *zero = 0ull;
+  const int64_t row = b * 4 + (threadIdx.x >> 6);
   if (row >= n) return;
   count_row_wave(v + row * ld, n_f, counts + 4 * row, accumulate,
                  row >= flag_from ? flag : nullptr, id);
@@ -32,12 +34,13 @@ hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n
                               hipStream_t stream, unsigned long long* flag,
                               unsigned long long id, int64_t flag_from) {
   if (n <= 0) return hipSuccess;
-  dim3 grid((unsigned)((n + 3) / 4));
   timing_begin("count1", stream);
-  hipLaunchKernelGGL(count1_kernel, grid, dim3(256), 0, stream, v, ld, n, n_f, counts,
-                     accumulate, zero, flag, id, flag_from);
+  const hipError_t e = launch_slices((n + 3) / 4, 256, [&](int64_t base, dim3 grid) {
+    hipLaunchKernelGGL(count1_kernel, grid, dim3(256), 0, stream, v, ld, n, n_f, counts,
+                       accumulate, zero, flag, id, flag_from, base);
+  });
   timing_end(stream);
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_count1(const uint8_t* v, int64_t ld, int64_t n, int64_t n_f, int32_t* counts,

@@ -43,6 +43,7 @@ struct Pair2Args {
   int64_t row_begin, row_end;
   int64_t p_base;
   int64_t sq_offset;          // first square tile of the row range (triangle)
+  int64_t tile_base;          // tile of the launch's first workgroup (launch_slices)
   Select sel;                 // threshold selection (sel.count != null) instead of dense output
   // Device flag that holds `id` when some row of A or B misses an entry (any
   // other value: every row has all n_f fields present); null: no such check
@@ -82,6 +83,22 @@ inline int64_t operand_steps(int64_t n_f) { return (n_f + 255) / 256; }
 inline int64_t operand_blocks(int64_t n) { return (n + 15) / 16; }
 inline int64_t operand_bytes(int64_t n, int64_t n_f) {
   return operand_blocks(n) * operand_steps(n_f) * 1024;
+}
+
+// HIP launches fewer than 2^32 work-items along a dimension, so a kernel with
+// more is launched in slices: launch(first workgroup, workgroups), in order.
+// Slices are whole multiples of 2048 workgroups, which keeps the kernels'
+// mapping of workgroups to XCDs.
+constexpr int64_t slice_workgroups(int threads) { return 0xFFFFFFFFll / threads / 2048 * 2048; }
+template <typename Launch>
+hipError_t launch_slices(int64_t count, int threads, Launch launch) {
+  const int64_t most = slice_workgroups(threads);
+  for (int64_t base = 0; base < count; base += most) {
+    launch(base, dim3((unsigned)(count - base < most ? count - base : most)));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Largest n_f for which the MFMA kernels may take fp4 operands (their fp32

@@ -86,9 +86,11 @@ constexpr int kPopTile = 64;
 
 __global__ __launch_bounds__(256) void count_many_kernel(const ProbDesc* __restrict__ d,
                                                          int n_probs, int64_t total_rows,
-                                                         unsigned* __restrict__ counters) {
-  if (blockIdx.x == 0 && threadIdx.x < kVariants) counters[threadIdx.x] = 0u;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                         unsigned* __restrict__ counters,
+                                                         int64_t base) {
+  const int64_t b = base + blockIdx.x;
+  if (b == 0 && threadIdx.x < kVariants) counters[threadIdx.x] = 0u;
+  const int64_t row = b * 4 + (threadIdx.x >> 6);
   if (row >= total_rows) return;
   int lo = 0, hi = n_probs;  // d[lo].row_begin <= row < d[hi].row_begin
   while (hi - lo > 1) {
@@ -103,8 +105,8 @@ __global__ __launch_bounds__(256) void count_many_kernel(const ProbDesc* __restr
 // The same on operands: one workgroup per 16-row block writes its counts and
 // operands.
 __global__ __launch_bounds__(512) void operands_many_kernel(const ProbDesc* __restrict__ d,
-                                                            int n_probs) {
-  const int64_t block = blockIdx.x;
+                                                            int n_probs, int64_t base) {
+  const int64_t block = base + blockIdx.x;
   int lo = 0, hi = n_probs;  // d[lo].block_begin <= block < d[hi].block_begin
   while (hi - lo > 1) {
     int mid = (lo + hi) >> 1;
@@ -143,6 +145,7 @@ __device__ __forceinline__ Pair2Args pair_args(const ProbDesc& p, double gamma) 
   a.row_end = p.n_v;
   a.p_base = 0;
   a.sq_offset = 0;
+  a.tile_base = 0;
   a.sel = Select{nullptr, 0, 0.0, nullptr, nullptr, nullptr};
   a.flag = nullptr;
   a.id = 0;
@@ -232,11 +235,11 @@ constexpr int kManyStripRows = 4;
 template <int WM, int WN, int MIN_WG>
 __global__ __launch_bounds__(256, MIN_WG) void many_staged_kernel(
     const ProbDesc* __restrict__ d, const WorkItem* __restrict__ items, int n_items,
-    double gamma) {
+    double gamma, int base) {
   constexpr int BM = 32 * WM, BN = 32 * WN, PARTS = BN / BM;
   static_assert(BN == PARTS * BM, "a square is whole workgroup tiles");
   __shared__ u4 stage[3][2 * WM + 2 * WN][64];
-  const WorkItem w = items[item_of(blockIdx.x, n_items)];
+  const WorkItem w = items[item_of(base + blockIdx.x, n_items)];
   const ProbDesc p = d[w.prob];
   int64_t I, J;
   strip_square(w.tile / PARTS, p.tiles_side, 0, p.tiles_side, I, J, kManyStripRows);
@@ -246,10 +249,10 @@ __global__ __launch_bounds__(256, MIN_WG) void many_staged_kernel(
 
 __global__ __launch_bounds__(256, 3) void many_split_kernel(const ProbDesc* __restrict__ d,
                                                             const WorkItem* __restrict__ items,
-                                                            int n_items, double gamma) {
+                                                            int n_items, double gamma, int base) {
   __shared__ v4i red[4][4][64];
   __shared__ tile2::SplitSides sides;
-  const WorkItem w = items[item_of(blockIdx.x, n_items)];
+  const WorkItem w = items[item_of(base + blockIdx.x, n_items)];
   const ProbDesc p = d[w.prob];
   const Pair2Args a = pair_args(p, gamma);
   int64_t I, J;
@@ -365,17 +368,13 @@ hipError_t launch_variant(const Entry& e, int v, hipStream_t stream) {
     return hipGetLastError();
   }
   if (e.operands) {
-    const dim3 grid((unsigned)e.n_items[v]), wg(256);
-    if (v == 0)
-      hipLaunchKernelGGL((many_staged_kernel<2, 4, 2>), grid, wg, 0, stream, e.d, items,
-                         e.n_items[v], e.gamma);
-    else if (v == 1)
-      hipLaunchKernelGGL(many_split_kernel, grid, wg, 0, stream, e.d, items, e.n_items[v],
-                         e.gamma);
-    else
-      hipLaunchKernelGGL((many_staged_kernel<2, 2, 4>), grid, wg, 0, stream, e.d, items,
-                         e.n_items[v], e.gamma);
-    return hipGetLastError();
+    auto* kernel = v == 0   ? many_staged_kernel<2, 4, 2>
+                   : v == 1 ? many_split_kernel
+                            : many_staged_kernel<2, 2, 4>;
+    return launch_slices(e.n_items[v], 256, [&](int64_t base, dim3 grid) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, e.d, items, e.n_items[v], e.gamma,
+                         (int)base);
+    });
   }
   switch (v * 2 + (e.f4 ? 1 : 0)) {
     case 0: launch_mfma<0, false>(e, items, stream); break;
@@ -394,13 +393,16 @@ hipError_t launch_variant(const Entry& e, int v, hipStream_t stream) {
 // the first non-empty one runs on a forked stream joined back before the
 // end, so the variants' kernels can share the GPU.
 hipError_t enqueue(const Entry& e, hipStream_t stream, bool fork) {
-  if (e.operands)
-    hipLaunchKernelGGL(operands_many_kernel, dim3((unsigned)e.total_blocks), dim3(512), 0, stream,
-                       e.d, e.n_probs);
-  else
-    hipLaunchKernelGGL(count_many_kernel, dim3((unsigned)((e.total_rows + 3) / 4)), dim3(256), 0,
-                       stream, e.d, e.n_probs, e.total_rows, e.counters);
-  hipError_t err = hipGetLastError();
+  hipError_t err =
+      e.operands ? launch_slices(e.total_blocks, 512,
+                                 [&](int64_t base, dim3 grid) {
+                                   hipLaunchKernelGGL(operands_many_kernel, grid, dim3(512), 0,
+                                                      stream, e.d, e.n_probs, base);
+                                 })
+                 : launch_slices((e.total_rows + 3) / 4, 256, [&](int64_t base, dim3 grid) {
+                     hipLaunchKernelGGL(count_many_kernel, grid, dim3(256), 0, stream, e.d,
+                                        e.n_probs, e.total_rows, e.counters, base);
+                   });
   if (err != hipSuccess) return err;
   int first = -1, forked = 0;
   for (int v = 0; v < kVariants; ++v) {

@@ -30,6 +30,22 @@ __global__ __launch_bounds__(1024) void complete_flag_kernel(const int32_t* __re
   if (threadIdx.x == 0) *flag = ok ? 0ull : id;
 }
 
+// Tile index of this workgroup (launch_slices): the XCDs take contiguous runs.
+__device__ __forceinline__ int64_t launch_tile(const Pair2Args& a) {
+  return a.tile_base + xcd_unit(blockIdx.x, gridDim.x);
+}
+
+// Launch a kernel over `tiles` workgroups of 256 threads.
+template <typename Kernel, typename... Rest>
+hipError_t launch_tiles(Kernel kernel, int64_t tiles, Pair2Args a, hipStream_t stream,
+                        Rest... rest) {
+  if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+  return launch_slices(tiles, 256, [&](int64_t base, dim3 grid) {
+    a.tile_base = base;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, a, rest...);
+  });
+}
+
 // Workgroup tile (I, J) of `b` in a grid of tiles of BM x BN pairs.  A
 // triangle is cut into squares of the larger side, each a few whole tiles,
 // the squares in strips of H square rows.
@@ -69,8 +85,7 @@ __global__ __launch_bounds__(256, 2) void mfma2_complete_kernel(Pair2Args a,
   constexpr int BM = 32 * WM, BN = 32 * WN, NB = 2 * WM + 2 * WN;
   const int wave = threadIdx.x >> 6;
   int64_t I, J;
-  tile_of<BM, BN, kCompleteStripRows>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I,
-                                      J);
+  tile_of<BM, BN, kCompleteStripRows>(a, launch_tile(a), tiles_side, tiles_n, I, J);
   __shared__ u4 stage[2][NB][64];
   __shared__ u4 outs[4][128];
   tile2::mfma2_complete_wave_tile<WM, WN, F4>(a, I * BM + (wave & 1) * 16 * WM,
@@ -90,7 +105,7 @@ __global__ __launch_bounds__(256, MIN_WG) void mfma2_kernel(Pair2Args a, int64_t
   // XCD-contiguous runs of tiles (triangle: in strip order, so that a run
   // shares row and column blocks in one L2)
   int64_t I, J;
-  tile_of<BM, BN>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I, J);
+  tile_of<BM, BN>(a, launch_tile(a), tiles_side, tiles_n, I, J);
   // the cooperative form's partial tiles (64 KB), or else the workgroup's
   // two stage buffers of NB row blocks
   __shared__ u4 smem[kCoop ? 4 * 16 * 64 : 2 * NB * 64];
@@ -115,8 +130,7 @@ __global__ __launch_bounds__(256, 2) void mfma2_complete_operand_kernel(Pair2Arg
   if (*a.flag == a.id) return;  // uniform: some row is not complete
   constexpr int BM = 32 * WM, BN = 32 * WN;
   int64_t I, J;
-  tile_of<BM, BN, kCompleteStripRows>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I,
-                                      J);
+  tile_of<BM, BN, kCompleteStripRows>(a, launch_tile(a), tiles_side, tiles_n, I, J);
   __shared__ u4 stage[3][2 * WM + 2 * WN][64];
   tile2::complete_tile<OUT, WM, WN>(a, I * BM, J * BN, stage);
 }
@@ -129,7 +143,7 @@ __global__ __launch_bounds__(256, MIN_WG) void mfma2_operand_kernel(Pair2Args a,
   if (a.flag && *a.flag != a.id) return;  // uniform: the complete-data kernel covers the call
   constexpr int BM = 32 * WM, BN = 32 * WN;
   int64_t I, J;
-  tile_of<BM, BN, kOperandStripRows>(a, xcd_unit(blockIdx.x, gridDim.x), tiles_side, tiles_n, I, J);
+  tile_of<BM, BN, kOperandStripRows>(a, launch_tile(a), tiles_side, tiles_n, I, J);
   __shared__ u4 stage[3][2 * WM + 2 * WN][64];
   tile2::staged_tile<OUT, WM, WN>(a, I * BM, J * BN, stage);
 }
@@ -155,7 +169,7 @@ __global__ __launch_bounds__(256, 3) void mfma2_split_kernel(Pair2Args a, int64_
   __shared__ v4i red[4][4][64];
   __shared__ SplitSides sides;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t b = xcd_unit(blockIdx.x, gridDim.x), t = b / splits;
+  const int64_t b = launch_tile(a), t = b / splits;
   const int sp = (int)(b % splits);
   int64_t I0, J0;
   split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
@@ -180,7 +194,7 @@ __global__ __launch_bounds__(256) void mfma2_split_finish_kernel(Pair2Args a, in
                                                                  int64_t tiles_n, int splits) {
   __shared__ SplitSides sides;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t = xcd_unit(blockIdx.x, gridDim.x);
+  const int64_t t = launch_tile(a);
   int64_t I0, J0;
   split_tile_of(a, t, tiles_side, tiles_n, I0, J0);
   const bool whole = tile2::wave_complete<kSplitTile, kSplitTile>(a, I0, J0);
@@ -224,11 +238,7 @@ template <int WM, int WN, bool F4, int MIN_WG>
 hipError_t launch_shape(const Pair2Args& a, hipStream_t stream) {
   int64_t tm, tn;
   const int64_t ntiles = tile_grid<32 * WM, 32 * WN>(a, tm, tn);
-  if (ntiles <= 0) return hipSuccess;
-  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((mfma2_kernel<WM, WN, F4, MIN_WG>), dim3((unsigned)ntiles), dim3(256), 0,
-                     stream, a, tm, tn);
-  return hipGetLastError();
+  return launch_tiles(mfma2_kernel<WM, WN, F4, MIN_WG>, ntiles, a, stream, tm, tn);
 }
 
 // Shapes of the general kernel, picked per call by the kernel-shape table
@@ -256,11 +266,7 @@ template <bool F4>
 hipError_t launch_complete(const Pair2Args& a, hipStream_t stream) {
   int64_t tm, tn;
   const int64_t ntiles = tile_grid<32 * kCWM, 32 * kCWN>(a, tm, tn);
-  if (ntiles <= 0) return hipSuccess;
-  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((mfma2_complete_kernel<kCWM, kCWN, F4>), dim3((unsigned)ntiles), dim3(256),
-                     0, stream, a, tm, tn);
-  return hipGetLastError();
+  return launch_tiles(mfma2_complete_kernel<kCWM, kCWN, F4>, ntiles, a, stream, tm, tn);
 }
 
 template <bool F4>
@@ -313,26 +319,17 @@ template <tile2::Out OUT, int WM, int WN, int MIN_WG>
 hipError_t launch_operand_shape(const Pair2Args& a, hipStream_t stream) {
   int64_t tm, tn;
   const int64_t ntiles = tile_grid<32 * WM, 32 * WN>(a, tm, tn);
-  if (ntiles <= 0) return hipSuccess;
-  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((mfma2_operand_kernel<OUT, WM, WN, MIN_WG>), dim3((unsigned)ntiles),
-                     dim3(256), 0, stream, a, tm, tn);
-  return hipGetLastError();
+  return launch_tiles(mfma2_operand_kernel<OUT, WM, WN, MIN_WG>, ntiles, a, stream, tm, tn);
 }
 
 template <tile2::Out OUT>
 hipError_t launch_split(const Pair2Args& a, int splits, hipStream_t stream) {
   int64_t tm, tn;
   const int64_t ntiles = split_tiles(a, tm, tn);
-  if (ntiles <= 0) return hipSuccess;
-  if (ntiles * splits > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(mfma2_split_kernel<OUT>, dim3((unsigned)(ntiles * splits)), dim3(256), 0,
-                     stream, a, tm, tn, splits);
-  hipError_t e = hipGetLastError();
+  const hipError_t e =
+      launch_tiles(mfma2_split_kernel<OUT>, ntiles * splits, a, stream, tm, tn, splits);
   if (e != hipSuccess || splits == 1) return e;
-  hipLaunchKernelGGL(mfma2_split_finish_kernel<OUT>, dim3((unsigned)ntiles), dim3(256), 0, stream,
-                     a, tm, tn, splits);
-  return hipGetLastError();
+  return launch_tiles(mfma2_split_finish_kernel<OUT>, ntiles, a, stream, tm, tn, splits);
 }
 
 template <tile2::Out OUT>
@@ -343,7 +340,6 @@ hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
   if (s.variant == 1) return launch_split<OUT>(a, s.splits, stream);  // its tiles vote
   if constexpr (OUT != tile2::kAccumulate) {  // (whose counts are running totals)
     const int64_t n = tile_grid<32 * kCOM, 32 * kCON>(a, tm, tn);
-    if (n > 0x7FFFFFFF) return hipErrorInvalidValue;
     // Long fields bind these tiles by their operand reads, which a plain
     // output stream pushes out of L2; short ones by the output, whose lines
     // plain stores let L2 join (16000 x 40000: 3.20 ms plain, 2.87 with the
@@ -352,10 +348,7 @@ hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
     auto* kernel = mfma2_complete_operand_kernel<OUT, kCOM, kCON>;
     if constexpr (OUT == tile2::kDense)
       if (a.n_f >= 12288) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
-    if (n > 0) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(256), 0, stream, a, tm, tn);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
+    if (hipError_t e = launch_tiles(kernel, n, a, stream, tm, tn); e != hipSuccess) return e;
   }
   return s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)
                         : launch_operand_shape<OUT, 2, 4, 2>(a, stream);

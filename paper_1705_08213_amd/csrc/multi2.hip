@@ -215,7 +215,8 @@ struct MultiShape<4, false> {
 };
 
 template <int S, bool F4>
-__global__ __launch_bounds__(256, 2) void multi2_kernel(Multi2Args a, int64_t tiles_side) {
+__global__ __launch_bounds__(256, 2) void multi2_kernel(Multi2Args a, int64_t tiles_side,
+                                                        int64_t tile_base) {
   constexpr int WM = MultiShape<S, F4>::WM, WN = MultiShape<S, F4>::WN;
   constexpr int BM = 32 * WM, BN = 32 * WN, PARTS = BM / BN;
   static_assert(BM % BN == 0, "square tiles split into whole column parts");
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void multi2_kernel(Multi2Args a, int64_t ti
   const int g = lane >> 4, rl = lane & 15;
   // XCD-contiguous runs of squares in strip order: a run shares row and
   // column blocks in one L2
-  const int64_t b = xcd_unit(blockIdx.x, gridDim.x);
+  const int64_t b = tile_base + xcd_unit(blockIdx.x, gridDim.x);
   int64_t sq_i, sq_j;
   strip_square(b / PARTS, tiles_side, 0, tiles_side, sq_i, sq_j);
   const int64_t row0 = sq_i * BM + (wave & 1) * 16 * WM;
@@ -584,7 +585,8 @@ constexpr int kMultiPieces = S > 2 ? 2 : 1;
 template <int S>
 __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, const void* z,
                                                                 int64_t steps,
-                                                                int64_t tiles_side) {
+                                                                int64_t tiles_side,
+                                                                int64_t tile_base) {
   constexpr int WM = MultiShape<S, true>::WM, WN = MultiShape<S, true>::WN;
   constexpr int BM = 32 * WM, BN = 32 * WN, PARTS = BM / BN, P = kMultiPieces<S>;
   constexpr int ND = (2 * WM + 2 * WN) * P, DPW = ND / 4;
@@ -592,7 +594,7 @@ __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, co
   __shared__ u4 stage[3][ND][64];
   const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform
-  const int64_t b = xcd_unit(blockIdx.x, gridDim.x);
+  const int64_t b = tile_base + xcd_unit(blockIdx.x, gridDim.x);
   int64_t sq_i, sq_j;
   strip_square(b / PARTS, tiles_side, 0, tiles_side, sq_i, sq_j);
   const int64_t I0 = sq_i * BM, J0 = (sq_j * PARTS + b % PARTS) * BN;
@@ -702,10 +704,12 @@ hipError_t launch_multi2_operands(const Multi2Args& a, const void* z, hipStream_
   if (ntiles <= 0) return hipSuccess;
   if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   timing_begin("multi2", stream);
-  hipLaunchKernelGGL(multi2_operand_kernel<S>, dim3((unsigned)ntiles), dim3(256), 0, stream, a, z,
-                     (a.n_f + 127) / 128, T);
+  const hipError_t e = launch_slices(ntiles, 256, [&](int64_t base, dim3 grid) {
+    hipLaunchKernelGGL(multi2_operand_kernel<S>, grid, dim3(256), 0, stream, a, z,
+                       (a.n_f + 127) / 128, T, base);
+  });
   timing_end(stream);
-  return hipGetLastError();
+  return e;
 }
 
 template <int S, bool F4>
@@ -716,9 +720,11 @@ hipError_t launch_multi2_shape(const Multi2Args& a, hipStream_t stream) {
   if (ntiles <= 0) return hipSuccess;
   if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   timing_begin("multi2", stream);
-  hipLaunchKernelGGL((multi2_kernel<S, F4>), dim3((unsigned)ntiles), dim3(256), 0, stream, a, T);
+  const hipError_t e = launch_slices(ntiles, 256, [&](int64_t base, dim3 grid) {
+    hipLaunchKernelGGL((multi2_kernel<S, F4>), grid, dim3(256), 0, stream, a, T, base);
+  });
   timing_end(stream);
-  return hipGetLastError();
+  return e;
 }
 
 template <int S>

@@ -7,11 +7,11 @@ namespace ccc {
 namespace {
 
 // One workgroup per block of 16 rows and share of the fields.
-__global__ __launch_bounds__(1024) void operands_kernel(OperandJob job) {
-  if (job.zero && blockIdx.x == 0 && threadIdx.x == 0) *job.zero = 0ull;
-  const bool second = blockIdx.x >= job.set[0].blocks;
-  operand_block(job, job.set[second ? 1 : 0],
-                (int64_t)blockIdx.x - (second ? job.set[0].blocks : 0), blockIdx.y);
+__global__ __launch_bounds__(1024) void operands_kernel(OperandJob job, int64_t base) {
+  const int64_t b = base + blockIdx.x;
+  if (job.zero && b == 0 && threadIdx.x == 0) *job.zero = 0ull;
+  const bool second = b >= job.set[0].blocks;
+  operand_block(job, job.set[second ? 1 : 0], b - (second ? job.set[0].blocks : 0), blockIdx.y);
 }
 
 // The counts of a pass in several shares.
@@ -33,13 +33,13 @@ hipError_t launch_operands(OperandJob job, hipStream_t stream) {
   if (job.shares < 1 || !job.part || job.set[1].blocks) job.shares = 1;
   const int64_t blocks = (int64_t)job.set[0].blocks + job.set[1].blocks;
   if (blocks <= 0) return hipSuccess;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   // a wave per super-step up to sixteen: few blocks leave the chip idle
   const int waves = job.steps > 8 ? 16 : 4;
   timing_begin("count1", stream);
-  hipLaunchKernelGGL(operands_kernel, dim3((unsigned)blocks, (unsigned)job.shares),
-                     dim3(64 * waves), 0, stream, job);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_slices(blocks, 64 * waves, [&](int64_t base, dim3 grid) {
+    grid.y = (unsigned)job.shares;
+    hipLaunchKernelGGL(operands_kernel, grid, dim3(64 * waves), 0, stream, job, base);
+  });
   if (e == hipSuccess && job.shares > 1) {
     hipLaunchKernelGGL(share_counts_kernel, dim3((unsigned)((job.set[0].n + 63) / 64)), dim3(64), 0,
                        stream, job);

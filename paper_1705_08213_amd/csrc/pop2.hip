@@ -10,12 +10,13 @@ namespace {
 __global__ __launch_bounds__(256) void pop2_kernel(Pair2Args a, int64_t tiles_side,
                                                    int64_t tiles_n) {
   __shared__ tile2::Pop2Smem sm;
+  const int64_t b = a.tile_base + blockIdx.x;
   int64_t I, J;
   if (a.tri) {
-    tri_tile(blockIdx.x + a.sq_offset, tiles_side, I, J);
+    tri_tile(b + a.sq_offset, tiles_side, I, J);
   } else {
-    I = blockIdx.x / tiles_n;
-    J = blockIdx.x % tiles_n;
+    I = b / tiles_n;
+    J = b % tiles_n;
   }
   tile2::pop2_block_tile(a, I, J, sm);
 }
@@ -34,9 +35,12 @@ hipError_t launch_pop2(const Pair2Args& a, hipStream_t stream) {
   if (ntiles <= 0) return hipSuccess;
   if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   timing_begin("pop2", stream);
-  hipLaunchKernelGGL(pop2_kernel, dim3((unsigned)ntiles), dim3(256), 0, stream, b, tm, tn);
+  const hipError_t e = launch_slices(ntiles, 256, [&](int64_t base, dim3 grid) {
+    b.tile_base = base;
+    hipLaunchKernelGGL(pop2_kernel, grid, dim3(256), 0, stream, b, tm, tn);
+  });
   timing_end(stream);
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace ccc

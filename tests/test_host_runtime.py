@@ -1,0 +1,54 @@
+"""The library's host code (dispatch, launch sizes, workspaces) over a HIP
+runtime of the host alone: the sources are compiled for the host only and
+linked with tests/native/fake_hip.h, which counts allocations, frees and
+waits and keeps a list of the launches.  No GPU, and no device code."""
+import concurrent.futures as cf
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_1705_08213_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def host_check(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    from paper_1705_08213_amd.build import SOURCES
+    tmp = tmp_path_factory.mktemp("host")
+    srcs = [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(HERE, "native", "host_check.cpp")]
+
+    def compile_one(src):
+        obj = str(tmp / (os.path.basename(src) + ".o"))
+        r = subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-x", "hip",
+                            "-I", os.path.join(ROOT, "include"), "-c", src, "-o", obj],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return obj
+
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(compile_one, srcs))
+    exe = str(tmp / "host_check")
+    # the device code of the sources, which is not there, is never looked at
+    r = subprocess.run(["g++", "-no-pie", *objs, "-o", exe, "-lpthread", "-ldl",
+                        "-Wl,--unresolved-symbols=ignore-in-object-files"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def run(scenario, **env):
+        out = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=120,
+                             env=dict(os.environ, **env))
+        assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
+    return run
+
+
+def test_launches_stay_within_the_runtime_limits(host_check):
+    """No launch of 2^32 or more work-items along a dimension, whatever the
+    sizes: a call of 200,000 rows and 1000 fields is 19.5 million 32 x 32
+    tiles of 256 threads."""
+    host_check("launch_limits")
