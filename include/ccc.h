@@ -51,15 +51,21 @@
  *  - The library keeps one workspace per device and stream (allocated on
  *    first need, grown on demand, at most 16 per device besides those that a
  *    captured graph holds, released by ccc_release_workspace), so that calls
- *    on different streams never share scratch.  A call holds a lock while it
+ *    on different streams never share scratch.  Calls under stream capture get
+ *    a workspace of that capture alone, so that its graph may be replayed on
+ *    any stream beside other graphs and calls; it stays at its address while
+ *    the graph or an executable of it exists (ccc_release_workspace frees it
+ *    regardless).
+ *    (Replays of one graph on several streams write the same outputs and are
+ *    ordered by the caller, as are ccc_3way_noalloc calls, whose scratch is
+ *    shared.)  A call holds a lock while it
  *    enqueues its kernels.  Besides what the calls below state, a workspace
  *    holds the fp4 calls' operands: ceil(n/16) 16-row blocks of ceil(n_f/256)
  *    KB (2-way), of ceil(n_f/128) KB (multi-allelic, twice that for three and
  *    four states), and the partial sums of split tiles (16 KB a workgroup, at
  *    most 32 MB).  Where the operands would pass 16 GiB ($CCC_OPERAND_LIMIT,
  *    bytes) or find no memory, the call reads the packed rows instead, with
- *    the same results.  A workspace used while its stream is captured stays
- *    at its address until ccc_release_workspace.
+ *    the same results.
  */
 #ifndef CCC_H
 #define CCC_H

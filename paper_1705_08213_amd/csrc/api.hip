@@ -9,9 +9,12 @@
 
 #include <stdlib.h>
 
+#include <algorithm>
 #include <atomic>
 #include <functional>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -35,25 +38,33 @@ constexpr int64_t kGramMaxRows = 32768;
 // overrides it.
 constexpr int64_t kOperandLimit = int64_t(16) << 30;
 
-// Workspaces: one buffer per (device, stream), so that calls on different
-// streams never share scratch.  A call holds g_mu while it enqueues its
+// Workspaces: one buffer per (device, stream) for eager calls, so that calls
+// on different streams never share scratch, and one per (device, stream,
+// capture) for captured calls: a graph may be replayed on any stream, beside
+// other graphs captured on the same one and beside eager calls there, so it
+// shares its scratch with neither.  A call holds g_mu while it enqueues its
 // kernels, so that calls of several threads on one stream do not interleave.
-// Buffers used under stream capture are pinned: a graph holds their address,
-// so they are given back by ccc_release_workspace alone.
+// A graph holds the address of its buffers: they stay until the graph and its
+// executables are destroyed, which a user object of the graph tells (`gone`).
+// What such an executable last launched may still run, so the buffers are
+// freed behind a wait, by a later eager call that finds more than kMaxGone of
+// them or runs out of memory.
 struct Workspace {
   int dev = 0;
   hipStream_t stream = nullptr;
   size_t thread = 0;  // of hipStreamPerThread, which names a stream per thread
+  unsigned long long capture = 0;  // id of the capture it belongs to, 0: eager calls
+  std::shared_ptr<std::atomic<bool>> gone;  // of a capture: its graph is no more
   void* ptr = nullptr;
   size_t bytes = 0;
-  bool pinned = false;
   uint64_t last_use = 0;
 };
-constexpr size_t kMaxWorkspaces = 16;  // per device, pinned ones aside
+constexpr int kMaxGone = 8;
+constexpr size_t kMaxWorkspaces = 16;  // per device, those of captures aside
 
 std::mutex g_mu;
 std::vector<Workspace> g_ws;
-std::vector<Workspace> g_retired;  // outgrown while pinned or under capture
+std::vector<Workspace> g_retired;  // outgrown by a capture that may hold their address
 uint64_t g_clock = 0;
 
 // Identity of a call in the complete-data flag (Pair2Args::flag).
@@ -111,13 +122,59 @@ namespace ccc {
 
 namespace {
 
-bool capturing(hipStream_t stream) {
+// Id of the capture that `stream` is part of (its forks have the same one), or 0.
+unsigned long long capture_id(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(stream, &st, &id) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    return 0;
   }
-  return st == hipStreamCaptureStatusActive;
+  return st == hipStreamCaptureStatusActive ? id : 0;
+}
+
+// Note when the graph that `stream` is being captured into is no more (the
+// callback may come on any thread and calls no HIP function).
+std::shared_ptr<std::atomic<bool>> watch_graph(hipStream_t stream) {
+  using Mark = std::shared_ptr<std::atomic<bool>>;
+  Mark mark = std::make_shared<std::atomic<bool>>(false);
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  hipGraph_t graph = nullptr;
+  const hipGraphNode_t* deps = nullptr;
+  size_t n_deps = 0;
+  hipUserObject_t object = nullptr;
+  Mark* held = new Mark(mark);
+  auto tell = [](void* p) {
+    Mark* m = static_cast<Mark*>(p);
+    (*m)->store(true);
+    delete m;
+  };
+  if (hipStreamGetCaptureInfo_v2(stream, &st, &id, &graph, &deps, &n_deps) != hipSuccess ||
+      !graph ||
+      hipUserObjectCreate(&object, held, tell, 1, hipUserObjectNoDestructorSync) != hipSuccess) {
+    (void)hipGetLastError();
+    delete held;
+    return mark;  // never told: the buffer stays until ccc_release_workspace
+  }
+  if (hipGraphRetainUserObject(graph, object, 1, hipGraphUserObjectMove) != hipSuccess) {
+    (void)hipGetLastError();
+    mark = std::make_shared<std::atomic<bool>>(false);  // likewise; the object has the old one
+    (void)hipUserObjectRelease(object, 1);
+  }
+  return mark;
+}
+
+bool is_gone(const Workspace& w) { return w.gone && w.gone->load(); }
+
+// Free the workspaces on `dev` whose graph is no more; it has been waited for.
+void free_gone(int dev) {
+  for (auto* list : {&g_ws, &g_retired})
+    for (size_t i = list->size(); i-- > 0;) {
+      if ((*list)[i].dev != dev || !is_gone((*list)[i])) continue;
+      if ((*list)[i].ptr) (void)hipFree((*list)[i].ptr);
+      list->erase(list->begin() + i);
+    }
 }
 
 // hipMalloc that is also allowed while a stream of this thread is captured.
@@ -136,18 +193,21 @@ void* allocate(size_t bytes, bool capture) {
   return p;
 }
 
-// Free every unpinned buffer of `dev` except index `keep` (waits for the
-// device); all: also those that only the bound on their number would evict.
+// Free every buffer on `dev` that no graph holds, except index `keep` (waits for
+// the device).
 void free_idle(int dev, size_t keep) {
   if (hipDeviceSynchronize() != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
-  for (size_t i = 0; i < g_ws.size(); ++i)
-    if (i != keep && g_ws[i].dev == dev && !g_ws[i].pinned && g_ws[i].ptr) {
-      (void)hipFree(g_ws[i].ptr);
-      g_ws[i].ptr = nullptr;
-      g_ws[i].bytes = 0;
+  for (auto* list : {&g_ws, &g_retired})
+    for (size_t i = 0; i < list->size(); ++i) {
+      Workspace& w = (*list)[i];
+      if ((list == &g_ws && i == keep) || w.dev != dev || !w.ptr) continue;
+      if (w.capture && !is_gone(w)) continue;
+      (void)hipFree(w.ptr);
+      w.ptr = nullptr;
+      w.bytes = 0;
     }
 }
 
@@ -155,24 +215,30 @@ void free_idle(int dev, size_t keep) {
 
 // A workspace of at least `bytes` for `stream` on the current device (grown
 // on demand); `lock` is held until the caller has enqueued its work.
-int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lock, void** out) {
+int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lock,
+              void** out) try {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return CCC_ERR_HIP;
   const size_t thread =
       stream == hipStreamPerThread ? std::hash<std::thread::id>()(std::this_thread::get_id()) : 0;
+  const unsigned long long capture = capture_id(stream);
   if (!lock.owns_lock()) lock = std::unique_lock<std::mutex>(g_mu);
+  if (!capture && std::count_if(g_ws.begin(), g_ws.end(), is_gone) > kMaxGone) {
+    if (hipDeviceSynchronize() == hipSuccess)
+      free_gone(dev);
+    else
+      (void)hipGetLastError();
+  }
   size_t at = g_ws.size(), mine = 0, oldest = g_ws.size();
   for (size_t i = 0; i < g_ws.size(); ++i) {
     const Workspace& w = g_ws[i];
     if (w.dev != dev) continue;
-    if (w.stream == stream && w.thread == thread) at = i;
-    else if (!w.pinned) {
+    if (w.stream == stream && w.thread == thread && w.capture == capture) at = i;
+    else if (!w.capture) {
       ++mine;
       if (oldest == g_ws.size() || w.last_use < g_ws[oldest].last_use) oldest = i;
     }
   }
-  const bool fits = at < g_ws.size() && g_ws[at].bytes >= bytes;
-  const bool capture = (!fits || !g_ws[at].pinned) && capturing(stream);
   if (at == g_ws.size()) {
     if (mine >= kMaxWorkspaces && !capture && hipDeviceSynchronize() == hipSuccess) {
       if (g_ws[oldest].ptr) (void)hipFree(g_ws[oldest].ptr);
@@ -184,10 +250,12 @@ int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lo
     g_ws[at].dev = dev;
     g_ws[at].stream = stream;
     g_ws[at].thread = thread;
+    g_ws[at].capture = capture;
+    if (capture) g_ws[at].gone = watch_graph(stream);
   }
   Workspace& w = g_ws[at];
-  if (!fits) {
-    if (w.ptr && (w.pinned || capture)) {
+  if (w.bytes < bytes) {
+    if (w.ptr && capture) {
       g_retired.push_back(w);
       w.ptr = nullptr;
     } else if (w.ptr) {
@@ -197,7 +265,6 @@ int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lo
       w.ptr = nullptr;
     }
     w.bytes = 0;
-    w.pinned = false;
     const size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
     w.ptr = allocate(want, capture);
     if (!w.ptr && !capture) {
@@ -207,10 +274,11 @@ int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lo
     if (!w.ptr) return CCC_ERR_NOMEM;
     w.bytes = want;
   }
-  w.pinned = w.pinned || capture;
   w.last_use = ++g_clock;
   *out = w.ptr;
   return CCC_OK;
+} catch (const std::bad_alloc&) {  // of the host's own lists
+  return CCC_ERR_NOMEM;
 }
 
 static int run_pair2(const Pair2Args& a, int path, hipStream_t stream) {

@@ -35,6 +35,18 @@ inline std::map<const void*, std::string>& names() {
 inline std::vector<Launch> launches;
 inline std::map<uintptr_t, size_t> allocated;
 inline std::map<hipStream_t, unsigned long long> capture;  // capture id of a stream
+struct Object {
+  void* p;
+  hipHostFn_t fn;
+};
+inline std::map<unsigned long long, std::vector<Object*>> graphs;  // user objects by capture id
+inline void destroy_graph(unsigned long long id) {
+  for (Object* o : graphs[id]) {
+    o->fn(o->p);
+    delete o;
+  }
+  graphs.erase(id);
+}
 inline size_t card = size_t(288) << 30, used = 0;
 inline uintptr_t next = uintptr_t(1) << 40;
 inline long mallocs = 0, failed = 0, frees = 0, syncs = 0;
@@ -160,6 +172,24 @@ hipError_t hipStreamGetCaptureInfo(hipStream_t s, hipStreamCaptureStatus* st,
   *id = fake::capture.count(s) ? fake::capture[s] : 0;
   return hipSuccess;
 }
+hipError_t hipStreamGetCaptureInfo_v2(hipStream_t s, hipStreamCaptureStatus* st,
+                                      unsigned long long* id, hipGraph_t* g,
+                                      const hipGraphNode_t** deps, size_t* n) {
+  hipStreamGetCaptureInfo(s, st, id);
+  *g = reinterpret_cast<hipGraph_t>(uintptr_t(*id));
+  *deps = nullptr;
+  *n = 0;
+  return hipSuccess;
+}
+hipError_t hipUserObjectCreate(hipUserObject_t* o, void* p, hipHostFn_t fn, unsigned, unsigned) {
+  *o = reinterpret_cast<hipUserObject_t>(new fake::Object{p, fn});
+  return hipSuccess;
+}
+hipError_t hipGraphRetainUserObject(hipGraph_t g, hipUserObject_t o, unsigned, unsigned) {
+  fake::graphs[reinterpret_cast<uintptr_t>(g)].push_back(reinterpret_cast<fake::Object*>(o));
+  return hipSuccess;
+}
+hipError_t hipUserObjectRelease(hipUserObject_t, unsigned) { return hipSuccess; }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   static int k = 1000;

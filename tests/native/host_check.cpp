@@ -91,10 +91,73 @@ int launch_limits() {
   return 0;
 }
 
+// The workspace of the last 2-way call: its flag and its operands.
+const Launch* last_tiles() {
+  for (size_t k = launches.size(); k-- > 0;)
+    if (is(launches[k], "mfma2_")) return &launches[k];
+  return nullptr;
+}
+
+// A capture shares its workspace with no other capture, no other stream and no
+// eager call, and what it was given stays where it is.
+int captures() {
+  std::vector<const void*> flags, ops;
+  auto call = [&](int s, unsigned long long id, int64_t n_v) {
+    if (id) capture[stream(s)] = id;
+    const int st = two_way(n_v, 2000, stream(s));
+    capture.clear();
+    if (st != CCC_OK) return false;
+    for (const void* f : flags)
+      if (f == last_tiles()->pair.flag) return false;
+    for (const void* z : ops)
+      if (z == last_tiles()->pair.za) return false;
+    flags.push_back(last_tiles()->pair.flag);
+    ops.push_back(last_tiles()->pair.za);
+    return true;
+  };
+  CHECK(call(1, 0, 300));
+  CHECK(call(1, 7, 300));   // beside the stream's eager calls
+  CHECK(call(1, 8, 300));   // another capture on the stream
+  CHECK(call(1, 9, 300));
+  CHECK(call(2, 9, 300));   // a fork of that capture
+  CHECK(call(2, 0, 300));
+  const long f0 = frees;
+  CHECK(call(1, 9, 3000));  // outgrown within the capture: nodes hold the old one
+  CHECK(frees == f0);
+  const size_t held = flags.size() - 1;
+  CHECK(call(1, 0, 6000));  // the eager call's own buffer alone goes
+  for (size_t k = 1; k < held; ++k) {
+    bool found = false;
+    for (auto& a : allocated)
+      if (a.first <= (uintptr_t)flags[k] && (uintptr_t)flags[k] < a.first + a.second) found = true;
+    CHECK(found);
+  }
+  // graphs that are no more give their buffers back, behind a wait; others stay
+  for (unsigned long long id = 100; id < 140; ++id) {
+    CHECK(call(1, id, 300));
+    if (id != 120) destroy_graph(id);
+    CHECK(call(3, 0, 200 + (int)id));  // eager
+    flags.pop_back();  // (its buffer is the same every time)
+    ops.pop_back();
+    CHECK(allocated.size() < 24);
+  }
+  const void* live = flags[flags.size() - 20];
+  CHECK(graphs.count(120) == 1);
+  bool found = false;
+  for (auto& a : allocated) found |= a.first <= (uintptr_t)live && (uintptr_t)live < a.first + a.second;
+  CHECK(found);
+  ccc_release_workspace();
+  CHECK(allocated.empty() && used == 0);
+  destroy_graph(120);  // later than its buffer
+  CHECK(call(1, 0, 300));
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   int r = 2;
   if (what == "launch_limits") r = launch_limits();
+  if (what == "captures") r = captures();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

@@ -52,3 +52,9 @@ def test_launches_stay_within_the_runtime_limits(host_check):
     sizes: a call of 200,000 rows and 1000 fields is 19.5 million 32 x 32
     tiles of 256 threads."""
     host_check("launch_limits")
+
+
+def test_captured_calls_have_workspaces_of_their_own(host_check):
+    """Two captures on one stream, the forks of a capture and the stream's eager
+    calls all have their own workspaces, and a capture's stay allocated."""
+    host_check("captures")
