@@ -63,9 +63,10 @@
  *    holds the fp4 calls' operands: ceil(n/16) 16-row blocks of ceil(n_f/256)
  *    KB (2-way), of ceil(n_f/128) KB (multi-allelic, twice that for three and
  *    four states), and the partial sums of split tiles (16 KB a workgroup, at
- *    most 32 MB).  Where the operands would pass 16 GiB ($CCC_OPERAND_LIMIT,
- *    bytes) or find no memory, the call reads the packed rows instead, with
- *    the same results.
+ *    most 8 MB).  Over all workspaces and batches of a device these take at
+ *    most 16 GiB ($CCC_OPERAND_LIMIT, bytes), and a buffer for them grows to at
+ *    most half of the memory that is free then; a call without them reads the
+ *    packed rows instead, with the same results and without waiting.
  */
 #ifndef CCC_H
 #define CCC_H

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <atomic>
 #include <functional>
+#include <map>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -33,9 +34,14 @@ constexpr int64_t kMaxLd = int64_t(1) << 28;
 // the general path.
 constexpr int64_t kGramMaxRows = 32768;
 
-// Largest operand layout (operands.hip) a call keeps in the workspace; beyond
-// it the fp4 kernels read the packed rows.  $CCC_OPERAND_LIMIT (bytes)
-// overrides it.
+// Most operands (operands.hip) that the library holds on a device, over all
+// its workspaces and batches; $CCC_OPERAND_LIMIT (bytes) overrides it.  They
+// also never take more than half of the memory that is free.  Where they find
+// no room the fp4 kernels read the packed rows, which is slower by a third at
+// most, while a wait for the device or another stream's buffers given back
+// and allocated again would cost milliseconds on every call of a card that is
+// nearly full.  The check is one query of the free memory (5 us), made only
+// when a buffer has to grow.
 constexpr int64_t kOperandLimit = int64_t(16) << 30;
 
 // Workspaces: one buffer per (device, stream) for eager calls, so that calls
@@ -55,8 +61,10 @@ struct Workspace {
   size_t thread = 0;  // of hipStreamPerThread, which names a stream per thread
   unsigned long long capture = 0;  // id of the capture it belongs to, 0: eager calls
   std::shared_ptr<std::atomic<bool>> gone;  // of a capture: its graph is no more
-  void* ptr = nullptr;
+  void* ptr = nullptr;  // what every call needs: flag, counts, Gram matrix
   size_t bytes = 0;
+  void* ops = nullptr;  // operands and split tiles' sums, if they have room
+  size_t ops_bytes = 0;
   uint64_t last_use = 0;
 };
 constexpr int kMaxGone = 8;
@@ -65,6 +73,7 @@ constexpr size_t kMaxWorkspaces = 16;  // per device, those of captures aside
 std::mutex g_mu;
 std::vector<Workspace> g_ws;
 std::vector<Workspace> g_retired;  // outgrown by a capture that may hold their address
+std::map<int, int64_t> g_batch_operands;  // held by ccc_2way_many's batches, by device
 uint64_t g_clock = 0;
 
 // Identity of a call in the complete-data flag (Pair2Args::flag).
@@ -165,18 +174,6 @@ std::shared_ptr<std::atomic<bool>> watch_graph(hipStream_t stream) {
   return mark;
 }
 
-bool is_gone(const Workspace& w) { return w.gone && w.gone->load(); }
-
-// Free the workspaces on `dev` whose graph is no more; it has been waited for.
-void free_gone(int dev) {
-  for (auto* list : {&g_ws, &g_retired})
-    for (size_t i = list->size(); i-- > 0;) {
-      if ((*list)[i].dev != dev || !is_gone((*list)[i])) continue;
-      if ((*list)[i].ptr) (void)hipFree((*list)[i].ptr);
-      list->erase(list->begin() + i);
-    }
-}
-
 // hipMalloc that is also allowed while a stream of this thread is captured.
 void* allocate(size_t bytes, bool capture) {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -193,41 +190,95 @@ void* allocate(size_t bytes, bool capture) {
   return p;
 }
 
-// Free every buffer on `dev` that no graph holds, except index `keep` (waits for
-// the device).
-void free_idle(int dev, size_t keep) {
-  if (hipDeviceSynchronize() != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
+bool is_gone(const Workspace& w) { return w.gone && w.gone->load(); }
+
+// Free the buffers of the workspaces on `dev` that `which` picks; the device has
+// been waited for.
+template <typename Which>
+void free_buffers(int dev, Which which) {
   for (auto* list : {&g_ws, &g_retired})
-    for (size_t i = 0; i < list->size(); ++i) {
-      Workspace& w = (*list)[i];
-      if ((list == &g_ws && i == keep) || w.dev != dev || !w.ptr) continue;
-      if (w.capture && !is_gone(w)) continue;
-      (void)hipFree(w.ptr);
-      w.ptr = nullptr;
-      w.bytes = 0;
+    for (Workspace& w : *list) {
+      if (w.dev != dev || !which(w)) continue;
+      if (w.ptr) (void)hipFree(w.ptr);
+      if (w.ops) (void)hipFree(w.ops);
+      w.ptr = w.ops = nullptr;
+      w.bytes = w.ops_bytes = 0;
     }
+}
+
+bool wait_for_device() {
+  if (hipDeviceSynchronize() == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Room for `bytes` of operands besides those held on the device, `own` of which
+// the caller would give back.
+bool room_for_operands(int dev, size_t bytes, size_t own, bool capture) {
+  int64_t held = (int64_t)bytes - (int64_t)own;
+  for (auto* list : {&g_ws, &g_retired})
+    for (const Workspace& w : *list)
+      if (w.dev == dev) held += (int64_t)w.ops_bytes;
+  if (auto it = g_batch_operands.find(dev); it != g_batch_operands.end()) held += it->second;
+  if (held > operand_limit()) return false;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (capture && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  size_t avail = 0, total = 0;
+  const bool known = hipMemGetInfo(&avail, &total) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  if (capture) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return known && bytes <= avail && bytes <= (avail + own) / 2;
+}
+
+// At least `bytes` of operand space in w, or not: never at another workspace's
+// cost, and where there is no room without waiting for anything.
+bool operand_space(Workspace& w, size_t bytes) {
+  if ((int64_t)bytes > operand_limit()) return false;
+  if (w.ops_bytes >= bytes) return true;
+  const bool capture = w.capture != 0;
+  const size_t own = capture ? 0 : w.ops_bytes;  // a graph keeps what it outgrew
+  if (!room_for_operands(w.dev, bytes, own, capture)) return false;
+  if (w.ops && !capture && !wait_for_device()) return false;  // its work may still be going on
+  void* p = allocate(bytes, capture);
+  if (!p) return false;
+  if (w.ops && capture) {
+    Workspace old = w;
+    old.ptr = nullptr;
+    old.bytes = 0;
+    g_retired.push_back(old);
+  } else if (w.ops) {
+    (void)hipFree(w.ops);
+  }
+  w.ops = p;
+  w.ops_bytes = bytes;
+  return true;
 }
 
 }  // namespace
 
-// A workspace of at least `bytes` for `stream` on the current device (grown
-// on demand); `lock` is held until the caller has enqueued its work.
-int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lock,
-              void** out) try {
+// The workspace of `stream` on the current device, grown on demand: at least
+// `bytes` at *out, and with op_bytes > 0 as many at *ops, or null there when
+// the operands have no room.  `lock` is held until the caller has enqueued its
+// work.
+int workspace(size_t bytes, size_t op_bytes, hipStream_t stream,
+              std::unique_lock<std::mutex>& lock, char** out, char** ops) try {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return CCC_ERR_HIP;
   const size_t thread =
       stream == hipStreamPerThread ? std::hash<std::thread::id>()(std::this_thread::get_id()) : 0;
   const unsigned long long capture = capture_id(stream);
-  if (!lock.owns_lock()) lock = std::unique_lock<std::mutex>(g_mu);
-  if (!capture && std::count_if(g_ws.begin(), g_ws.end(), is_gone) > kMaxGone) {
-    if (hipDeviceSynchronize() == hipSuccess)
-      free_gone(dev);
-    else
-      (void)hipGetLastError();
+  lock = std::unique_lock<std::mutex>(g_mu);
+  auto gone_here = [&](const Workspace& w) { return w.dev == dev && is_gone(w); };
+  if (!capture && std::count_if(g_ws.begin(), g_ws.end(), gone_here) > kMaxGone &&
+      wait_for_device()) {
+    free_buffers(dev, is_gone);
+    for (auto* list : {&g_ws, &g_retired})
+      list->erase(std::remove_if(list->begin(), list->end(),
+                                 [&](const Workspace& w) { return gone_here(w) && !w.ptr && !w.ops; }),
+                  list->end());
   }
   size_t at = g_ws.size(), mine = 0, oldest = g_ws.size();
   for (size_t i = 0; i < g_ws.size(); ++i) {
@@ -240,8 +291,9 @@ int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lo
     }
   }
   if (at == g_ws.size()) {
-    if (mine >= kMaxWorkspaces && !capture && hipDeviceSynchronize() == hipSuccess) {
-      if (g_ws[oldest].ptr) (void)hipFree(g_ws[oldest].ptr);
+    if (mine >= kMaxWorkspaces && !capture && wait_for_device()) {
+      const Workspace* evict = &g_ws[oldest];
+      free_buffers(dev, [&](const Workspace& w) { return &w == evict; });
       g_ws[oldest] = Workspace{};
       at = oldest;
     } else {
@@ -256,29 +308,41 @@ int workspace(size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lo
   Workspace& w = g_ws[at];
   if (w.bytes < bytes) {
     if (w.ptr && capture) {
-      g_retired.push_back(w);
-      w.ptr = nullptr;
+      Workspace old = w;
+      old.ops = nullptr;
+      old.ops_bytes = 0;
+      g_retired.push_back(old);
     } else if (w.ptr) {
       // the old buffer may still be in use by enqueued work
       if (hipDeviceSynchronize() != hipSuccess) return CCC_ERR_HIP;
       (void)hipFree(w.ptr);
-      w.ptr = nullptr;
     }
+    w.ptr = nullptr;
     w.bytes = 0;
     const size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
     w.ptr = allocate(want, capture);
-    if (!w.ptr && !capture) {
-      free_idle(dev, at);
+    if (!w.ptr && !capture && wait_for_device()) {  // whatever no graph holds makes room
+      free_buffers(dev, [](const Workspace& x) { return !x.capture || is_gone(x); });
       w.ptr = allocate(want, false);
     }
     if (!w.ptr) return CCC_ERR_NOMEM;
     w.bytes = want;
   }
   w.last_use = ++g_clock;
-  *out = w.ptr;
+  *out = static_cast<char*>(w.ptr);
+  if (ops) *ops = op_bytes > 0 && operand_space(w, op_bytes) ? static_cast<char*>(w.ops) : nullptr;
   return CCC_OK;
 } catch (const std::bad_alloc&) {  // of the host's own lists
   return CCC_ERR_NOMEM;
+}
+
+bool batch_operands_fit(int dev, size_t bytes) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  return room_for_operands(dev, bytes, 0, false);
+}
+void hold_batch_operands(int dev, int64_t bytes) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_batch_operands[dev] += bytes;
 }
 
 static int run_pair2(const Pair2Args& a, int path, hipStream_t stream) {
@@ -354,9 +418,9 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   if (n_v == 1) {
     if (!counts && !zero) return CCC_OK;
     if (!counts) {  // only the selection counter to clear
-      void* ws = nullptr;
-      if ((st = ccc::workspace(16, stream, lock, &ws))) return st;
-      counts = static_cast<int32_t*>(ws);
+      char* ws = nullptr;
+      if ((st = ccc::workspace(16, 0, stream, lock, &ws, nullptr))) return st;
+      counts = reinterpret_cast<int32_t*>(ws);
     }
     return ccc::launch_count1_zero(v, ld, n_v, n_f, counts, 0, zero, stream) == hipSuccess
                ? CCC_OK
@@ -382,32 +446,26 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   const bool have_pairs = row_end > i_begin;
   const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 16);
   const size_t head = 256 + cnt_bytes;
-  void* ws = nullptr;
-  bool operands = f4 && have_pairs && ccc::operand_bytes(n_v, n_f) <= operand_limit();
-  size_t op_bytes = 0;
-  if (operands) {
+  size_t op_bytes = 0, part_bytes = 0;
+  if (f4 && have_pairs) {
     a.steps = ccc::operand_steps(n_f);
     op_bytes = (size_t)ccc::operand_bytes(n_v, n_f);
     a.part_bytes = ccc::mfma2_part_bytes(a);
     // the pre-pass is done with its part when the tiles write theirs
     const size_t pre_bytes = ccc::operand_part_bytes(n_v, n_f);
-    st = ccc::workspace(head + op_bytes + (pre_bytes > a.part_bytes ? pre_bytes : a.part_bytes),
-                        stream, lock, &ws);
-    if (st == CCC_ERR_NOMEM) operands = false;  // the packed rows do
-    else if (st) return st;
+    part_bytes = pre_bytes > a.part_bytes ? pre_bytes : a.part_bytes;
   }
-  if (!operands && (st = ccc::workspace(head, stream, lock, &ws))) return st;
-  char* wsb = static_cast<char*>(ws);
+  char *wsb = nullptr, *z = nullptr;
+  if ((st = ccc::workspace(head, op_bytes + part_bytes, stream, lock, &wsb, &z))) return st;
   int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 256);
   a.counts_a = a.counts_b = a.chunk_a = a.chunk_b = cnt;
   a.flag = reinterpret_cast<unsigned long long*>(wsb);
   a.id = g_call++;
-  if (operands) {
-    a.za = a.zb = wsb + head;
-    a.part = wsb + head + op_bytes;
+  if (z) {
+    a.za = a.zb = z;
+    a.part = z + op_bytes;
     ccc::OperandJob job{};
-    job.set[0] = ccc::OperandSet{v, ld, n_v, (uint32_t)ccc::operand_blocks(n_v), wsb + head, cnt,
-                                 nullptr};
+    job.set[0] = ccc::OperandSet{v, ld, n_v, (uint32_t)ccc::operand_blocks(n_v), z, cnt, nullptr};
     job.n_f = n_f;
     job.steps = a.steps;
     job.zero = zero;
@@ -435,7 +493,7 @@ static __device__ __align__(256) unsigned char scratch[CCC_NOALLOC_SCRATCH_BYTES
 std::mutex g_scratch_mu;
 std::vector<void*> g_scratch;  // indexed by device ordinal; null until looked up
 
-int noalloc_scratch(void** out) {
+int noalloc_scratch(char** out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return CCC_ERR_HIP;
   std::lock_guard<std::mutex> lk(g_scratch_mu);
@@ -448,7 +506,7 @@ int noalloc_scratch(void** out) {
     }
     g_scratch[dev] = p;
   }
-  *out = g_scratch[dev];
+  *out = static_cast<char*>(g_scratch[dev]);
   return CCC_OK;
 }
 
@@ -520,12 +578,11 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
     if (use_gram && (size_t)ng * (size_t)ng * 4 > fixed->bytes - bound) use_gram = false;
   }
   const size_t gram_bytes = use_gram ? (size_t)ng * (size_t)ng * 4 : 0;
-  void* ws = nullptr;
+  char* wsb = nullptr;
   std::unique_lock<std::mutex> lock;
-  if ((st = fixed ? noalloc_scratch(&ws)
-                  : ccc::workspace(head_bytes + gram_bytes, stream, lock, &ws)))
+  if ((st = fixed ? noalloc_scratch(&wsb)
+                  : ccc::workspace(head_bytes + gram_bytes, 0, stream, lock, &wsb, nullptr)))
     return st;
-  char* wsb = static_cast<char*>(ws);
   int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(wsb + 256);
   ccc::Triple3Args a{};
   // the complete-data kernel (fp4 operands, with the Gram matrix)
@@ -640,33 +697,29 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
   // of split tiles
   const size_t cnt_bytes = acc ? round256((size_t)(n_a + n_b) * 16) : 0, head = 256 + cnt_bytes;
   const size_t op_a = (size_t)ccc::operand_bytes(n_a, n_f), op_b = (size_t)ccc::operand_bytes(n_b, n_f);
-  bool operands = f4 && (int64_t)(op_a + op_b) <= operand_limit();
   std::unique_lock<std::mutex> lock;
-  void* ws = nullptr;
-  if (operands) {
+  if (f4) {
     a.steps = ccc::operand_steps(n_f);
     a.part_bytes = ccc::mfma2_part_bytes(a);
-    st = ccc::workspace(head + op_a + op_b + a.part_bytes, stream, lock, &ws);
-    if (st == CCC_ERR_NOMEM) operands = false;  // the packed rows do
-    else if (st) return st;
   }
-  if (!operands && (st = ccc::workspace(head, stream, lock, &ws))) return st;
-  char* wsb = static_cast<char*>(ws);
+  char *wsb = nullptr, *z = nullptr;
+  if ((st = ccc::workspace(head, f4 ? op_a + op_b + a.part_bytes : 0, stream, lock, &wsb, &z)))
+    return st;
   int32_t* chunk_a = acc ? reinterpret_cast<int32_t*>(wsb + 256) : counts_a;
   int32_t* chunk_b = acc ? chunk_a + 4 * n_a : counts_b;
   a.chunk_a = chunk_a;
   a.chunk_b = chunk_b;
   a.flag = acc ? nullptr : reinterpret_cast<unsigned long long*>(wsb);
   a.id = g_call++;
-  if (operands) {
-    a.za = wsb + head;
-    a.zb = wsb + head + op_a;
-    a.part = wsb + head + op_a + op_b;
+  if (z) {
+    a.za = z;
+    a.zb = z + op_a;
+    a.part = z + op_a + op_b;
     ccc::OperandJob job{};
-    job.set[0] = ccc::OperandSet{va, lda, n_a, (uint32_t)ccc::operand_blocks(n_a), wsb + head,
-                                 counts_a, acc ? chunk_a : nullptr};
-    job.set[1] = ccc::OperandSet{vb, ldb, n_b, (uint32_t)ccc::operand_blocks(n_b),
-                                 wsb + head + op_a, counts_b, acc ? chunk_b : nullptr};
+    job.set[0] = ccc::OperandSet{va, lda, n_a, (uint32_t)ccc::operand_blocks(n_a), z, counts_a,
+                                 acc ? chunk_a : nullptr};
+    job.set[1] = ccc::OperandSet{vb, ldb, n_b, (uint32_t)ccc::operand_blocks(n_b), z + op_a,
+                                 counts_b, acc ? chunk_b : nullptr};
     job.n_f = n_f;
     job.steps = a.steps;
     job.accumulate = acc ? 1 : 0;
@@ -708,20 +761,15 @@ int ccc_2way_multi(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int s
   // workspace: the counts (unless the caller's) and on fp4 the operands
   std::unique_lock<std::mutex> lock;
   const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 32);
-  const size_t op_bytes = ccc::multi_operand_bytes(n_v, n_f, s);
-  bool operands = f4 && n_v >= 2 && n_f > 0 && (int64_t)op_bytes <= operand_limit();
-  void* ws = nullptr;
-  if (operands) {
-    st = ccc::workspace(cnt_bytes + op_bytes, stream, lock, &ws);
-    if (st == CCC_ERR_NOMEM) operands = false;  // the rows as given do
-    else if (st) return st;
-  }
-  if (!operands && cnt_bytes && (st = ccc::workspace(cnt_bytes, stream, lock, &ws))) return st;
-  int32_t* cnt = counts ? counts : static_cast<int32_t*>(ws);
-  void* z = operands ? static_cast<char*>(ws) + cnt_bytes : nullptr;
+  const size_t op_bytes = f4 && n_v >= 2 && n_f > 0 ? ccc::multi_operand_bytes(n_v, n_f, s) : 0;
+  char *ws = nullptr, *z = nullptr;
+  if ((cnt_bytes || op_bytes) &&
+      (st = ccc::workspace(cnt_bytes, op_bytes, stream, lock, &ws, &z)))
+    return st;
+  int32_t* cnt = counts ? counts : reinterpret_cast<int32_t*>(ws);
   const hipError_t e =
-      operands ? ccc::launch_multi_operands(v, ld, n_v, n_f, s, cnt, z, stream)
-               : ccc::launch_multi_count(v, ld, n_v, n_f, s, cnt, stream);
+      z ? ccc::launch_multi_operands(v, ld, n_v, n_f, s, cnt, z, stream)
+        : ccc::launch_multi_count(v, ld, n_v, n_f, s, cnt, stream);
   if (e != hipSuccess) return CCC_ERR_HIP;
   if (n_v < 2) return CCC_OK;
   return ccc::launch_multi2(v, ld, n_v, n_f, s, tables, ccc, cnt, o.gamma, f4, z, stream) ==
@@ -766,10 +814,11 @@ void ccc_release_workspace(void) {
   bool have_cur = hipGetDevice(&cur) == hipSuccess;
   for (auto* list : {&g_ws, &g_retired}) {
     for (const Workspace& w : *list) {
-      if (!w.ptr) continue;
+      if (!w.ptr && !w.ops) continue;
       if (hipSetDevice(w.dev) == hipSuccess) {
         (void)hipDeviceSynchronize();
         (void)hipFree(w.ptr);
+        (void)hipFree(w.ops);
       }
     }
     list->clear();

@@ -369,6 +369,10 @@ hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n
                               hipStream_t stream, unsigned long long* flag = nullptr,
                               unsigned long long id = 0, int64_t flag_from = 0);
 hipError_t launch_operands(OperandJob job, hipStream_t stream);
+// Room for a batch's operands beside the workspaces', and the account of those
+// that the batches hold (api.hip).
+bool batch_operands_fit(int dev, size_t bytes);
+void hold_batch_operands(int dev, int64_t bytes);
 // Shares of the fields for the pass over one set: few blocks of long rows are
 // bound by the memory path of the few CUs that hold them (24 blocks x 977
 // super-steps: 39 us in one share), but the counts' second launch costs 5 us.

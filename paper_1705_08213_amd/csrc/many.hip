@@ -300,6 +300,8 @@ struct Entry {
   int64_t total_rows = 0;
   int path = 0;
   bool operands = false;          // the rows as operands in dbuf
+  int dev = 0;
+  int64_t held = 0;               // bytes of them
   int64_t total_blocks = 0;       // 16-row blocks of all problems
   bool f4 = true;                 // fp4 operands (every n_f <= kF4MaxFields), else int8
   double gamma = 0;
@@ -323,6 +325,7 @@ void destroy(Entry* e) {
   }
   if (e->ev_fork) (void)hipEventDestroy(e->ev_fork);
   if (e->dbuf) (void)hipFree(e->dbuf);
+  if (e->held) hold_batch_operands(e->dev, -e->held);
   delete e;
 }
 
@@ -582,9 +585,11 @@ int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f
     e->key = key;
     int64_t op_bytes = 0;
     for (int p = 0; p < n_probs; ++p) op_bytes += operand_bytes(probs[p].n_v, probs[p].n_f);
-    const char* limit = getenv("CCC_OPERAND_LIMIT");
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
     const bool operands = f4 && opts.path != CCC_PATH_POPCOUNT &&
-                          op_bytes <= (limit && *limit ? atoll(limit) : kManyOperandLimit);
+                          op_bytes <= kManyOperandLimit &&
+                          batch_operands_fit(dev, (size_t)op_bytes);
     int st = build_entry(probs, n_probs, opts, f4, operands, e);
     if (st == CCC_ERR_NOMEM && operands) {  // the packed rows do
       delete e;
@@ -617,6 +622,8 @@ int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f
       }
     }
     g_cache.push_back(e);
+    e->dev = dev;
+    if (e->operands) hold_batch_operands(dev, e->held = op_bytes);
     timing_host("many_setup", std::chrono::duration<double, std::milli>(
                                   std::chrono::steady_clock::now() - t0).count());
   }

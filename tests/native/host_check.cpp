@@ -91,6 +91,12 @@ int launch_limits() {
   return 0;
 }
 
+bool is_allocated(const void* p) {
+  for (auto& a : allocated)
+    if (a.first <= (uintptr_t)p && (uintptr_t)p < a.first + a.second) return true;
+  return false;
+}
+
 // The workspace of the last 2-way call: its flag and its operands.
 const Launch* last_tiles() {
   for (size_t k = launches.size(); k-- > 0;)
@@ -102,13 +108,13 @@ const Launch* last_tiles() {
 // eager call, and what it was given stays where it is.
 int captures() {
   std::vector<const void*> flags, ops;
-  auto call = [&](int s, unsigned long long id, int64_t n_v) {
+  auto call = [&](int s, unsigned long long id, int64_t n_v, bool grows = false) {
     if (id) capture[stream(s)] = id;
     const int st = two_way(n_v, 2000, stream(s));
     capture.clear();
     if (st != CCC_OK) return false;
     for (const void* f : flags)
-      if (f == last_tiles()->pair.flag) return false;
+      if (!grows && f == last_tiles()->pair.flag) return false;
     for (const void* z : ops)
       if (z == last_tiles()->pair.za) return false;
     flags.push_back(last_tiles()->pair.flag);
@@ -122,34 +128,89 @@ int captures() {
   CHECK(call(2, 9, 300));   // a fork of that capture
   CHECK(call(2, 0, 300));
   const long f0 = frees;
-  CHECK(call(1, 9, 3000));  // outgrown within the capture: nodes hold the old one
+  CHECK(call(1, 9, 3000, true));  // outgrown within the capture: nodes hold the old one
   CHECK(frees == f0);
   const size_t held = flags.size() - 1;
-  CHECK(call(1, 0, 6000));  // the eager call's own buffer alone goes
-  for (size_t k = 1; k < held; ++k) {
-    bool found = false;
-    for (auto& a : allocated)
-      if (a.first <= (uintptr_t)flags[k] && (uintptr_t)flags[k] < a.first + a.second) found = true;
-    CHECK(found);
-  }
+  CHECK(call(1, 0, 6000, true));  // the eager call's own buffer alone goes
+  CHECK(frees == f0 + 1);
+  for (size_t k = 1; k < held; ++k) CHECK(is_allocated(flags[k]) && is_allocated(ops[k]));
   // graphs that are no more give their buffers back, behind a wait; others stay
   for (unsigned long long id = 100; id < 140; ++id) {
     CHECK(call(1, id, 300));
     if (id != 120) destroy_graph(id);
-    CHECK(call(3, 0, 200 + (int)id));  // eager
+    CHECK(call(3, 0, 200 + (int)id, true));  // eager
     flags.pop_back();  // (its buffer is the same every time)
     ops.pop_back();
-    CHECK(allocated.size() < 24);
+    CHECK(allocated.size() < 48);
   }
-  const void* live = flags[flags.size() - 20];
   CHECK(graphs.count(120) == 1);
-  bool found = false;
-  for (auto& a : allocated) found |= a.first <= (uintptr_t)live && (uintptr_t)live < a.first + a.second;
-  CHECK(found);
+  CHECK(is_allocated(flags[flags.size() - 20]) && is_allocated(ops[flags.size() - 20]));
   ccc_release_workspace();
   CHECK(allocated.empty() && used == 0);
   destroy_graph(120);  // later than its buffer
   CHECK(call(1, 0, 300));
+  return 0;
+}
+
+int64_t operand_bytes(int64_t n_v, int64_t n_f) { return ccc::operand_bytes(n_v, n_f); }
+bool on_operands() { return last_tiles()->pair.za != nullptr; }
+
+// On a card that is nearly full a call takes the packed rows at once: no waits,
+// no failed allocation, and nobody's buffers go; with room again it takes
+// operands.  They never take more than half of what is free.
+int nearly_full() {
+  for (int s = 1; s <= 3; ++s) CHECK(two_way(400, 4000, stream(s)) == CCC_OK && on_operands());
+  const long f0 = frees, s0 = syncs, m0 = mallocs;
+  const size_t whole = card;
+  card = used + (size_t(20) << 20);
+  const auto before = allocated;
+  for (int rep = 0; rep < 3; ++rep)
+    for (int s = 1; s <= 3; ++s) {
+      CHECK(operand_bytes(3000, 40000) > (int64_t(20) << 20));
+      CHECK(two_way(3000, 40000, stream(s)) == CCC_OK && !on_operands());
+      CHECK(two_way(2000, 25000, stream(s)) == CCC_OK && !on_operands());  // past half
+    }
+  CHECK(block(3000, 3000, 20000) == CCC_OK && !on_operands());  // (a workspace of its own)
+  CHECK(ccc_2way_multi(fk<uint8_t>(), 3000, 20000, 20000, 4, fk<int32_t>(), nullptr,
+                       fk<int32_t>(), nullptr, stream(2)) == CCC_OK);
+  CHECK(frees == f0 && syncs == s0 && failed == 0 && mallocs == m0 + 1);
+  for (auto& a : before) CHECK(allocated.count(a.first) == 1);
+  CHECK(two_way(400, 4000, stream(2)) == CCC_OK && on_operands());  // fits what it has
+  card = whole;
+  CHECK(two_way(3000, 40000, stream(2)) == CCC_OK && on_operands());
+  // what a call cannot do without evicts what no graph holds
+  card = used + (size_t(4) << 20);
+  launches.clear();
+  CHECK(ccc_2way(fk<uint8_t>(), 600000, 40, 16, fk<int32_t>(), nullptr, nullptr, nullptr,
+                 stream(3)) == CCC_OK);  // 9.6 MB of counts
+  CHECK(failed == 1);
+  return 0;
+}
+
+// Over all streams and batches the library holds at most 16 GiB of operands.
+int held() {
+  const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
+  int on = 0;
+  for (int s = 1; s <= 12; ++s) {
+    CHECK(two_way(65536, 200000, stream(s)) == CCC_OK);  // 3.3 GB
+    on += on_operands();
+    CHECK(used <= limit + rest);
+  }
+  CHECK(on == 5);
+  std::vector<ccc_problem> p(1, ccc_problem{fk<uint8_t>(), 40000, 100000, ld_of(100000),
+                                            fk<int32_t>(), fk<double>(), fk<int32_t>()});
+  for (int k = 0; k < 6; ++k) {  // 1 GB each
+    p[0].tables = fk<int32_t>(1024 * k);
+    CHECK(ccc_2way_many(p.data(), 1, nullptr, nullptr) == CCC_OK);
+    CHECK(used <= limit + rest);
+  }
+  ccc_release_workspace();
+  CHECK(used == 0);
+  for (int k = 0; k < 6; ++k) {
+    p[0].tables = fk<int32_t>(1024 * k);
+    CHECK(ccc_2way_many(p.data(), 1, nullptr, nullptr) == CCC_OK);
+  }
+  CHECK(used > size_t(5) << 30);  // operands again
   return 0;
 }
 
@@ -158,6 +219,8 @@ int main(int argc, char** argv) {
   int r = 2;
   if (what == "launch_limits") r = launch_limits();
   if (what == "captures") r = captures();
+  if (what == "nearly_full") r = nearly_full();
+  if (what == "held") r = held();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

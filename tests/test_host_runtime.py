@@ -58,3 +58,14 @@ def test_captured_calls_have_workspaces_of_their_own(host_check):
     """Two captures on one stream, the forks of a capture and the stream's eager
     calls all have their own workspaces, and a capture's stay allocated."""
     host_check("captures")
+
+
+def test_operands_without_room_cost_nothing(host_check):
+    """On a nearly full card calls read the packed rows without a wait, a failed
+    allocation or another stream's buffers given back."""
+    host_check("nearly_full")
+
+
+def test_operands_held_are_bounded(host_check):
+    """Twelve streams of 3.3 GB and six batches of 1 GB hold 16 GiB at most."""
+    host_check("held")
