@@ -49,7 +49,7 @@
  *    work is enqueued; outputs are then untouched.  CCC_ERR_HIP means a HIP
  *    call or launch failed after validation.
  *  - The library keeps one workspace per device and stream (allocated on
- *    first need, grown on demand, at most 16 per device besides those that a
+ *    first need, grown on demand, at most 128 per device besides those that a
  *    captured graph holds, released by ccc_release_workspace), so that calls
  *    on different streams never share scratch.  Calls under stream capture get
  *    a workspace of that capture alone, so that its graph may be replayed on

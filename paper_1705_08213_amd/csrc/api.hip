@@ -68,7 +68,11 @@ struct Workspace {
   uint64_t last_use = 0;
 };
 constexpr int kMaxGone = 8;
-constexpr size_t kMaxWorkspaces = 16;  // per device, those of captures aside
+// Workspaces of eager calls per device.  A framework's stream pool has 32
+// streams; one past the bound waits for the device and gives back the half that
+// was used longest ago, so that a program which makes streams without end waits
+// once in 64 of them.
+constexpr size_t kMaxWorkspaces = 128;
 
 std::mutex g_mu;
 std::vector<Workspace> g_ws;
@@ -280,25 +284,26 @@ int workspace(size_t bytes, size_t op_bytes, hipStream_t stream,
                                  [&](const Workspace& w) { return gone_here(w) && !w.ptr && !w.ops; }),
                   list->end());
   }
-  size_t at = g_ws.size(), mine = 0, oldest = g_ws.size();
+  size_t at = g_ws.size();
+  std::vector<uint64_t> used;  // last uses of the other streams'
   for (size_t i = 0; i < g_ws.size(); ++i) {
     const Workspace& w = g_ws[i];
     if (w.dev != dev) continue;
     if (w.stream == stream && w.thread == thread && w.capture == capture) at = i;
-    else if (!w.capture) {
-      ++mine;
-      if (oldest == g_ws.size() || w.last_use < g_ws[oldest].last_use) oldest = i;
-    }
+    else if (!w.capture) used.push_back(w.last_use);
   }
   if (at == g_ws.size()) {
-    if (mine >= kMaxWorkspaces && !capture && wait_for_device()) {
-      const Workspace* evict = &g_ws[oldest];
-      free_buffers(dev, [&](const Workspace& w) { return &w == evict; });
-      g_ws[oldest] = Workspace{};
-      at = oldest;
-    } else {
-      g_ws.push_back(Workspace{});
+    if (used.size() >= kMaxWorkspaces && !capture && wait_for_device()) {
+      std::nth_element(used.begin(), used.begin() + used.size() / 2, used.end());
+      const uint64_t median = used[used.size() / 2];
+      auto old = [&](const Workspace& w) {
+        return w.dev == dev && !w.capture && w.last_use < median;
+      };
+      free_buffers(dev, old);
+      g_ws.erase(std::remove_if(g_ws.begin(), g_ws.end(), old), g_ws.end());
     }
+    at = g_ws.size();
+    g_ws.push_back(Workspace{});
     g_ws[at].dev = dev;
     g_ws[at].stream = stream;
     g_ws[at].thread = thread;

@@ -187,6 +187,28 @@ int nearly_full() {
   return 0;
 }
 
+// Forty streams in turn: once each has its workspace, no call waits or allocates;
+// streams without end do not add up, and seldom wait.
+int many_streams() {
+  for (int rep = 0; rep < 4; ++rep) {
+    const long s0 = syncs, m0 = mallocs;
+    for (int s = 1; s <= 40; ++s) {
+      CHECK(two_way(400, 4000, stream(s)) == CCC_OK && on_operands());
+      CHECK(select3(40, 100) == CCC_OK);
+    }
+    if (rep) CHECK(syncs == s0 && mallocs == m0);
+  }
+  const long s0 = syncs;
+  for (int s = 100; s < 1100; ++s) {
+    CHECK(two_way(400, 4000, stream(s)) == CCC_OK && on_operands());
+    CHECK(allocated.size() <= 2 * 130);
+  }
+  CHECK(syncs - s0 <= 20);
+  ccc_release_workspace();
+  CHECK(allocated.empty());
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -221,6 +243,7 @@ int main(int argc, char** argv) {
   if (what == "captures") r = captures();
   if (what == "nearly_full") r = nearly_full();
   if (what == "held") r = held();
+  if (what == "many_streams") r = many_streams();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

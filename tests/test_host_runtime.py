@@ -69,3 +69,9 @@ def test_operands_without_room_cost_nothing(host_check):
 def test_operands_held_are_bounded(host_check):
     """Twelve streams of 3.3 GB and six batches of 1 GB hold 16 GiB at most."""
     host_check("held")
+
+
+def test_forty_streams_in_turn_wait_for_nothing(host_check):
+    """More streams than a framework's pool has: no waits and no allocations
+    after the first round; a thousand streams wait once in 64."""
+    host_check("many_streams")
