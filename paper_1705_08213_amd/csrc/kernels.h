@@ -349,8 +349,9 @@ struct TuneChoice {
 int tune_forced_oneshot(int n_variants);
 // Shape of a 2-way call on operands by its 32 x 32 tiles and fields: 0 = 64 x
 // 128 staged tiles, 1 = field-split 32 x 32 tiles, 2 = 64 x 64 staged tiles
-// (mfma2.hip).
-int operand_variant(int64_t tiles, int64_t n_f, bool selection);
+// (mfma2.hip).  dense_ccc: a dense triangle with CCC rows; mixed: a selection or
+// an accumulating call.
+int operand_variant(int64_t tiles, int64_t n_f, bool dense_ccc, bool mixed);
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants);
 
 // Optional event timing around the main kernel of a launcher (no-ops unless

@@ -469,7 +469,7 @@ int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, boo
       const char* forced = getenv("CCC_MANY_VARIANT");  // 0 .. 2 of the operand shapes
       x.variant = forced && q.n_f <= tile2::kStagedMaxFields && tc.variant < 3
                       ? tc.variant
-                      : operand_variant(t, q.n_f, false);
+                      : operand_variant(t, q.n_f, q.ccc != nullptr, false);
       // a work list of millions of small tiles costs the host more than they gain
       if (x.variant == 1 && t > (1 << 23) && q.n_f <= tile2::kStagedMaxFields) x.variant = 0;
     }

@@ -302,7 +302,8 @@ OperandShape operand_shape(const Pair2Args& a) {
   if (forced >= 0 && a.n_f <= tile2::kStagedMaxFields)
     s.variant = forced;
   else
-    s.variant = operand_variant(tiles, a.n_f, a.sel.count != nullptr);
+    s.variant = operand_variant(tiles, a.n_f, a.tri && a.ccc && !a.sel.count,
+                                a.sel.count || a.accumulate);
   if (s.variant == 1 && tiles > 0) {
     // Enough workgroups for two per CU, but no share below 16 super-steps:
     // the sums' way through memory and the second launch cost about 5 us
@@ -363,20 +364,33 @@ hipError_t launch_operands_out(const Pair2Args& a, hipStream_t stream) {
 }  // namespace
 
 // The shape by the number of 32 x 32 tiles (n^2 / 2048 for a triangle) and
-// super-steps, from timings of whole calls with 1% missing, us for shapes 1 /
-// 2 / 0: 1500 x 9000 39 / 51 / 56, 2600 x 6000 69 / 65 / 70, 2600 x 20000 128 /
-// 134 / 144, 3500 x 4000 92 / 94 / 105, 4500 x 15000 273 / 249 / 298, 8000 x
-// 10000 656 / 569 / 586, 12000 x 4000 980 / 893 / 872, 16384 x 32768 6570 /
-// 5880 / 5660.  Small tiles give a small call more workgroups and a shorter
-// chain each; large ones read their operands less often.  With very short
-// fields a call is its output, and the 32 x 32 tiles, one block per wave,
-// start storing at once: 12000 x 1000 719 / 862 / 835.  A selection stores
-// little, so its smaller tiles pay for longer (12000 x 8009: 957 / 1000 for
-// shapes 2 / 0).
-int operand_variant(int64_t tiles, int64_t n_f, bool selection) {
+// fields, from timings of whole calls.  Small tiles give a small call more
+// workgroups and a shorter chain each; large ones read their operands less
+// often.
+//
+// Dense triangles with CCC rows (us for shapes 1 / 2 / 0, 1% missing): 1500 x
+// 9000 39 / 51 / 56, 2600 x 6000 69 / 65 / 70, 2600 x 20000 128 / 134 / 144,
+// 3500 x 4000 92 / 94 / 105, 4500 x 15000 273 / 249 / 298, 8000 x 10000 656 /
+// 569 / 586, 12000 x 4000 980 / 893 / 872, 16384 x 32768 6570 / 5880 / 5660.
+// With very short fields such a call is its output, 48 bytes a pair in rows
+// that start anywhere in a line, and the 32 x 32 tiles, one block per wave,
+// start storing at once: 12000 x 1000 719 / 862 / 835, complete data 9000 x
+// 1000 406 / 536 / 547.
+//
+// Every other form puts out less (selections, tables alone), reads what it
+// adds to, or writes rows of a rectangle that start on whole 16 bytes times
+// n_b, so the operands' reads weigh more, however short the fields: selection
+// 3000 x 300 48 / 32 / 38, 30000 x 1000 3547 / 1814 / 1988, 2400 x 300 34 / 24,
+// but 2100 x 20000 89 / 109; tables alone 4000 x 1000 67 / 38 / 47; rectangles
+// 4000 x 1024 x 4000 77 / 62 / 64, 256 x 1000000 x 1000 3528 / 2590 / 2585;
+// accumulating 8000 x 8000 x 256 616 / 400 / 546, 8000 x 8000 x 8192 1076 /
+// 783 / 934, but 1500 x 1500 x 8192 49 / 57 / 71.  Selections and accumulating
+// calls (`mixed`) keep the 64 x 64 tile for longer: 12000 x 12000 x 8192
+// accumulating 2418 / 1836 / 2061, selection 12000 x 8009 957 / 1000 (2 / 0).
+int operand_variant(int64_t tiles, int64_t n_f, bool dense_ccc, bool mixed) {
   if (n_f > tile2::kStagedMaxFields) return 1;  // four waves' sums, each exact
-  if (tiles < 6000 || n_f <= 1024) return 1;
-  return tiles < 50000 || (selection && n_f < 16384) ? 2 : 0;
+  if (dense_ccc ? tiles < 6000 || n_f <= 1024 : tiles < 2500) return 1;
+  return tiles < 50000 || (mixed && n_f < 16384) ? 2 : 0;
 }
 
 size_t mfma2_part_bytes(const Pair2Args& a) {

@@ -66,7 +66,7 @@ int launch_limits() {
       for (int64_t n_f : {1000, 1025, 9000}) {
         launches.clear();
         CHECK(select2(n, n_f, o) == CCC_OK);
-        if (!o && n_f == 1000) CHECK(covers("mfma2_split_kernel", squares(n, 32)));
+        if (!o && n > 2000 && n_f < 1100) CHECK(covers("mfma2_operand_kernel", squares(n, 64)));
         if (o == &pop) CHECK(covers("pop2_kernel", squares(n, 64)));
       }
     }
@@ -209,6 +209,36 @@ int many_streams() {
   return 0;
 }
 
+// The 2-way tiles that calls take, by form and size.
+int shapes() {
+  ccc_opts acc = ccc_default_opts(), fin = ccc_default_opts();
+  acc.flags = CCC_ACCUMULATE;
+  fin.flags = CCC_FINALIZE;
+  auto split = [] { return is(*last_tiles(), "mfma2_split"); };
+  auto staged64 = [] { return is(*last_tiles(), "mfma2_operand_kernel") && is(*last_tiles(), "ELi2ELi2ELi4E"); };
+  auto tables = [](int64_t n_v, int64_t n_f) {
+    return ccc_2way(fk<uint8_t>(), n_v, n_f, ld_of(n_f), fk<int32_t>(), nullptr, fk<int32_t>(),
+                    nullptr, nullptr);
+  };
+  // dense triangles with CCC rows: small tiles while small or short
+  CHECK(two_way(3000, 4000) == CCC_OK && split());
+  CHECK(two_way(9000, 1000) == CCC_OK && split());
+  CHECK(two_way(5000, 4000) == CCC_OK && staged64());
+  // the other forms: larger tiles earlier, and however short the fields
+  CHECK(select2(2100, 20000) == CCC_OK && split());
+  CHECK(select2(2400, 300) == CCC_OK && staged64());
+  CHECK(select2(30000, 1000) == CCC_OK && staged64());
+  CHECK(tables(3000, 300) == CCC_OK && staged64());
+  CHECK(tables(8000, 1000) == CCC_OK && staged64());
+  CHECK(block(1024, 4000, 4000, &fin) == CCC_OK && staged64());
+  CHECK(block(256, 1000000, 1000, &fin) == CCC_OK && !split());
+  CHECK(block(1000, 1000, 4000, &fin) == CCC_OK && split());
+  CHECK(block(8000, 8000, 256, &acc) == CCC_OK && staged64());
+  CHECK(block(8000, 8000, 8192, &acc) == CCC_OK && staged64());
+  CHECK(block(1500, 1500, 8192, &acc) == CCC_OK && split());
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -244,6 +274,7 @@ int main(int argc, char** argv) {
   if (what == "nearly_full") r = nearly_full();
   if (what == "held") r = held();
   if (what == "many_streams") r = many_streams();
+  if (what == "shapes") r = shapes();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

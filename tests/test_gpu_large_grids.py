@@ -1,4 +1,4 @@
-"""A call of more tiles than one launch holds (200,000 rows: 19.5 million 32 x 32
+"""A call of more tiles than one launch holds (400,000 rows: 19.5 million 64 x 64
 tiles of 256 threads, where HIP takes fewer than 2^32 work-items)."""
 import pytest
 
@@ -13,14 +13,14 @@ def test_selection_past_one_launch():
     planted rows that do: one entry 0.5 (1 - 1/3)^2 = 0.222 per planted pair's
     (0,0) and (1,1), spread over the triangle from its first to its last tile."""
     import torch
-    n_v, n_f = 200000, 1000
+    n_v, n_f = 400000, 1000
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     lo = torch.randint(0, 256, (n_v, 256), dtype=torch.uint8, device="cuda", generator=g) & 0x55
     hi = torch.randint(0, 256, (n_v, 256), dtype=torch.uint8, device="cuda", generator=g) & 0xAA
     v = lo | (hi & (lo << 1))  # codes 00, 01, 11
-    pairs = [(0, 1), (0x1F, 199999), (77, 150000), (100000, 100001), (123456, 185400),
-             (185344, 185345), (199990, 199998)]
+    pairs = [(0, 1), (0x1F, 399999), (77, 150000), (200000, 200001), (234567, 385400),
+             (370688, 370689), (399990, 399998)]
     for k, (i, j) in enumerate(pairs):  # half the fields 11, half 00, another pattern each
         bits = torch.randint(0, 2, (1024,), dtype=torch.uint8, generator=torch.Generator().manual_seed(k))
         row = (bits.view(256, 4) * torch.tensor([3, 12, 48, 192], dtype=torch.uint8)).sum(1)

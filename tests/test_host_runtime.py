@@ -49,7 +49,7 @@ def host_check(tmp_path_factory):
 
 def test_launches_stay_within_the_runtime_limits(host_check):
     """No launch of 2^32 or more work-items along a dimension, whatever the
-    sizes: a call of 200,000 rows and 1000 fields is 19.5 million 32 x 32
+    sizes: a selection of 400,000 rows and 1000 fields is 19.5 million 64 x 64
     tiles of 256 threads."""
     host_check("launch_limits")
 
@@ -75,3 +75,9 @@ def test_forty_streams_in_turn_wait_for_nothing(host_check):
     """More streams than a framework's pool has: no waits and no allocations
     after the first round; a thousand streams wait once in 64."""
     host_check("many_streams")
+
+
+def test_tile_shapes_by_form_and_size(host_check):
+    """Selections, tables alone, rectangles and accumulating calls leave the
+    32 x 32 tiles earlier than dense triangles with CCC rows do."""
+    host_check("shapes")
