@@ -333,6 +333,18 @@ hipError_t launch_split(const Pair2Args& a, int splits, hipStream_t stream) {
   return launch_tiles(mfma2_split_finish_kernel<OUT>, ntiles, a, stream, tm, tn, splits);
 }
 
+// Whether the complete-data tiles stream their tables.  Long fields bind them by
+// their operand reads, which a plain output stream pushes out of L2; short
+// ones by the output, whose lines plain stores let L2 join (triangles, plain /
+// streamed: 16000 x 40000 3.20 / 2.87 ms, 16384 x 16384 2.26 / 2.19, 16384 x
+// 2000 1.71 / 2.06).  In a rectangle whose rows start on multiples of 64 bytes
+// there is little to join (us, 12000 x 12000: x 1500 1356 / 1386, x 3000 1430 /
+// 1412, x 4000 1470 / 1391, x 9000 1649 / 1511; 12000 x 12004 x 4000 1570 / 1504;
+// but 12000 x 12001 x 4000 1825 / 2131).
+bool stream_tables(const Pair2Args& a) {
+  return a.n_f >= (!a.tri && a.n_b % 4 == 0 ? 3000 : 12288);
+}
+
 template <tile2::Out OUT>
 hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
   OperandShape s = operand_shape(a);
@@ -341,14 +353,9 @@ hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
   if (s.variant == 1) return launch_split<OUT>(a, s.splits, stream);  // its tiles vote
   if constexpr (OUT != tile2::kAccumulate) {  // (whose counts are running totals)
     const int64_t n = tile_grid<32 * kCOM, 32 * kCON>(a, tm, tn);
-    // Long fields bind these tiles by their operand reads, which a plain
-    // output stream pushes out of L2; short ones by the output, whose lines
-    // plain stores let L2 join (16000 x 40000: 3.20 ms plain, 2.87 with the
-    // tables streamed; 16384 x 16384: 2.26 and 2.19; 16384 x 2000: 1.71 and
-    // 2.06).
     auto* kernel = mfma2_complete_operand_kernel<OUT, kCOM, kCON>;
     if constexpr (OUT == tile2::kDense)
-      if (a.n_f >= 12288) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
+      if (stream_tables(a)) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
     if (hipError_t e = launch_tiles(kernel, n, a, stream, tm, tn); e != hipSuccess) return e;
   }
   return s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)

@@ -239,6 +239,30 @@ int shapes() {
   return 0;
 }
 
+// Whether the complete-data tiles of the last call stream their tables (Out 3) or not (0).
+int streams() {
+  const Launch* complete = nullptr;
+  for (const Launch& l : launches)
+    if (is(l, "mfma2_complete_operand")) complete = &l;
+  if (!complete) return -1;
+  return is(*complete, "OutE3") ? 1 : is(*complete, "OutE0") ? 0 : -1;
+}
+int streamed_tables() {
+  ccc_opts fin = ccc_default_opts();
+  fin.flags = CCC_FINALIZE;
+  auto rect = [&](int64_t n_b, int64_t n_f) {
+    launches.clear();
+    return block(12000, n_b, n_f, &fin) == CCC_OK ? streams() : -2;
+  };
+  CHECK(rect(12000, 1500) == 0 && rect(12000, 3000) == 1 && rect(12000, 4000) == 1);
+  CHECK(rect(12004, 4000) == 1 && rect(12001, 4000) == 0 && rect(12001, 16000) == 1);
+  launches.clear();
+  CHECK(two_way(16384, 8000) == CCC_OK && streams() == 0);
+  launches.clear();
+  CHECK(two_way(16384, 16384) == CCC_OK && streams() == 1);
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -275,6 +299,7 @@ int main(int argc, char** argv) {
   if (what == "held") r = held();
   if (what == "many_streams") r = many_streams();
   if (what == "shapes") r = shapes();
+  if (what == "streamed_tables") r = streamed_tables();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

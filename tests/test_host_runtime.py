@@ -81,3 +81,9 @@ def test_tile_shapes_by_form_and_size(host_check):
     """Selections, tables alone, rectangles and accumulating calls leave the
     32 x 32 tiles earlier than dense triangles with CCC rows do."""
     host_check("shapes")
+
+
+def test_streamed_tables_of_complete_data(host_check):
+    """Rectangles whose rows start on multiples of 64 bytes stream their tables
+    from shorter fields on than other outputs."""
+    host_check("streamed_tables")
