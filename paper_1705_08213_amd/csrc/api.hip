@@ -563,14 +563,18 @@ int three_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_
   bool use_gram = o.path != CCC_PATH_POPCOUNT && ng <= kGramMaxRows && i_begin < row_end;
   // Small fp4 calls take the general kernel whatever their rows: the Gram
   // matrix and the complete-data kernel's few, longer workgroups cost more than
-  // its eight planes while its units make no more than two turns of the chip
-  // (us, complete data, complete-data form / general: 60 x 2000 83 / 34, 120 x
-  // 10000 150 / 67, 200 x 10000 185 / 135, 200 x 50000 481 / 464; 260 x 1000,
-  // 1320 units, 121 / 91, but 260 x 10000 187 / 204 and 260 x 50000 476 / 721).
+  // its eight planes while its units make one turn of the chip, and in two
+  // turns while the fields are not long (us, complete data, complete-data form /
+  // general: 60 x 2000 83 / 34, 120 x 10000 150 / 67, 180 x 200000, 430 units,
+  // 1484 / 1207; 200 x 10000, 630 units, 185 / 135, 200 x 100000 884 / 917; 228 x
+  // 20000, 904 units, 286 / 276, 228 x 40000 430 / 492; 260 x 1000, 1257 units,
+  // 121 / 91, but 260 x 10000 187 / 204 and 260 x 50000 476 / 721).
   if (f4 && use_gram) {
     const int64_t units =
         ccc::grid_unit_count(ccc::unit_grid(n_v, ccc::kRunTile, i_begin, row_end, 4));
-    if (units <= 1024 || (units < 2048 && n_f <= 2048)) use_gram = false;
+    if (units <= 512 || (units <= 1024 && units * n_f <= 20000000) ||
+        (units < 2048 && n_f <= 2048))
+      use_gram = false;
   }
   if (fixed) {
     // the bound of the documented interface: tables of unit offsets (8 bytes

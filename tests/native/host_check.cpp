@@ -263,6 +263,24 @@ int streamed_tables() {
   return 0;
 }
 
+// Which 3-way calls take the complete-data form.
+int small_triples() {
+  auto general_alone = [](int64_t n_v, int64_t n_f) {
+    launches.clear();
+    if (ccc_3way(fk<uint8_t>(), n_v, n_f, ld_of(n_f), fk<int32_t>(), fk<double>(), fk<int32_t>(),
+                 nullptr, nullptr) != CCC_OK)
+      return -1;
+    for (const Launch& l : launches)
+      if (is(l, "mfma3_complete")) return 0;
+    return 1;
+  };
+  CHECK(general_alone(60, 2000) == 1 && general_alone(180, 200000) == 1);    // one turn
+  CHECK(general_alone(200, 20000) == 1 && general_alone(200, 100000) == 0);  // two turns
+  CHECK(general_alone(228, 20000) == 1 && general_alone(228, 40000) == 0);
+  CHECK(general_alone(260, 1000) == 1 && general_alone(260, 10000) == 0);
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -300,6 +318,7 @@ int main(int argc, char** argv) {
   if (what == "many_streams") r = many_streams();
   if (what == "shapes") r = shapes();
   if (what == "streamed_tables") r = streamed_tables();
+  if (what == "small_triples") r = small_triples();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

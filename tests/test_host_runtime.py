@@ -87,3 +87,9 @@ def test_streamed_tables_of_complete_data(host_check):
     """Rectangles whose rows start on multiples of 64 bytes stream their tables
     from shorter fields on than other outputs."""
     host_check("streamed_tables")
+
+
+def test_small_triples_rule(host_check):
+    """Two turns of the chip take the general 3-way kernel alone only while the
+    fields are not long."""
+    host_check("small_triples")
