@@ -654,8 +654,7 @@ __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, co
   __syncthreads();  // every wave is done with the stage
   constexpr int NS = 16 * (WM + WN);
   constexpr int SS = S * S;
-  using TV = std::conditional_t<SS % 4 == 0, u4, int>;      // pieces of tables
-  using CV = std::conditional_t<SS % 2 == 0, u4, double>;   // and of CCC rows
+  using CV = std::conditional_t<SS % 2 == 0, u4, double>;   // pieces of CCC rows
   constexpr int kOut = 4 * 16 * SS * sizeof(int);           // 4 rows' tables, or 2 rows' CCC
   constexpr int kWave = (NS * S * (int)sizeof(double) + kOut + 15) / 16 * 16;
   static_assert(4 * kWave <= sizeof(stage), "factors and store staging fit in the stage");
@@ -685,7 +684,20 @@ __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, co
         int t[SS];
 #pragma unroll
         for (int x = 0; x < SS; ++x) t[x] = tile2::f4_count(acc[m][n][x][e]);
-        if (a.tables) store_rows<SS, 4, int, TV>(a, a.tables, t, 0, ib, 4, j0, mine);
+        if constexpr (S == 3) {
+          // nine single words a pair: regrouping them costs more operations
+          // than its longer stretches save (us, through LDS and here: 100 x
+          // 1000 45.7 and 32.2, 4000 x 14000 620 and 543; tables alone 2000 x
+          // 100 47.4 and 35.0, 8000 x 1000 442 and 358)
+          const int64_t i = ib + 4 * g, j = j0 + rl;
+          if (a.tables && i < j && j < a.n) {
+            int32_t* o = a.tables + SS * pair_index(a.n, i, j);
+#pragma unroll
+            for (int x = 0; x < SS; ++x) o[x] = t[x];
+          }
+        } else if (a.tables) {
+          store_rows<SS, 4, int, u4>(a, a.tables, t, 0, ib, 4, j0, mine);
+        }
         if (a.ccc) {
           double r[SS];
           multi_values<S>(t, wi, wj, r);
