@@ -452,7 +452,7 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 16);
   const size_t head = 256 + cnt_bytes;
   size_t op_bytes = 0, part_bytes = 0;
-  if (f4 && have_pairs) {
+  if (f4 && have_pairs && ccc::operands_serve(a)) {
     a.steps = ccc::operand_steps(n_f);
     op_bytes = (size_t)ccc::operand_bytes(n_v, n_f);
     a.part_bytes = ccc::mfma2_part_bytes(a);
@@ -707,13 +707,14 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
   const size_t cnt_bytes = acc ? round256((size_t)(n_a + n_b) * 16) : 0, head = 256 + cnt_bytes;
   const size_t op_a = (size_t)ccc::operand_bytes(n_a, n_f), op_b = (size_t)ccc::operand_bytes(n_b, n_f);
   std::unique_lock<std::mutex> lock;
-  if (f4) {
+  size_t op_bytes = 0;
+  if (f4 && ccc::operands_serve(a)) {
     a.steps = ccc::operand_steps(n_f);
     a.part_bytes = ccc::mfma2_part_bytes(a);
+    op_bytes = op_a + op_b + a.part_bytes;
   }
   char *wsb = nullptr, *z = nullptr;
-  if ((st = ccc::workspace(head, f4 ? op_a + op_b + a.part_bytes : 0, stream, lock, &wsb, &z)))
-    return st;
+  if ((st = ccc::workspace(head, op_bytes, stream, lock, &wsb, &z))) return st;
   int32_t* chunk_a = acc ? reinterpret_cast<int32_t*>(wsb + 256) : counts_a;
   int32_t* chunk_b = acc ? chunk_a + 4 * n_a : counts_b;
   a.chunk_a = chunk_a;

@@ -370,6 +370,14 @@ hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n
                               hipStream_t stream, unsigned long long* flag = nullptr,
                               unsigned long long id = 0, int64_t flag_from = 0);
 hipError_t launch_operands(OperandJob job, hipStream_t stream);
+// Whether a 2-way call (or `tiles` 32 x 32 tiles of a batch's problem) is to run
+// on operands.  Past kStagedMaxFields fields only the field-split tiles keep
+// their sums exact there, and many of those read the operands too often: from
+// 3000 tiles on the packed rows are faster (ms, operands / packed rows: 2000
+// rows x 1,900,000 6.8 / 11.2, complete data 5.1 / 9.0; 3000 rows 13.9 / 15.6,
+// complete 13.4 / 9.1; 12000 x 4,000,000 500 / 365, complete 567 / 156).
+bool operands_serve(const Pair2Args& a);
+bool operands_serve(int64_t tiles, int64_t n_f);
 // Room for a batch's operands beside the workspaces', and the account of those
 // that the batches hold (api.hip).
 bool batch_operands_fit(int dev, size_t bytes);

@@ -428,16 +428,18 @@ hipError_t enqueue(const Entry& e, hipStream_t stream, bool fork) {
   return hipSuccess;
 }
 
+// 32 x 32 tiles of a problem.
+int64_t small_tiles(int64_t n_v) {
+  const int64_t t = (n_v + tile2::kSplitTile - 1) / tile2::kSplitTile;
+  return t * (t + 1) / 2;
+}
+
 // Build descriptors and the LPT-ordered work list; allocate and upload.
 int build_entry(const ccc_problem* probs, int n, const ccc_opts& o, bool f4, bool operands,
                 Entry* e) {
   e->f4 = f4;
   e->operands = operands;
   int64_t blocks = 0, batch_tiles = 0;  // 32 x 32 tiles of the whole batch
-  auto small_tiles = [](int64_t n_v) {
-    const int64_t t = (n_v + tile2::kSplitTile - 1) / tile2::kSplitTile;
-    return t * (t + 1) / 2;
-  };
   for (int p = 0; p < n; ++p) batch_tiles += small_tiles(probs[p].n_v);
   std::vector<ProbDesc> d(n);
   std::vector<WorkItem> items[kVariants];
@@ -584,11 +586,14 @@ int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f
     e = new Entry();
     e->key = key;
     int64_t op_bytes = 0;
-    for (int p = 0; p < n_probs; ++p) op_bytes += operand_bytes(probs[p].n_v, probs[p].n_f);
+    bool serve = f4 && opts.path != CCC_PATH_POPCOUNT;
+    for (int p = 0; p < n_probs; ++p) {
+      op_bytes += operand_bytes(probs[p].n_v, probs[p].n_f);
+      serve = serve && operands_serve(small_tiles(probs[p].n_v), probs[p].n_f);
+    }
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const bool operands = f4 && opts.path != CCC_PATH_POPCOUNT &&
-                          op_bytes <= kManyOperandLimit &&
+    const bool operands = serve && op_bytes <= kManyOperandLimit &&
                           batch_operands_fit(dev, (size_t)op_bytes);
     int st = build_entry(probs, n_probs, opts, f4, operands, e);
     if (st == CCC_ERR_NOMEM && operands) {  // the packed rows do

@@ -400,6 +400,14 @@ int operand_variant(int64_t tiles, int64_t n_f, bool dense_ccc, bool mixed) {
   return tiles < 50000 || (mixed && n_f < 16384) ? 2 : 0;
 }
 
+bool operands_serve(int64_t tiles, int64_t n_f) {
+  return n_f <= tile2::kStagedMaxFields || tiles < 3000;
+}
+bool operands_serve(const Pair2Args& a) {
+  int64_t tm, tn;
+  return operands_serve(split_tiles(a, tm, tn), a.n_f);
+}
+
 size_t mfma2_part_bytes(const Pair2Args& a) {
   const OperandShape s = operand_shape(a);
   if (s.variant != 1 || s.splits == 1) return 0;

@@ -281,6 +281,22 @@ int small_triples() {
   return 0;
 }
 
+// Where exact sums need the field-split tiles, large calls take the packed rows.
+int long_fields() {
+  const int64_t most = 1864135;  // 9 n_f <= 2^24
+  CHECK(two_way(8000, most) == CCC_OK && on_operands());
+  CHECK(two_way(8000, most + 1) == CCC_OK && !on_operands());
+  CHECK(two_way(2400, 4000000) == CCC_OK && on_operands() && is(*last_tiles(), "split"));
+  CHECK(block(40, 8000, 2000000) == CCC_OK && on_operands());
+  CHECK(block(4000, 4000, 2000000) == CCC_OK && !on_operands());
+  ccc_problem p{fk<uint8_t>(), 4000, 1900000, ld_of(1900000), fk<int32_t>(), fk<double>(),
+                fk<int32_t>()};
+  launches.clear();
+  CHECK(ccc_2way_many(&p, 1, nullptr, nullptr) == CCC_OK);
+  for (const Launch& l : launches) CHECK(!is(l, "operands_many"));
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -319,6 +335,7 @@ int main(int argc, char** argv) {
   if (what == "shapes") r = shapes();
   if (what == "streamed_tables") r = streamed_tables();
   if (what == "small_triples") r = small_triples();
+  if (what == "long_fields") r = long_fields();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

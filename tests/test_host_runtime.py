@@ -93,3 +93,9 @@ def test_small_triples_rule(host_check):
     """Two turns of the chip take the general 3-way kernel alone only while the
     fields are not long."""
     host_check("small_triples")
+
+
+def test_large_calls_on_long_fields_read_packed_rows(host_check):
+    """Past 1,864,135 fields only the field-split tiles are exact on operands;
+    calls of 3000 of them and more read the packed rows."""
+    host_check("long_fields")
