@@ -452,9 +452,10 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   const size_t cnt_bytes = counts ? 0 : round256((size_t)n_v * 16);
   const size_t head = 256 + cnt_bytes;
   size_t op_bytes = 0, part_bytes = 0;
+  const int64_t first = ccc::operand_first(i_begin);  // earlier rows are in no pair of the range
   if (f4 && have_pairs && ccc::operands_serve(a)) {
     a.steps = ccc::operand_steps(n_f);
-    op_bytes = (size_t)ccc::operand_bytes(n_v, n_f);
+    op_bytes = (size_t)ccc::operand_bytes(n_v - 16 * first, n_f);
     a.part_bytes = ccc::mfma2_part_bytes(a);
     // the pre-pass is done with its part when the tiles write theirs
     const size_t pre_bytes = ccc::operand_part_bytes(n_v, n_f);
@@ -467,10 +468,13 @@ int two_way(const uint8_t* v, int64_t n_v, int64_t n_f, int64_t ld, int64_t i_be
   a.flag = reinterpret_cast<unsigned long long*>(wsb);
   a.id = g_call++;
   if (z) {
-    a.za = a.zb = z;
+    // block 0's address, were it laid out
+    a.za = a.zb = reinterpret_cast<const void*>(reinterpret_cast<uintptr_t>(z) -
+                                                (uintptr_t)(first * a.steps * 1024));
     a.part = z + op_bytes;
     ccc::OperandJob job{};
-    job.set[0] = ccc::OperandSet{v, ld, n_v, (uint32_t)ccc::operand_blocks(n_v), z, cnt, nullptr};
+    job.set[0] = ccc::OperandSet{v, ld, n_v, (uint32_t)ccc::operand_blocks(n_v), (uint32_t)first, z,
+                                 cnt, nullptr};
     job.n_f = n_f;
     job.steps = a.steps;
     job.zero = zero;
@@ -726,9 +730,9 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
     a.zb = z + op_a;
     a.part = z + op_a + op_b;
     ccc::OperandJob job{};
-    job.set[0] = ccc::OperandSet{va, lda, n_a, (uint32_t)ccc::operand_blocks(n_a), z, counts_a,
+    job.set[0] = ccc::OperandSet{va, lda, n_a, (uint32_t)ccc::operand_blocks(n_a), 0, z, counts_a,
                                  acc ? chunk_a : nullptr};
-    job.set[1] = ccc::OperandSet{vb, ldb, n_b, (uint32_t)ccc::operand_blocks(n_b), z + op_a,
+    job.set[1] = ccc::OperandSet{vb, ldb, n_b, (uint32_t)ccc::operand_blocks(n_b), 0, z + op_a,
                                  counts_b, acc ? chunk_b : nullptr};
     job.n_f = n_f;
     job.steps = a.steps;

@@ -65,7 +65,8 @@ struct OperandSet {
   const uint8_t* v;
   int64_t ld, n;
   uint32_t blocks;  // (n + 15) / 16, or 0: no such set
-  void* z;          // [blocks][steps][1024 bytes]
+  uint32_t first;   // first block to lay out; those before are only counted
+  void* z;          // [blocks - first][steps][1024 bytes]
   int32_t* counts;  // [n][4] or null; added to when accumulating
   int32_t* chunk;   // [n][4] or null: this call's own counts
 };
@@ -370,6 +371,9 @@ hipError_t launch_count1_zero(const uint8_t* v, int64_t ld, int64_t n, int64_t n
                               hipStream_t stream, unsigned long long* flag = nullptr,
                               unsigned long long id = 0, int64_t flag_from = 0);
 hipError_t launch_operands(OperandJob job, hipStream_t stream);
+// First 16-row block that the tiles of a triangle's rows from i_begin on read:
+// no tile is larger than 256 rows.
+inline int64_t operand_first(int64_t i_begin) { return i_begin / 256 * 16; }
 // Whether a 2-way call (or `tiles` 32 x 32 tiles of a batch's problem) is to run
 // on operands.  Past kStagedMaxFields fields only the field-split tiles keep
 // their sums exact there, and many of those read the operands too often: from

@@ -54,7 +54,8 @@ __device__ __forceinline__ void operand_block(const OperandJob& job, const Opera
   const int64_t end = job.steps * (share + 1) / job.shares;
   const bool have = row < s.n;
   const uint8_t* p = s.v + (have ? row : s.n - 1) * s.ld + 16 * g;
-  u4* z = reinterpret_cast<u4*>(s.z) + b * job.steps * 64 + lane;
+  const bool lay = b >= s.first;  // uniform
+  u4* z = reinterpret_cast<u4*>(s.z) + (lay ? b - s.first : 0) * job.steps * 64 + lane;
   int n1 = 0, miss = 0;
   auto put = [&](int64_t st, const u4& x) {
     u4 o;
@@ -66,7 +67,7 @@ __device__ __forceinline__ void operand_block(const OperandJob& job, const Opera
       miss += __popc(ms);
       o[q] = c;
     }
-    z[st * 64] = o;
+    if (lay) z[st * 64] = o;
   };
   const u4 none = u4{0u, 0u, 0u, 0u};
   const int64_t whole = n_f / 256, nfull = end < whole ? end : whole;

@@ -297,6 +297,29 @@ int long_fields() {
   return 0;
 }
 
+// A row range lays out the rows from its first tile on, no more.
+int row_ranges() {
+  const int64_t n_v = 100000, n_f = 10000;
+  for (int64_t i0 : {0, 255, 256, 50000, 98976, 99990}) {
+    ccc_release_workspace();
+    launches.clear();
+    CHECK(ccc_2way_rows(fk<uint8_t>(), n_v, n_f, ld_of(n_f), i0, i0 + 8, fk<int32_t>(),
+                        fk<double>(), fk<int32_t>(), nullptr, nullptr) == CCC_OK);
+    const Launch& p = launches[0];
+    CHECK(is(p, "15operands_kernel"));
+    const int64_t first = p.job.set[0].first, step = p.job.steps * 1024;
+    CHECK(first == i0 / 256 * 16);
+    const uintptr_t z = (uintptr_t)p.job.set[0].z;
+    CHECK((uintptr_t)last_tiles()->pair.za + first * step == z);
+    // what the blocks from `first` on take is there
+    auto it = allocated.find(z);
+    const int64_t need = (n_v / 16 - first) * step;
+    CHECK(it != allocated.end() && (int64_t)it->second >= need);
+    CHECK((int64_t)it->second <= need + (int64_t(16) << 20));
+  }
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -336,6 +359,7 @@ int main(int argc, char** argv) {
   if (what == "streamed_tables") r = streamed_tables();
   if (what == "small_triples") r = small_triples();
   if (what == "long_fields") r = long_fields();
+  if (what == "row_ranges") r = row_ranges();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

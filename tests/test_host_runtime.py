@@ -99,3 +99,8 @@ def test_large_calls_on_long_fields_read_packed_rows(host_check):
     """Past 1,864,135 fields only the field-split tiles are exact on operands;
     calls of 3000 of them and more read the packed rows."""
     host_check("long_fields")
+
+
+def test_row_ranges_lay_out_their_own_rows(host_check):
+    """Rows before a range's first tile are counted, not laid out."""
+    host_check("row_ranges")
