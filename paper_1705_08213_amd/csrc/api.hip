@@ -739,7 +739,16 @@ int ccc_2way_block(const uint8_t* va, int64_t n_a, int64_t lda, const uint8_t* v
     job.accumulate = acc ? 1 : 0;
     job.flag = a.flag;
     job.id = a.id;
+    // Counts that share entries (both sides rows of one set, say) are written
+    // or added to one side after the other, as by the passes over packed rows.
+    const bool shared = counts_a < counts_b + 4 * n_b && counts_b < counts_a + 4 * n_a;
+    const ccc::OperandSet second = job.set[1];
+    if (shared) job.set[1] = ccc::OperandSet{};
     if (ccc::launch_operands(job, stream) != hipSuccess) return CCC_ERR_HIP;
+    if (shared) {
+      job.set[0] = second;
+      if (ccc::launch_operands(job, stream) != hipSuccess) return CCC_ERR_HIP;
+    }
   } else {
     if (acc && (ccc::launch_count1(va, lda, n_a, n_f, chunk_a, 0, stream) != hipSuccess ||
                 ccc::launch_count1(vb, ldb, n_b, n_f, chunk_b, 0, stream) != hipSuccess))

@@ -320,6 +320,30 @@ int row_ranges() {
   return 0;
 }
 
+// A block whose sides share counts adds to them one side after the other.
+int shared_counts() {
+  ccc_opts acc = ccc_default_opts();
+  acc.flags = CCC_ACCUMULATE;
+  auto passes = [&](int64_t n_a, int64_t n_b, int64_t offset) {
+    launches.clear();
+    int32_t* c = fk<int32_t>();
+    if (ccc_2way_block(fk<uint8_t>(), n_a, 256, fk<uint8_t>(), n_b, 256, 1000, fk<int32_t>(), c,
+                       c + 4 * offset, fk<double>(), &acc, nullptr) != CCC_OK)
+      return -1;
+    int k = 0;
+    for (const Launch& l : launches)
+      if (is(l, "15operands_kernel")) {
+        ++k;
+        if (l.job.set[0].blocks == 0 || (k == 2 && l.job.set[1].blocks != 0)) return -2;
+      }
+    return k;
+  };
+  CHECK(passes(100, 100, 0) == 2);   // the same counts
+  CHECK(passes(100, 50, 99) == 2);   // one entry shared
+  CHECK(passes(100, 50, 100) == 1);  // none
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -360,6 +384,7 @@ int main(int argc, char** argv) {
   if (what == "small_triples") r = small_triples();
   if (what == "long_fields") r = long_fields();
   if (what == "row_ranges") r = row_ranges();
+  if (what == "shared_counts") r = shared_counts();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

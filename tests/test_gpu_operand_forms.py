@@ -208,3 +208,32 @@ def test_batch_with_a_large_problem_on_long_fields():
     for i in list(range(0, n - 1, 97)) + [31, 32, 63, 64, 127, 128, 2477, 2478]:
         p = _pair0(n, i)
         assert_tables_equal(got[p:p + n - 1 - i], pt[i % k][np.arange(i + 1, n) % k])
+
+
+@pytest.mark.parametrize("limit", ["", "0"])
+@pytest.mark.parametrize("shift", [0, 100])
+def test_blocks_whose_sides_share_counts(shift, limit, monkeypatch):
+    """Both sides are rows of one set and point into one array of counts; an
+    accumulating call adds both sides' counts to the shared entries."""
+    import torch
+    if limit:
+        monkeypatch.setenv("CCC_OPERAND_LIMIT", limit)
+    n, n_f, chunk = 300, 900, 512
+    m = n - shift
+    v = synth.beta_hw(n, n_f, seed=7700, missing=0.02)
+    dv = dev(v)
+    va, vb = dv[:m].contiguous(), dv[shift:].contiguous()
+    counts = torch.zeros((n, 4), dtype=torch.int32, device="cuda")
+    t = torch.zeros((m, m, 4), dtype=torch.int32, device="cuda")
+    say("2way block shared counts", shift, limit)
+    for f0, k in ((0, chunk), (chunk, n_f - chunk)):
+        ccc.ccc_2way_block(va, vb, k, t, counts[:m], counts[shift:], accumulate=True,
+                           finalize=False, field_offset=f0 // 4)
+    ot, _ = oracle.block(v[:m], v[shift:], n_f)
+    assert_tables_equal(host(t), ot)
+    _, _, one = ccc.ccc_2way(dv, n_f)
+    want = host(one)
+    times = np.zeros(n, dtype=np.int64)
+    times[:m] += 1
+    times[shift:] += 1
+    assert np.array_equal(host(counts), want * times[:, None])

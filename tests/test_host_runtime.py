@@ -104,3 +104,9 @@ def test_large_calls_on_long_fields_read_packed_rows(host_check):
 def test_row_ranges_lay_out_their_own_rows(host_check):
     """Rows before a range's first tile are counted, not laid out."""
     host_check("row_ranges")
+
+
+def test_blocks_with_shared_counts_add_one_side_after_the_other(host_check):
+    """Two sides that share count entries are not added to by one launch, whose
+    workgroups would race on them."""
+    host_check("shared_counts")
