@@ -157,7 +157,7 @@ __device__ __forceinline__ void copy_async(gbytes base, uint32_t off, uint32_t d
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(dst), "v"(off), "s"(base)
-               : "memory");
+               : "memory", "m0");
 }
 
 // Steps 0 .. n - 1 of a workgroup of four waves whose ND pieces of 1 KB per
