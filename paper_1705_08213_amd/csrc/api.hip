@@ -113,11 +113,6 @@ bool fields_in_range(int64_t n_f, int64_t mult) { return n_f <= kInt32Max / mult
 
 size_t round256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-int64_t operand_limit() {
-  const char* env = getenv("CCC_OPERAND_LIMIT");
-  return env && *env ? atoll(env) : kOperandLimit;
-}
-
 int check_input(const uint8_t* v, int64_t n, int64_t n_f, int64_t ld) {
   if (n < 0 || n_f < 0 || ld < 0) return CCC_ERR_ARG;
   if (n > kInt32Max) return CCC_ERR_ARG;
@@ -132,6 +127,11 @@ int check_input(const uint8_t* v, int64_t n, int64_t n_f, int64_t ld) {
 }  // namespace
 
 namespace ccc {
+
+int64_t operand_limit() {
+  const char* env = getenv("CCC_OPERAND_LIMIT");
+  return env && *env ? atoll(env) : kOperandLimit;
+}
 
 namespace {
 

@@ -382,6 +382,8 @@ inline int64_t operand_first(int64_t i_begin) { return i_begin / 256 * 16; }
 // complete 13.4 / 9.1; 12000 x 4,000,000 500 / 365, complete 567 / 156).
 bool operands_serve(const Pair2Args& a);
 bool operands_serve(int64_t tiles, int64_t n_f);
+// Most operands that the library holds on a device (api.hip).
+int64_t operand_limit();
 // Room for a batch's operands beside the workspaces', and the account of those
 // that the batches hold (api.hip).
 bool batch_operands_fit(int dev, size_t bytes);

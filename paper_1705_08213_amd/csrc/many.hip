@@ -344,7 +344,10 @@ std::vector<unsigned char> make_key(const ccc_problem* probs, int n, const ccc_o
   memcpy(k.data() + off, &dev, sizeof(int));
   off += sizeof(int);
   // the choices can be forced from the environment; make them part of the key
-  for (const char* name : {"CCC_MANY_VARIANT", "CCC_MANY_WG", "CCC_OPERAND_LIMIT"}) {
+  const int64_t limit = operand_limit();
+  memcpy(k.data() + off, &limit, sizeof limit);
+  off += sizeof limit;
+  for (const char* name : {"CCC_MANY_VARIANT", "CCC_MANY_WG"}) {
     const char* env = getenv(name);
     const int forced = env ? atoi(env) + 1 : 0;
     memcpy(k.data() + off, &forced, sizeof(int));

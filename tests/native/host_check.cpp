@@ -344,6 +344,28 @@ int shared_counts() {
   return 0;
 }
 
+// A batch built under one operand limit is not replayed under another.
+int batch_limits() {
+  ccc_problem p{fk<uint8_t>(), 1000, 2000, ld_of(2000), fk<int32_t>(), fk<double>(), fk<int32_t>()};
+  auto built = [&](const char* limit) {  // launches of a build: -1 on operands, 1 on packed rows
+    if (limit)
+      setenv("CCC_OPERAND_LIMIT", limit, 1);
+    else
+      unsetenv("CCC_OPERAND_LIMIT");
+    launches.clear();
+    if (ccc_2way_many(&p, 1, nullptr, nullptr) != CCC_OK) return 9;
+    for (const Launch& l : launches)
+      if (is(l, "operands_many")) return -1;
+    return launches.empty() ? 0 : 1;
+  };
+  CHECK(built("0") == 1);
+  CHECK(built("17179869184") == -1);  // 2^34, 0 in 32 bits
+  CHECK(built("4294967296") == -1);
+  CHECK(built("0") == 0 && built("17179869184") == 0);  // replays
+  CHECK(built(nullptr) == 0);  // the default is 2^34
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -385,6 +407,7 @@ int main(int argc, char** argv) {
   if (what == "long_fields") r = long_fields();
   if (what == "row_ranges") r = row_ranges();
   if (what == "shared_counts") r = shared_counts();
+  if (what == "batch_limits") r = batch_limits();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

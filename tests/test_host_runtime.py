@@ -110,3 +110,8 @@ def test_blocks_with_shared_counts_add_one_side_after_the_other(host_check):
     """Two sides that share count entries are not added to by one launch, whose
     workgroups would race on them."""
     host_check("shared_counts")
+
+
+def test_batches_under_different_operand_limits(host_check):
+    """Limits that differ past 32 bits are different batches."""
+    host_check("batch_limits")
