@@ -348,6 +348,8 @@ struct TuneChoice {
 };
 // The one-shot variant that the environment forces (0 .. n_variants - 1), or -1.
 int tune_forced_oneshot(int n_variants);
+// Workgroups per field-split tile that the environment forces (1 .. 64), or -1.
+int tune_forced_split();
 // Shape of a 2-way call on operands by its 32 x 32 tiles and fields: 0 = 64 x
 // 128 staged tiles, 1 = field-split 32 x 32 tiles, 2 = 64 x 64 staged tiles
 // (mfma2.hip).  dense_ccc: a dense triangle with CCC rows; mixed: a selection or

@@ -3,8 +3,6 @@
 // (ccc_2way_block).  The tile bodies and their design notes are in tile2o.h
 // (fp4, on the operands of the pre-pass) and tile2.h (packed rows: int8, and
 // fp4 where the operands find no room).
-#include <stdlib.h>
-
 #include "tile2.h"
 #include "tile2o.h"
 
@@ -310,7 +308,7 @@ OperandShape operand_shape(const Pair2Args& a) {
     // (384 x 250007: 173 us with 1 split, 94 with 3, 83 with 6, 85 with 12;
     // 700 x 50000: 48, 44 with 2, 46 with 6; 700 x 5000: 18, 20 with 2).
     int64_t n = 512 / tiles < a.steps / 16 ? 512 / tiles : a.steps / 16;
-    if (const char* env = getenv("CCC_SPLIT")) n = atoi(env) < a.steps ? atoi(env) : a.steps;
+    if (const int forced = tune_forced_split(); forced > 0) n = forced < a.steps ? forced : a.steps;
     s.splits = n > 1 ? (int)n : 1;
   }
   return s;

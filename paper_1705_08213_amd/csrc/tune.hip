@@ -14,7 +14,10 @@
 // The table is read once from $CCC_TUNE_FILE, else from tune_gfx950.txt next
 // to the library.  A missing table or line gives variant 0.  For the
 // autotuner, $CCC_MANY_VARIANT and $CCC_MANY_WG force the batched choice and
-// $CCC_ONESHOT_VARIANT the one-shot one, on packed rows and on operands alike.
+// $CCC_ONESHOT_VARIANT the one-shot one, on packed rows and on operands alike;
+// $CCC_SPLIT (1 .. 64) forces how many workgroups share a field-split tile on
+// operands, whose partial sums then take 16 KB a workgroup.  Values that are
+// not such whole numbers force nothing.
 #include <dlfcn.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -91,6 +94,8 @@ static int env_int(const char* name, int lo, int hi) {
 int tune_forced_oneshot(int n_variants) {
   return env_int("CCC_ONESHOT_VARIANT", 0, n_variants - 1);
 }
+
+int tune_forced_split() { return env_int("CCC_SPLIT", 1, 64); }
 
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants) {
   TuneChoice c{0, 0};

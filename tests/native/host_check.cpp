@@ -366,6 +366,26 @@ int batch_limits() {
   return 0;
 }
 
+// CCC_SPLIT forces whole numbers in its range and nothing else.
+int forced_splits() {
+  auto workgroups = [](const char* split) -> int64_t {
+    if (split)
+      setenv("CCC_SPLIT", split, 1);
+    else
+      unsetenv("CCC_SPLIT");
+    launches.clear();
+    if (two_way(384, 250000) != CCC_OK) return -1;
+    for (const Launch& l : launches)
+      if (is(l, "mfma2_split_kernel")) return l.grid.x;
+    return -2;
+  };
+  const int64_t tiles = 78, own = workgroups(nullptr);
+  CHECK(own == tiles * 6);
+  CHECK(workgroups("1") == tiles && workgroups("3") == tiles * 3 && workgroups("64") == tiles * 64);
+  for (const char* bad : {"", "0", "-3", "65", "1000000", "3x", "abc"}) CHECK(workgroups(bad) == own);
+  return 0;
+}
+
 // Over all streams and batches the library holds at most 16 GiB of operands.
 int held() {
   const size_t limit = size_t(16) << 30, rest = size_t(64) << 20;
@@ -408,6 +428,7 @@ int main(int argc, char** argv) {
   if (what == "row_ranges") r = row_ranges();
   if (what == "shared_counts") r = shared_counts();
   if (what == "batch_limits") r = batch_limits();
+  if (what == "forced_splits") r = forced_splits();
   if (r == 2) printf("no such scenario\n");
   if (r == 0) printf("ok\n");
   return r;

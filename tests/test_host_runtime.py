@@ -115,3 +115,9 @@ def test_blocks_with_shared_counts_add_one_side_after_the_other(host_check):
 def test_batches_under_different_operand_limits(host_check):
     """Limits that differ past 32 bits are different batches."""
     host_check("batch_limits")
+
+
+def test_forced_splits(host_check):
+    """The environment's split of a tile's fields takes 1 to 64 and ignores
+    anything else."""
+    host_check("forced_splits")
