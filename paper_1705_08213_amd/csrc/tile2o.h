@@ -154,10 +154,10 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 // addresses; callers wait themselves (ring_loop).  It has no output register,
 // and its inputs are read as it issues.
 __device__ __forceinline__ void copy_async(gbytes base, uint32_t off, uint32_t dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
-               : "s"(dst), "v"(off), "s"(base)
-               : "memory", "m0");
+               : "v"(off), "s"(base), "{m0}"(dst)
+               : "memory");
 }
 
 // Steps 0 .. n - 1 of a workgroup of four waves whose ND pieces of 1 KB per
