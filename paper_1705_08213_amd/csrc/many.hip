@@ -123,7 +123,8 @@ __global__ __launch_bounds__(512) void operands_many_kernel(const ProbDesc* __re
   s.n = p.n_v;
   s.z = p.z;
   s.counts = p.counts;
-  operand_block(job, s, block - p.block_begin, 0);
+  __shared__ int part[16][16][2];
+  operand_block<true>(job, s, block - p.block_begin, 0, part);
 }
 
 __device__ __forceinline__ Pair2Args pair_args(const ProbDesc& p, double gamma) {

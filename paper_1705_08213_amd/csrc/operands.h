@@ -44,9 +44,11 @@ __device__ __forceinline__ void put_counts(const OperandJob& job, const OperandS
 }
 
 // Share `share` of block b of 16 rows of set s, by the whole workgroup (up to
-// 16 waves, which take the share's super-steps in turn).
+// 16 waves, which take the share's super-steps in turn).  LAY: not of a block
+// before s.first, which is only counted.
+template <bool LAY>
 __device__ __forceinline__ void operand_block(const OperandJob& job, const OperandSet& s,
-                                              int64_t b, int share) {
+                                              int64_t b, int share, int (*part)[16][2]) {
   const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
   const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   const int64_t n_f = job.n_f, row = 16 * b + rl;
@@ -54,8 +56,7 @@ __device__ __forceinline__ void operand_block(const OperandJob& job, const Opera
   const int64_t end = job.steps * (share + 1) / job.shares;
   const bool have = row < s.n;
   const uint8_t* p = s.v + (have ? row : s.n - 1) * s.ld + 16 * g;
-  const bool lay = b >= s.first;  // uniform
-  u4* z = reinterpret_cast<u4*>(s.z) + (lay ? b - s.first : 0) * job.steps * 64 + lane;
+  u4* z = reinterpret_cast<u4*>(s.z) + (b - s.first) * job.steps * 64 + lane;
   int n1 = 0, miss = 0;
   auto put = [&](int64_t st, const u4& x) {
     u4 o;
@@ -67,7 +68,7 @@ __device__ __forceinline__ void operand_block(const OperandJob& job, const Opera
       miss += __popc(ms);
       o[q] = c;
     }
-    if (lay) z[st * 64] = o;
+    if constexpr (LAY) z[st * 64] = o;
   };
   const u4 none = u4{0u, 0u, 0u, 0u};
   const int64_t whole = n_f / 256, nfull = end < whole ? end : whole;
@@ -112,7 +113,6 @@ __device__ __forceinline__ void operand_block(const OperandJob& job, const Opera
     n1 += __shfl_xor(n1, o);
     miss += __shfl_xor(miss, o);
   }
-  __shared__ int part[16][16][2];
   if (lane < 16) {
     part[wave][lane][0] = n1;
     part[wave][lane][1] = miss;

@@ -11,7 +11,13 @@ __global__ __launch_bounds__(1024) void operands_kernel(OperandJob job, int64_t 
   const int64_t b = base + blockIdx.x;
   if (job.zero && b == 0 && threadIdx.x == 0) *job.zero = 0ull;
   const bool second = b >= job.set[0].blocks;
-  operand_block(job, job.set[second ? 1 : 0], b - (second ? job.set[0].blocks : 0), blockIdx.y);
+  const OperandSet& s = job.set[second ? 1 : 0];
+  const int64_t block = b - (second ? job.set[0].blocks : 0);
+  __shared__ int part[16][16][2];
+  if (block >= s.first)  // uniform
+    operand_block<true>(job, s, block, blockIdx.y, part);
+  else
+    operand_block<false>(job, s, block, blockIdx.y, part);
 }
 
 // The counts of a pass in several shares.
