@@ -351,8 +351,8 @@ int tune_forced_oneshot(int n_variants);
 // Workgroups per field-split tile that the environment forces (1 .. 64), or -1.
 int tune_forced_split();
 // Shape of a 2-way call on operands by its 32 x 32 tiles and fields: 0 = 64 x
-// 128 staged tiles, 1 = field-split 32 x 32 tiles, 2 = 64 x 64 staged tiles
-// (mfma2.hip).  dense_ccc: a dense triangle with CCC rows; mixed: a selection or
+// 128 staged tiles, 1 = field-split 32 x 32 tiles, 2 = 64 x 64 staged tiles, 3 =
+// packed rows (mfma2.hip).  dense_ccc: a dense triangle with CCC rows; mixed: a selection or
 // an accumulating call.
 int operand_variant(int64_t tiles, int64_t n_f, bool dense_ccc, bool mixed);
 TuneChoice tune_pick(int kind, int64_t n_v, int64_t n_f, int n_variants);
@@ -376,14 +376,9 @@ hipError_t launch_operands(OperandJob job, hipStream_t stream);
 // First 16-row block that the tiles of a triangle's rows from i_begin on read:
 // no tile is larger than 256 rows.
 inline int64_t operand_first(int64_t i_begin) { return i_begin / 256 * 16; }
-// Whether a 2-way call (or `tiles` 32 x 32 tiles of a batch's problem) is to run
-// on operands.  Past kStagedMaxFields fields only the field-split tiles keep
-// their sums exact there, and many of those read the operands too often: from
-// 3000 tiles on the packed rows are faster (ms, operands / packed rows: 2000
-// rows x 1,900,000 6.8 / 11.2, complete data 5.1 / 9.0; 3000 rows 13.9 / 15.6,
-// complete 13.4 / 9.1; 12000 x 4,000,000 500 / 365, complete 567 / 156).
+// Whether a 2-way call has a use for operands (an accumulating one whose tiles
+// would all read the packed rows has not).
 bool operands_serve(const Pair2Args& a);
-bool operands_serve(int64_t tiles, int64_t n_f);
 // Most operands that the library holds on a device (api.hip).
 int64_t operand_limit();
 // Room for a batch's operands beside the workspaces', and the account of those

@@ -593,7 +593,7 @@ int run_many(const ccc_problem* probs, int n_probs, const ccc_opts& opts, bool f
     bool serve = f4 && opts.path != CCC_PATH_POPCOUNT;
     for (int p = 0; p < n_probs; ++p) {
       op_bytes += operand_bytes(probs[p].n_v, probs[p].n_f);
-      serve = serve && operands_serve(small_tiles(probs[p].n_v), probs[p].n_f);
+      serve = serve && operand_variant(small_tiles(probs[p].n_v), probs[p].n_f, true, false) != 3;
     }
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;

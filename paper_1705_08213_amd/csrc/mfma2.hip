@@ -282,7 +282,8 @@ hipError_t launch_f(const Pair2Args& a, hipStream_t stream) {
 }
 
 // Shapes on operands: 0 = 64 x 128 staged tiles, 1 = field-split 32 x 32
-// tiles, 2 = 64 x 64 staged tiles.
+// tiles, 2 = 64 x 64 staged tiles, 3 = the packed rows' kernel (the
+// complete-data kernel on operands all the same).
 struct OperandShape {
   int variant;
   int splits;  // workgroups per tile (variant 1)
@@ -356,8 +357,9 @@ hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
       if (stream_tables(a)) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
     if (hipError_t e = launch_tiles(kernel, n, a, stream, tm, tn); e != hipSuccess) return e;
   }
-  return s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)
-                        : launch_operand_shape<OUT, 2, 4, 2>(a, stream);
+  return s.variant == 3   ? launch_general<true>(a, stream)
+         : s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)
+                          : launch_operand_shape<OUT, 2, 4, 2>(a, stream);
 }
 
 hipError_t launch_operands_out(const Pair2Args& a, hipStream_t stream) {
@@ -393,17 +395,22 @@ hipError_t launch_operands_out(const Pair2Args& a, hipStream_t stream) {
 // calls (`mixed`) keep the 64 x 64 tile for longer: 12000 x 12000 x 8192
 // accumulating 2418 / 1836 / 2061, selection 12000 x 8009 957 / 1000 (2 / 0).
 int operand_variant(int64_t tiles, int64_t n_f, bool dense_ccc, bool mixed) {
-  if (n_f > tile2::kStagedMaxFields) return 1;  // four waves' sums, each exact
+  // Past kStagedMaxFields fields the staged tiles' sums are not exact.  Those of
+  // the field-split tiles are, each wave having a quarter of the fields, but
+  // many such tiles read the operands too often, while the packed rows' kernel
+  // and the one-plane tiles of complete data stay exact to kF4MaxFields (ms,
+  // field-split / packed: 2000 rows x 1,900,000 6.8 / 11.2, 3000 rows 13.9 /
+  // 15.6, 12000 x 4,000,000 500 / 365; complete data, field-split / packed /
+  // one-plane tiles on operands: 2000 x 1,900,000 5.1 / 9.0, 3000 x 1,900,000
+  // 13.4 / 9.1 / 7.5, 12000 x 4,000,000 567 / 156 / 119).
+  if (n_f > tile2::kStagedMaxFields) return tiles < 3000 ? 1 : 3;
   if (dense_ccc ? tiles < 6000 || n_f <= 1024 : tiles < 2500) return 1;
   return tiles < 50000 || (mixed && n_f < 16384) ? 2 : 0;
 }
 
-bool operands_serve(int64_t tiles, int64_t n_f) {
-  return n_f <= tile2::kStagedMaxFields || tiles < 3000;
-}
 bool operands_serve(const Pair2Args& a) {
   int64_t tm, tn;
-  return operands_serve(split_tiles(a, tm, tn), a.n_f);
+  return !a.accumulate || operand_variant(split_tiles(a, tm, tn), a.n_f, false, true) != 3;
 }
 
 size_t mfma2_part_bytes(const Pair2Args& a) {

@@ -281,14 +281,22 @@ int small_triples() {
   return 0;
 }
 
-// Where exact sums need the field-split tiles, large calls take the packed rows.
+// Where exact sums need the field-split tiles, large calls take the packed rows,
+// complete data its one-plane tiles on operands.
 int long_fields() {
   const int64_t most = 1864135;  // 9 n_f <= 2^24
   CHECK(two_way(8000, most) == CCC_OK && on_operands());
-  CHECK(two_way(8000, most + 1) == CCC_OK && !on_operands());
+  launches.clear();
+  CHECK(two_way(8000, most + 1) == CCC_OK && is(*last_tiles(), "12mfma2_kernel"));
+  bool one_plane = false;
+  for (const Launch& l : launches) one_plane |= is(l, "mfma2_complete_operand");
+  CHECK(one_plane);
   CHECK(two_way(2400, 4000000) == CCC_OK && on_operands() && is(*last_tiles(), "split"));
   CHECK(block(40, 8000, 2000000) == CCC_OK && on_operands());
-  CHECK(block(4000, 4000, 2000000) == CCC_OK && !on_operands());
+  CHECK(block(4000, 4000, 2000000) == CCC_OK && is(*last_tiles(), "12mfma2_kernel"));
+  ccc_opts acc = ccc_default_opts();
+  acc.flags = CCC_ACCUMULATE;
+  CHECK(block(4000, 4000, 2000000, &acc) == CCC_OK && !on_operands());
   ccc_problem p{fk<uint8_t>(), 4000, 1900000, ld_of(1900000), fk<int32_t>(), fk<double>(),
                 fk<int32_t>()};
   launches.clear();

@@ -237,3 +237,26 @@ def test_blocks_whose_sides_share_counts(shift, limit, monkeypatch):
     times[:m] += 1
     times[shift:] += 1
     assert np.array_equal(host(counts), want * times[:, None])
+
+
+@pytest.mark.parametrize("complete", [False, True])
+def test_large_call_on_long_fields(complete):
+    """3000 tiles past the staged tiles' fields: the packed rows' kernel, or the
+    one-plane tiles of complete data with the largest sums (rows all 11)."""
+    n_f, n = STAGED_MOST + 1, 2480
+    base = _extremes(n_f, seed=16)
+    if complete:
+        base = np.ascontiguousarray(np.concatenate([
+            synth.constant([3, 3, 0, 1], n_f, seed=17),
+            synth.beta_hw(3, n_f, seed=18, missing=0.0)]))
+    k = base.shape[0]
+    say("2way long fields", complete)
+    big = dev(base)[dev((np.arange(n) % k).astype(np.int64))].contiguous()
+    t, c, _ = ccc.ccc_2way(big, n_f)
+    bt, bc = oracle.block(base, base, n_f)
+    bt, bc = bt.reshape(k, k, 4), bc.reshape(k, k, 4)
+    t, c = host(t), host(c)
+    for i in list(range(0, n - 1, 97)) + [31, 32, 63, 64, 127, 128, 255, 256, 2477, 2478]:
+        p, js = _pair0(n, i), np.arange(i + 1, n) % k
+        assert_tables_equal(t[p:p + n - 1 - i], bt[i % k][js])
+        assert_ccc_identical(c[p:p + n - 1 - i], bc[i % k][js])
