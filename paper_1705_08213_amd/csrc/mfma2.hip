@@ -163,7 +163,9 @@ using tile2::SplitSides;
 
 template <tile2::Out OUT>
 __global__ __launch_bounds__(256, 3) void mfma2_split_kernel(Pair2Args a, int64_t tiles_side,
-                                                             int64_t tiles_n, int splits) {
+                                                             int64_t tiles_n, int splits,
+                                                             int complete_only) {
+  if (complete_only && *a.flag == a.id) return;  // uniform: another kernel covers the call
   __shared__ v4i red[4][4][64];
   __shared__ SplitSides sides;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -323,11 +325,13 @@ hipError_t launch_operand_shape(const Pair2Args& a, hipStream_t stream) {
 }
 
 template <tile2::Out OUT>
-hipError_t launch_split(const Pair2Args& a, int splits, hipStream_t stream) {
+hipError_t launch_split(const Pair2Args& a, int splits, hipStream_t stream,
+                        bool complete_only = false) {
   int64_t tm, tn;
   const int64_t ntiles = split_tiles(a, tm, tn);
   const hipError_t e =
-      launch_tiles(mfma2_split_kernel<OUT>, ntiles * splits, a, stream, tm, tn, splits);
+      launch_tiles(mfma2_split_kernel<OUT>, ntiles * splits, a, stream, tm, tn, splits,
+                   complete_only ? 1 : 0);
   if (e != hipSuccess || splits == 1) return e;
   return launch_tiles(mfma2_split_finish_kernel<OUT>, ntiles, a, stream, tm, tn, splits);
 }
@@ -344,6 +348,21 @@ bool stream_tables(const Pair2Args& a) {
   return a.n_f >= (!a.tri && a.n_b % 4 == 0 ? 3000 : 12288);
 }
 
+// Whether complete data takes the 32 x 32 tiles where other data takes the
+// staged ones: as long as the 128 x 256 one-plane tiles are few, or short and
+// bound by CCC rows (us, complete data, 32 x 32 / 128 x 256 tiles: 1700 x 1700 x
+// 1000 38 / 48, x 9000 65 / 80, 2200 x 2200 x 4000 equal; selection 3000 x 1000 42 /
+// 48, 2400 x 16000 63 / 108, but 5000 x 1000 93 / 63; tables alone 2400 x 16000 60 /
+// 91, 3000 x 1000 38 / 33, 3200 x 16000 86 / 99; with CCC 6000 x 6000 x 1000 310 /
+// 362, x 2000 375 / 373, 4000 x 32000 x 1000 0.84 of the time, but 4096 x 50000 x 1000
+// 2306 / 1955 and 1000000 x 200 x 1000 2720 / 2135).
+bool complete_by_split(const Pair2Args& a, int64_t tiles) {
+  if (a.sel.count) return tiles < 6000;
+  if (!a.ccc) return tiles < 4000 || (tiles < 6000 && a.n_f > 8192);
+  return tiles < 6000 ||
+         (a.n_f <= 1024 && (a.tri || (a.n_a <= 65536 && a.n_b <= 40000)));
+}
+
 template <tile2::Out OUT>
 hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
   OperandShape s = operand_shape(a);
@@ -351,11 +370,17 @@ hipError_t launch_operand_kernels(Pair2Args a, hipStream_t stream) {
   if (s.variant == 1 && s.splits > 1 && mfma2_part_bytes(a) > a.part_bytes) s.splits = 1;
   if (s.variant == 1) return launch_split<OUT>(a, s.splits, stream);  // its tiles vote
   if constexpr (OUT != tile2::kAccumulate) {  // (whose counts are running totals)
-    const int64_t n = tile_grid<32 * kCOM, 32 * kCON>(a, tm, tn);
-    auto* kernel = mfma2_complete_operand_kernel<OUT, kCOM, kCON>;
-    if constexpr (OUT == tile2::kDense)
-      if (stream_tables(a)) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
-    if (hipError_t e = launch_tiles(kernel, n, a, stream, tm, tn); e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (complete_by_split(a, split_tiles(a, tm, tn))) {
+      e = launch_split<OUT>(a, 1, stream, true);
+    } else {
+      const int64_t n = tile_grid<32 * kCOM, 32 * kCON>(a, tm, tn);
+      auto* kernel = mfma2_complete_operand_kernel<OUT, kCOM, kCON>;
+      if constexpr (OUT == tile2::kDense)
+        if (stream_tables(a)) kernel = mfma2_complete_operand_kernel<tile2::kStream, kCOM, kCON>;
+      e = launch_tiles(kernel, n, a, stream, tm, tn);
+    }
+    if (e != hipSuccess) return e;
   }
   return s.variant == 3   ? launch_general<true>(a, stream)
          : s.variant == 2 ? launch_operand_shape<OUT, 2, 2, 4>(a, stream)

@@ -236,6 +236,25 @@ int shapes() {
   CHECK(block(8000, 8000, 256, &acc) == CCC_OK && staged64());
   CHECK(block(8000, 8000, 8192, &acc) == CCC_OK && staged64());
   CHECK(block(1500, 1500, 8192, &acc) == CCC_OK && split());
+  // beside the staged tiles, complete data's: 32 x 32 (1) or 128 x 256 (0)
+  auto small_complete = [&](int status) {
+    int one_plane = 0, small = 0;
+    for (const Launch& l : launches) {
+      one_plane += is(l, "mfma2_complete_operand");
+      small += is(l, "mfma2_split_kernel");
+    }
+    launches.clear();
+    return status != CCC_OK || one_plane + small != 1 ? -1 : small;
+  };
+  launches.clear();
+  CHECK(small_complete(block(1700, 1700, 1000, &fin)) == 1);
+  CHECK(small_complete(block(6000, 6000, 1000, &fin)) == 1);
+  CHECK(small_complete(block(6000, 6000, 2000, &fin)) == 0);
+  CHECK(small_complete(block(4096, 50000, 1000, &fin)) == 0);
+  CHECK(small_complete(block(6000, 6000, 1000)) == 0);  // tables alone
+  CHECK(small_complete(select2(3000, 8000)) == 1 && small_complete(select2(5000, 1000)) == 0);
+  CHECK(small_complete(select2(2400, 16000)) == 1);
+  CHECK(small_complete(tables(3000, 300)) == 0 && small_complete(tables(3000, 16000)) == 1);
   return 0;
 }
 
