@@ -67,6 +67,7 @@ def committed_traffic(kernel_sources, profile):
 
 
 MFMA2_SOURCES = ["paper_1705_08213_amd/csrc/mfma2.hip", "paper_1705_08213_amd/csrc/tile2o.h",
+                 "paper_1705_08213_amd/csrc/operands.h", "paper_1705_08213_amd/csrc/operands.hip",
                  "paper_1705_08213_amd/csrc/tile2.h",
                  "paper_1705_08213_amd/csrc/common.h", "paper_1705_08213_amd/csrc/kernels.h"]
 MULTI2_SOURCES = ["paper_1705_08213_amd/csrc/multi2.hip", "paper_1705_08213_amd/csrc/tile2o.h",
@@ -75,6 +76,13 @@ MULTI2_SOURCES = ["paper_1705_08213_amd/csrc/multi2.hip", "paper_1705_08213_amd/
 MFMA3_SOURCES = ["paper_1705_08213_amd/csrc/mfma3.hip", "paper_1705_08213_amd/csrc/tile3.h",
                  "paper_1705_08213_amd/csrc/tile2o.h", "paper_1705_08213_amd/csrc/tile2.h",
                  "paper_1705_08213_amd/csrc/common.h", "paper_1705_08213_amd/csrc/kernels.h"]
+
+
+def mfma2_kernel_name(fmt, complete):
+    """The kernel that does a large 2-way call's work: on fp4 the one on the
+    operands that operands_kernel lays out, on int8 the one on packed rows."""
+    return ("mfma2_complete_" if complete else "mfma2_") + (
+        "operand_kernel" if fmt == "fp4" else "kernel")
 
 
 def timing_query(lib, name):
@@ -251,8 +259,8 @@ def bench_2way(args, lib, n_v, n_f, missing, gen, path, workload):
                                # every row complete: the complete-data kernel does the
                                # work (the general one exits at once); kernel_ms is the
                                # HIP-event interval around the launcher's kernels
-                               kernel="mfma2_complete_kernel" if missing == 0.0
-                               else "mfma2_kernel", kernel_ms=kms, operands=fmt,
+                               kernel=mfma2_kernel_name(fmt, missing == 0.0), kernel_ms=kms,
+                               operands=fmt,
                                ops_per_comparison=2 if missing == 0.0 else 8)
         other = {"fp4": "int8", "int8": "fp4"}[fmt]
         if args.other_steps > 0 and mfma_format(n_f, other)[0] == other and (
@@ -405,7 +413,8 @@ def bench_multi(args, lib):
                              if fmt == "fp4" else None,
                              traffic_unit="bytes per launch (FETCH_SIZE+WRITE_SIZE, scaled)",
                              algorithmic_bytes=n_v * n_f + P * s * s * 12 + 32 * n_v,
-                             kernel="multi2_kernel", kernel_ms=kms,
+                             kernel="multi2_operand_kernel" if fmt == "fp4" else "multi2_kernel",
+                             kernel_ms=kms,
                              ops_per_comparison=int(2 * s * s)))
     if not args.no_cpu:
         import oracle
@@ -449,7 +458,8 @@ def bench_block(args, lib):
                 config=dict(workload="2-way block 16384 x 16384, n_f=131072 in 8 chunks of "
                                      "16384, Beta/HW, 2% missing", path="mfma", operands=fmt),
                 roofline=dict(bound="mfma", achieved=ach, peak=peak, unit="TFLOP/s",
-                              frac=ach / peak, traffic=None, kernel="mfma2_kernel",
+                              frac=ach / peak, traffic=None,
+                              kernel=mfma2_kernel_name(fmt, False),
                               kernel_ms=kms, operands=fmt))
     if not args.no_cpu:
         import oracle
@@ -507,8 +517,12 @@ def bench_many(args, lib):
                 roofline=dict(bound="mfma", achieved=8.0 * comps / (kms / 1e3) / 1e12,
                               peak=peak, unit="TFLOP/s",
                               frac=8.0 * comps / (kms / 1e3) / 1e12 / peak,
-                              traffic=None, kernel="graph replay (count + persistent tally "
-                                                   "launches)", kernel_ms=kms, operands=fmt),
+                              traffic=None,
+                              kernel="graph replay (" + (
+                                  "operands_many_kernel, many_staged_kernel, many_split_kernel"
+                                  if fmt == "fp4" else
+                                  "count_many_kernel, many_mfma_kernel") + ")",
+                              kernel_ms=kms, operands=fmt),
                 graph=dict(setup_ms=setup_ms, first_call_ms=first_ms,
                            note="setup_ms: host time of the work list, its upload, graph "
                                 "capture and instantiation on first sight of the batch; "

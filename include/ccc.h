@@ -254,12 +254,14 @@ typedef struct {
 
 /*
  * ccc_2way_many -- many independent 2-way problems of uneven n_v and n_f in
- * one persistent launch.  `probs` is a HOST array of n_probs descriptors
- * (device pointers inside).  Each problem gives exactly what ccc_2way would.
- * The launch sequence is captured once into a HIP graph per distinct batch
- * (same descriptors) and replayed on later calls with that batch; a batch
- * keeps its fp4 operands (up to 2 GiB, else it reads the packed rows) as long
- * as its graph, of which the library keeps eight.
+ * one call.  `probs` is a HOST array of n_probs descriptors (device pointers
+ * inside).  Each problem gives exactly what ccc_2way would.  The launch
+ * sequence is captured once into a HIP graph per distinct batch (same
+ * descriptors) and replayed on later calls with that batch, which the caller
+ * orders (they write the same outputs).  On fp4 operands it is one pass over
+ * the rows and a workgroup per tile, else a count pass and persistent launches.
+ * A batch keeps its operands (up to 2 GiB, within the bound above) as long as
+ * its graph, of which the library keeps eight.
  * Validation covers every problem before anything is enqueued.
  */
 int ccc_2way_many(const ccc_problem* probs, int n_probs, const ccc_opts* opts,

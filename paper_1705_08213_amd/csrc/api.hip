@@ -284,15 +284,14 @@ int workspace(size_t bytes, size_t op_bytes, hipStream_t stream,
                                  [&](const Workspace& w) { return gone_here(w) && !w.ptr && !w.ops; }),
                   list->end());
   }
-  size_t at = g_ws.size();
-  std::vector<uint64_t> used;  // last uses of the other streams'
-  for (size_t i = 0; i < g_ws.size(); ++i) {
-    const Workspace& w = g_ws[i];
-    if (w.dev != dev) continue;
-    if (w.stream == stream && w.thread == thread && w.capture == capture) at = i;
-    else if (!w.capture) used.push_back(w.last_use);
-  }
+  size_t at = 0;
+  while (at < g_ws.size() && !(g_ws[at].dev == dev && g_ws[at].stream == stream &&
+                               g_ws[at].thread == thread && g_ws[at].capture == capture))
+    ++at;
   if (at == g_ws.size()) {
+    std::vector<uint64_t> used;  // last uses of the other streams'
+    for (const Workspace& w : g_ws)
+      if (w.dev == dev && !w.capture) used.push_back(w.last_use);
     if (used.size() >= kMaxWorkspaces && !capture && wait_for_device()) {
       std::nth_element(used.begin(), used.begin() + used.size() / 2, used.end());
       const uint64_t median = used[used.size() / 2];

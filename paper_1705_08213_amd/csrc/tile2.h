@@ -72,7 +72,8 @@ __device__ __forceinline__ void emit_pair_staged(const Pair2Args& a, bool valid,
   valid = valid && i >= a.row_begin && i < a.row_end;
   const int lane = threadIdx.x & 63, g = lane >> 4, rl = lane & 15;
   const int64_t p = valid ? (a.tri ? pair_index(a.n_a, i, j) : i * a.n_b + j) - a.p_base : 0;
-  // streaming stores: the dense output is written once and not read back here
+  // plain stores for the tables (L2 joins the ends of the rows' stretches, which
+  // start anywhere in a line), streaming ones for the CCC rows below
   if (valid && a.tables)
     *reinterpret_cast<v4i*>(a.tables + 4 * p) = t;
   if (!a.ccc) return;

@@ -1,6 +1,6 @@
 // tile2o.h -- 2-way tally tiles on fp4 operands that the pre-pass has laid out
 // (operands.h): device bodies of the one-shot kernels (mfma2.hip) and the
-// persistent batched ones (many.hip).
+// batched ones (many.hip).
 //
 // A tile needs the four sums of the planes W = rho(1) + 3 [missing], the
 // 2-bit code of the layout as it lies, and M = [missing]:
