@@ -54,7 +54,7 @@ constexpr int64_t kOperandLimit = int64_t(16) << 30;
 // executables are destroyed, which a user object of the graph tells (`gone`).
 // What such an executable last launched may still run, so the buffers are
 // freed behind a wait, by a later eager call that finds more than kMaxGone of
-// them or runs out of memory.
+// them, or more than kMaxGoneBytes, or runs out of memory.
 struct Workspace {
   int dev = 0;
   hipStream_t stream = nullptr;
@@ -67,7 +67,7 @@ struct Workspace {
   size_t ops_bytes = 0;
   uint64_t last_use = 0;
 };
-constexpr int kMaxGone = 8;
+constexpr size_t kMaxGone = 8, kMaxGoneBytes = size_t(1) << 30;
 // Workspaces of eager calls per device.  A framework's stream pool has 32
 // streams; one past the bound waits for the device and gives back the half that
 // was used longest ago, so that a program which makes streams without end waits
@@ -276,8 +276,14 @@ int workspace(size_t bytes, size_t op_bytes, hipStream_t stream,
   const unsigned long long capture = capture_id(stream);
   lock = std::unique_lock<std::mutex>(g_mu);
   auto gone_here = [&](const Workspace& w) { return w.dev == dev && is_gone(w); };
-  if (!capture && std::count_if(g_ws.begin(), g_ws.end(), gone_here) > kMaxGone &&
-      wait_for_device()) {
+  size_t gone = 0, gone_bytes = 0;
+  for (auto* list : {&g_ws, &g_retired})
+    for (const Workspace& w : *list)
+      if (gone_here(w)) {
+        ++gone;
+        gone_bytes += w.bytes + w.ops_bytes;
+      }
+  if (!capture && (gone > kMaxGone || gone_bytes > kMaxGoneBytes) && wait_for_device()) {
     free_buffers(dev, is_gone);
     for (auto* list : {&g_ws, &g_retired})
       list->erase(std::remove_if(list->begin(), list->end(),

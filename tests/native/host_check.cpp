@@ -437,6 +437,16 @@ int held() {
     CHECK(ccc_2way_many(p.data(), 1, nullptr, nullptr) == CCC_OK);
   }
   CHECK(used > size_t(5) << 30);  // operands again
+  // what a graph held is free again soon after it is gone
+  ccc_release_workspace();
+  for (unsigned long long id = 200; id < 203; ++id) {
+    capture[stream(1)] = id;
+    CHECK(two_way(65536, 300000, stream(1)) == CCC_OK && on_operands());  // 4.9 GB each
+    capture.clear();
+  }
+  CHECK(two_way(65536, 300000, stream(2)) == CCC_OK && !on_operands());
+  destroy_graph(201);
+  CHECK(two_way(65536, 300000, stream(2)) == CCC_OK && on_operands());
   return 0;
 }
 
