@@ -580,7 +580,7 @@ constexpr int kMultiPieces = S > 2 ? 2 : 1;
 // The fp4 form on operands: the packed kernel's tiles and sums; copies are 1 KB
 // contiguous, an operand takes 1.9 VALU operations per MFMA instead of 5.3
 // (s = 4), and the rows' values leave through LDS.  Bound by its output, the
-// matrix cores 40% busy at 16384 fields.  s = 4: 4096 x 16384 1.50 ms from the
+// matrix cores 50% busy at 4096 x 16384 and 61% at 16384 x 32768.  s = 4: 4096 x 16384 1.50 ms from the
 // one-byte rows, 0.97 here; 16384 x 32768 38.9-39.2 and 26.0.
 template <int S>
 __global__ __launch_bounds__(256, 2) void multi2_operand_kernel(Multi2Args a, const void* z,

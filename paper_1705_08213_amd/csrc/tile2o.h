@@ -323,8 +323,9 @@ __device__ __forceinline__ void emit_blocks(const Pair2Args& a, const Sides<NR, 
 
 // One workgroup's tile of (32 WM) x (32 WN) pairs at (I0, J0), 2 x 2 waves;
 // `stage` is its LDS (three buffers), reused for the epilogue's inputs.  Bound
-// by MFMA issue (matrix cores 65% busy over long fields, where power holds
-// the clock near 2.0 GHz), then by the output.  16384 x 32768: 6.50 ms from
+// by MFMA issue (matrix cores 69% busy at 16384 x 32768, where power holds the
+// clock at 2.03 GHz, 73% and 2.13 at 32768 x 65536), then by the output.
+// 16384 x 32768: 6.50 ms from
 // packed rows, 5.69 here; 32768 x 65536: 45.2-48.1 and 41.2.
 template <Out OUT, int WM, int WN>
 __device__ __forceinline__ void staged_tile(const Pair2Args& a, int64_t I0, int64_t J0,
