@@ -37,11 +37,12 @@ constexpr int64_t kGramMaxRows = 32768;
 // Most operands (operands.hip) that the library holds on a device, over all
 // its workspaces and batches; $CCC_OPERAND_LIMIT (bytes) overrides it.  They
 // also never take more than half of the memory that is free.  Where they find
-// no room the fp4 kernels read the packed rows, which is slower by a third at
-// most, while a wait for the device or another stream's buffers given back
-// and allocated again would cost milliseconds on every call of a card that is
-// nearly full.  The check is one query of the free memory (5 us), made only
-// when a buffer has to grow.
+// no room the fp4 kernels read the packed rows.  That takes large calls up to
+// 1.4 times as long (few rows of long fields, whose operands are small, up to
+// eight times), but a wait for the device and other streams' buffers given
+// back and allocated again would cost every call of a card that is nearly full
+// milliseconds, and hold up everyone else's.  The check is one query of the
+// free memory (5 us), made only when a buffer has to grow.
 constexpr int64_t kOperandLimit = int64_t(16) << 30;
 
 // Workspaces: one buffer per (device, stream) for eager calls, so that calls
